@@ -22,7 +22,8 @@
 // V^-1 D^-1 L^-1: the two triangular inverses in one dense n x n array, D^-1 in
 // a block-diagonal one.  The apply is then two triangular GEMVs (together one
 // pass over the array), a block-diagonal product and banded products, all
-// bound by HBM bandwidth.
+// bound by HBM bandwidth when formed from the stored blocks; the single-problem
+// FP64 apply forms the banded products from kernel tables (papply.hip).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -89,6 +90,12 @@ __global__ void k_diag_blocks(double *D11, double *D12, double *D22, int N, doub
 // through the point is exactly zero (its antiderivative term is then dropped);
 // a difference of separately rounded coordinates can leave a few ulp there, and
 // the logarithm of the near-zero argument that goes with it is not finite.
+// OFFSETS: the nodes' offsets from the point likewise from mesh indices, as the
+// tables of the single-problem FP64 apply hold them (here and in k_band_rows;
+// the Schur complement then belongs to the operator that the apply convolves
+// with: |P z - r| grew tenfold in the rows of block 2 without); otherwise from
+// rounded coordinates, a difference of 1e-14 relative next to the point.
+template <bool OFFSETS>
 __global__ __launch_bounds__(64) void k_k5_rowsum(double *rowsum, double *I5, int N, int M, double x1, double dx,
                                                   double y1, double dy, int nimg) {
     const int t = blockIdx.x;  // l (N-1) + k
@@ -101,7 +108,8 @@ __global__ __launch_bounds__(64) void k_k5_rowsum(double *rowsum, double *I5, in
         for (int n = lane; n < N * M; n += 64) {
             const int m = n / N, i = n - m * N;
             const double ci = (i == 0 || i == N - 1) ? 0.5 : 1.0, cm = (m == 0 || m == M - 1) ? 0.5 : 1.0;
-            const double s = x1 + i * dx - xs, tt = iota * (y1 + m * dy) - ys;
+            const double s = OFFSETS ? (i - k - 0.5) * dx : x1 + i * dx - xs;
+            const double tt = OFFSETS ? (img ? -(m + l) : m - l) * dy : iota * (y1 + m * dy) - ys;
             v += dx * dy * ci * cm / sqrt(s * s + tt * tt);
         }
     }
@@ -127,6 +135,7 @@ __global__ __launch_bounds__(64) void k_k5_rowsum(double *rowsum, double *I5, in
 // P31 (K7 on zeta_x) and P23 = P32 (K6 on the node values of a potential).
 // One wave per (l, band offset, k) row; zero rows 0, 1 (radiation) are left
 // from the initial clear.
+template <bool OFFSETS>
 __global__ __launch_bounds__(64) void k_band_rows(double *B21, double *B23, double *B31, const double *rowsum,
                                                   const double *I5, int N, int M, int h, double x1, double dx,
                                                   double y1, double dy, int nimg) {
@@ -155,9 +164,9 @@ __global__ __launch_bounds__(64) void k_band_rows(double *B21, double *B23, doub
         if (i < N) {
             const double ci = (i == 0 || i == N - 1) ? 0.5 : 1.0;
             const double w = dx * dy * ci * cm;
-            const double sx = x1 + i * dx - xs;
+            const double sx = OFFSETS ? (i - k - 0.5) * dx : x1 + i * dx - xs;
             for (int img = 0; img < nimg; ++img) {
-                const double tt = (img ? -1.0 : 1.0) * (y1 + m * dy) - ys;
+                const double tt = OFFSETS ? (img ? -(m + l) : m - l) * dy : (img ? -1.0 : 1.0) * (y1 + m * dy) - ys;
                 const double r2 = sx * sx + tt * tt;
                 k5 += w / sqrt(r2);
                 const double q = 1.0 / sqrt(r2 + 1.0);
@@ -292,6 +301,44 @@ static int precond_round_to_fp32(Precond *pc, hipStream_t st) {
     return rc;
 }
 
+// Tables, stacked slice blocks and scratch of the single-problem FP64 apply.
+static int precond_table_alloc(Precond *pc, const bim_problem *p) {
+    const int N = pc->N, M = pc->M, s = pc->s;
+    PcDesc &d = pc->d;
+    d.N = N;
+    d.M = M;
+    d.s = s;
+    d.h = pc->h;
+    d.half = p->half_domain ? 1 : 0;
+    d.chunks = pc_conv_chunks(N, M, pc->h);
+    d.n = pc->n;
+    d.dx = p->dx;
+    d.dy = p->dy;
+    const size_t nst = (size_t)(s + N) * s, nq = (size_t)M * N + kPcSourcePad, np = (size_t)d.chunks * M * (N - 1);
+    double *ETs, *tab, *corr;
+    struct {
+        double **p;
+        size_t elems;
+    } want[] = {{&ETs, nst}, {&tab, (size_t)3 * (2 * M - 1) * (N - 1)}, {&corr, (size_t)(N - 1) * M},
+                {&d.q1, nq},   {&d.q2, nq}, {&d.p1, np}, {&d.p2, np}};
+    size_t bytes = 0;
+    for (auto &w : want) bytes += (sizeof(double) * w.elems + 255) & ~(size_t)255;
+    const int rc = hip_check(hipMalloc(&pc->table_mem, bytes), "hipMalloc(preconditioner tables)");
+    if (rc) return rc;
+    pc->bytes += bytes;
+    DevArena ar{(char *)pc->table_mem, 0, bytes};
+    for (auto &w : want) *w.p = ar.take<double>(w.elems);
+    d.iD11 = pc->Dinv11;  // their first slice blocks
+    d.iD22 = pc->Dinv22;
+    d.ETs = ETs;
+    d.tab = tab;
+    d.corr = corr;
+    d.a1 = pc->scratch;
+    d.a3 = d.a1 + pc->n;
+    d.t2 = d.a3 + pc->n;
+    return BIM_OK;
+}
+
 int precond_build(const bim_problem *p, int hb, int storage, Precond **out, hipStream_t st) {
     const Dims d(p);
     const int N = d.N, M = d.M, s = N + 1;
@@ -334,6 +381,17 @@ int precond_build(const bim_problem *p, int hb, int storage, Precond **out, hipS
     pc->Sinv = ar.take<double>((size_t)n * n);
     pc->Uinv = ar.take<double>(band_elems(M, 0, s));
     pc->scratch = ar.take<double>((size_t)4 * n);
+    // Tables from 150 MB of stored bands on: below, reading the blocks takes no
+    // longer than the convolutions' launches and latencies (apply from blocks /
+    // from tables, half domains: 61 x 21, 23 MB: 41 / 63 us; 91 x 31, 92 MB: 54 /
+    // 72; 106 x 36, 172 MB: 110 / 79; 121 x 41, 293 MB: 122 / 90; 181 x 61, 1.36
+    // GB: 433 / 249; full 61 x 61, 158 MB: 76 / 75)
+    const bool tables = storage == BIM_STORE_FP64 && sizeof(double) * 4 * band_elems(M, h, s) >= (size_t)150000000;
+    pc->tables = tables;
+    if (tables && (rc = precond_table_alloc(pc, p))) {
+        precond_free(pc);
+        return rc;
+    }
 
     // setup-only scratch
     size_t tmp = 0;
@@ -361,8 +419,7 @@ int precond_build(const bim_problem *p, int hb, int storage, Precond **out, hipS
     void *tbase = nullptr;
     rc = hip_check(hipMallocAsync(&tbase, tmp, st), "hipMallocAsync(preconditioner setup)");
     if (rc) {
-        (void)hipFree(pc->mem);
-        delete pc;
+        precond_free(pc);
         return rc;
     }
     DevArena ta{(char *)tbase, 0, tmp};
@@ -453,11 +510,15 @@ int precond_build(const bim_problem *p, int hb, int storage, Precond **out, hipS
     // 2. band blocks of P21, P23 (= P32), P31
     for (double *b : {pc->B21, pc->B23, pc->B31})
         RUN(hip_check(hipMemsetAsync(b, 0, sizeof(double) * band_elems(M, h, s), st), "memset"));
-    hipLaunchKernelGGL(k_k5_rowsum, dim3(d.ntg), dim3(64), 0, st, rowsum, I5, N, M, p->x1, p->dx, p->y1, p->dy,
-                       d.nimg);
-    hipLaunchKernelGGL(k_band_rows, dim3(M * (2 * h + 1) * (N - 1)), dim3(64), 0, st, pc->B21, pc->B23, pc->B31,
-                       rowsum, I5, N, M, h, p->x1, p->dx, p->y1, p->dy, d.nimg);
+    const auto rowsums = tables ? k_k5_rowsum<true> : k_k5_rowsum<false>;
+    const auto band_rows = tables ? k_band_rows<true> : k_band_rows<false>;
+    hipLaunchKernelGGL(rowsums, dim3(d.ntg), dim3(64), 0, st, rowsum, I5, N, M, p->x1, p->dx, p->y1, p->dy, d.nimg);
+    hipLaunchKernelGGL(band_rows, dim3(M * (2 * h + 1) * (N - 1)), dim3(64), 0, st, pc->B21, pc->B23, pc->B31, rowsum,
+                       I5, N, M, h, p->x1, p->dx, p->y1, p->dy, d.nimg);
     RUN(hip_check(hipGetLastError(), "band assembly launch"));
+    if (tables)
+        RUN(pc_tables_enqueue(const_cast<double *>(pc->d.tab), rowsum, I5, const_cast<double *>(pc->d.corr), N, M,
+                              p->dx, p->dy, st));
 
     {
         // E (one block) then replicated
@@ -537,6 +598,7 @@ int precond_build(const bim_problem *p, int hb, int storage, Precond **out, hipS
         RUN(run_op(ops[0], st));
         hipLaunchKernelGGL(k_replicate, dim3(cdiv((long)M * s * s, 256)), dim3(256), 0, st, rowtmp, pc->E, M,
                            (long)s * s);
+        if (tables) RUN(pc_stack_enqueue(rowtmp, const_cast<double *>(pc->d.ETs), N, p->dx, st));
         // T := B23 ; S := 0 with D22 on the diagonal
         RUN(copy2d_enqueue(pc->B23, 1, T, 1, 1, (int)band_elems(M, h, s), st));
         RUN(hip_check(hipMemsetAsync(S, 0, sizeof(double) * band_elems(M, w2, s), st), "memset"));
@@ -696,16 +758,16 @@ int precond_build(const bim_problem *p, int hb, int storage, Precond **out, hipS
     if (!rc && storage == BIM_STORE_FP32 && pc->storage != BIM_STORE_FP32) rc = precond_round_to_fp32(pc, st);
     if (rc) {
         (void)hipStreamSynchronize(st);
-        (void)hipFree(pc->mem);
-        delete pc;
+        precond_free(pc);
         return rc;
     }
     *out = pc;
     return BIM_OK;
 }
 
+// The apply from the stored blocks.
 template <typename T>
-static int precond_apply_impl(const Precond *pc, const PrecondArrays<const T> &a, const double *r, double *z,
+static int precond_apply_blocks(const Precond *pc, const PrecondArrays<const T> &a, const double *r, double *z,
                               hipStream_t st) {
     const int M = pc->M, s = pc->s, h = pc->h;
     const long n = pc->n;
@@ -730,11 +792,24 @@ int precond_apply_enqueue(const Precond *pc, const double *r, double *z, hipStre
     if (pc->storage == BIM_STORE_FP32) {
         const PrecondArrays<const float> a{pc->f32.Dinv11, pc->f32.Dinv22, pc->f32.E,    pc->f32.B21, pc->f32.B23,
                                            pc->f32.B31,    pc->f32.G,      pc->f32.Sinv, pc->f32.Uinv};
-        return precond_apply_impl(pc, a, r, z, st);
+        return precond_apply_blocks(pc, a, r, z, st);
     }
-    const PrecondArrays<const double> a{pc->Dinv11, pc->Dinv22, pc->E,    pc->B21, pc->B23,
-                                        pc->B31,    pc->G,      pc->Sinv, pc->Uinv};
-    return precond_apply_impl(pc, a, r, z, st);
+    if (!pc->tables) {
+        const PrecondArrays<const double> a{pc->Dinv11, pc->Dinv22, pc->E,    pc->B21, pc->B23,
+                                            pc->B31,    pc->G,      pc->Sinv, pc->Uinv};
+        return precond_apply_blocks(pc, a, r, z, st);
+    }
+    PcDesc d = pc->d;
+    d.r = r;
+    d.z = z;
+    double *t3 = d.t2 + d.n;
+    int rc = pc_before_schur(d, st);
+    if (rc) return rc;
+    // z2 = V^-1 D^-1 L^-1 t2
+    if ((rc = gemv_tri_enqueue(pc->Sinv, d.n, d.M, d.s, 1, d.t2, d.t2, t3, 1.0, 1.0, st))) return rc;
+    if ((rc = bandmv_enqueue(pc->Uinv, d.M, 0, d.s, t3, nullptr, d.t2, 1.0, 0.0, st))) return rc;
+    if ((rc = gemv_tri_enqueue(pc->Sinv, d.n, d.M, d.s, 2, d.t2, d.t2, z + d.n, 1.0, 1.0, st))) return rc;
+    return pc_after_schur(d, st);
 }
 
 const void *precond_array(const Precond *pc, int which) {
@@ -756,6 +831,7 @@ const void *precond_array(const Precond *pc, int which) {
 void precond_free(Precond *pc) {
     if (!pc) return;
     if (pc->mem) (void)hipFree(pc->mem);
+    if (pc->table_mem) (void)hipFree(pc->table_mem);
     delete pc;
 }
 

@@ -186,3 +186,30 @@ def test_precond_full_domain_with_offset_edges(bim):
         print(f"full {N}x{M} |Pz - r| / |r|", np.abs(res).max() / np.abs(r).max())
         assert np.abs(res).max() <= 1e-9 * np.abs(r).max()
         P.close()
+
+
+# The FP64 apply with table-formed banded products (stored bands of 150 MB and more): 1 to 4
+# targets per lane, one and two blocks of targets, odd and even s, a slice longer than one
+# table window (N > 512), half and full domains, at the working mesh's spacing of 1/3.
+# P z = r by the oracle's banded product; the bound is that of the other full-size checks here.
+# For s > 192 it holds for the rows of block 2 (the Schur complement's, where the products'
+# errors meet): there the slice blocks' 2 x 2 block inverses, which leave 1e-8 to 6e-8 in the
+# rows of blocks 1 and 3, have no part.
+@pytest.mark.parametrize("N,M,half", [(65, 61, False), (120, 41, True), (129, 41, True), (181, 31, False),
+                                      (257, 21, True), (300, 21, True), (600, 5, True)])
+def test_table_formed_apply_solves_banded_system(bim, N, M, half):
+    x, y = (N - 1) / 6.0, (M - 1) / 3.0
+    p = W.make_problem(N, M, -x, x, 0.0 if half else -y, y, 1.2, [W.Bump(0.2, 1.0, 1.0)], half_domain=half)
+    dp = bim.DeviceProblem(p)
+    P = bim.Preconditioner(dp)
+    assert 4 * 8 * M * (2 * P.band + 1) * (N + 1) ** 2 >= 150e6
+    r = np.random.default_rng(9).standard_normal(p.n_unknowns)
+    z = P.apply(torch.as_tensor(r, device="cuda"))
+    torch.cuda.synchronize()
+    res = Lin.banded_matvec(p, z.cpu().numpy(), P.band) - r
+    nb = (N + 1) * M
+    blocks = [np.abs(res[b * nb:(b + 1) * nb]).max() / np.abs(r).max() for b in range(3)]
+    print(f"{N}x{M} |Pz - r| / |r| by block", blocks)
+    assert blocks[1] <= 1e-9
+    assert max(blocks) <= 1e-9 or N + 1 > 192
+    P.close()
