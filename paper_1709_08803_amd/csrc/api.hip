@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "bim_common.h"
+#include "precond.h"
 #include "vec.h"
 
 namespace bim {
@@ -108,10 +109,15 @@ static int residual_call(const bim_problem *prob, const double *u, double *F, in
     const PairLaunch pl = pair_launch_for(prob, prec);
     std::lock_guard<std::mutex> lock(g_ws_mutex);
     void *ws = nullptr;
-    if ((rc = stream_workspace(s, residual_work_bytes(d, pl), &ws))) return rc;
+    // (the tables of the linear sums in every size, so that any evaluation leaves a
+    // workspace for a captured one of the same mesh)
+    const bool conv = linear && prec == BIM_FP64;
+    if ((rc = stream_workspace(s, residual_work_bytes(d, pl) + lin_table_bytes(d), &ws))) return rc;
     ResidualWork w;
     residual_work_carve(ws, d, pl, &w);
-    return residual_enqueue(prob, u, F, prec, pl, w, s, nullptr, linear);
+    double *tab = conv ? (double *)((char *)ws + w.bytes) : nullptr;
+    if (conv && (rc = kernel_tables_enqueue(tab, d.N, d.M, prob->dx, prob->dy, s))) return rc;
+    return residual_enqueue(prob, u, F, prec, pl, w, s, nullptr, linear, tab);
 }
 
 int bim_residual(const bim_problem *prob, const double *u, double *F, int prec, void *stream) {

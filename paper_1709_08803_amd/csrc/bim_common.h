@@ -131,10 +131,19 @@ void residual_work_carve(void *base, const Dims &d, const PairLaunch &pl, Residu
 
 // Enqueues F = F(u) using a caller-provided workspace (no allocation).
 // ev_pair (optional): two events recorded right before and after the all-pairs launch.
-// linear = 1 evaluates the linearised residual F_lin of Section 4.2 instead.
+// linear = 1 evaluates the linearised residual F_lin of Section 4.2 instead;
+// lin_tables (FP64, linear): the kernel tables of the mesh (lin_table_bytes, filled
+// by kernel_tables_enqueue), with which its sums are formed as convolutions
+// instead of pair by pair.
 int residual_enqueue(const bim_problem *p, const double *u, double *F, int prec,
                      const PairLaunch &pl, const ResidualWork &w, hipStream_t s,
-                     hipEvent_t *ev_pair = nullptr, int linear = 0);
+                     hipEvent_t *ev_pair = nullptr, int linear = 0, const double *lin_tables = nullptr);
+
+// The convolution form of the linear sums (linconv.hip): bytes of its tables, its
+// source chunks (at most `most`), and its launch (D.chunks chunks into D.part).
+size_t lin_table_bytes(const Dims &d);
+int lin_conv_chunks(const Dims &d, int most);
+int lin_conv_enqueue(const PairDesc &D, const double *tables, hipStream_t s);
 
 // Enqueues F_i = F(u_i) for `count` problems whose all-pairs sums share one
 // persistent launch.  pls[i] must have the same tpl/unroll for every i; ws[i]

@@ -115,6 +115,7 @@ struct Krylov {
     // Jacobian action of the current Newton point
     const double *u = nullptr, *Fin = nullptr;
     int prec = BIM_FP64, linear = 0;
+    const double *lin_tab = nullptr;  // FP64 linear products: the mesh's kernel tables
     double eps = 0;
 
     int jv(const double *z, double *out) {
@@ -126,7 +127,8 @@ struct Krylov {
             return rc;
         }
         if ((rc = axpy_dev_enqueue(u, z, scal + 2, ut, n, s))) return rc;
-        if ((rc = residual_enqueue(p, ut, Ft, prec, prec == BIM_FP64 ? pl64 : pl32, rw, s, nullptr, linear)))
+        if ((rc = residual_enqueue(p, ut, Ft, prec, prec == BIM_FP64 ? pl64 : pl32, rw, s, nullptr, linear,
+                                   lin_tab)))
             return rc;
         return quotient_enqueue(Ft, Fin, scal + 2, out, n, s);
     }
@@ -319,6 +321,8 @@ int solve_impl(const bim_problem *p, const bim_precond *P, double *u_io, const b
     bytes += vb * ((size_t)(m + 1) + m + 8);                        // V, Z, w, ut, Ft, r, x, F, Fin, delta
     bytes += al256(sizeof(double) * (size_t)reduce_parts() * (m + 1));  // part
     bytes += al256(sizeof(double) * 3 * (m + 1)) + al256(sizeof(double) * 8) + al256(sizeof(double) * (m + 1));
+    const bool lin_conv = linear_start_only && o->inner_prec == BIM_FP64;
+    if (lin_conv) bytes += lin_table_bytes(d);
     Workspace ws;
     ws.s = s;
     int rc = hip_check(hipMallocAsync(&ws.mem, bytes, s), "hipMallocAsync(jfnk)");
@@ -403,8 +407,14 @@ int solve_impl(const bim_problem *p, const bim_precond *P, double *u_io, const b
         // u_lin = u0 - J~^-1 F_lin(u0): one linear solve with the exact linear operator
         if ((rc = uniform_stream_enqueue(u_io, d.N, d.M, p->x1, s))) return rc;
         // (with inner_prec BIM_FP32C the operator's products use FP32C sums, the
-        // base point included, and the right-hand side stays FP64)
-        if ((rc = residual_enqueue(p, u_io, F, BIM_FP64, pl64, K.rw, s, nullptr, 1))) return rc;
+        // base point included, and the right-hand side stays FP64, summed pair by
+        // pair as they are; FP64 products are convolutions with the mesh's tables)
+        if (lin_conv) {
+            double *tab = take(lin_table_bytes(d));
+            if ((rc = kernel_tables_enqueue(tab, d.N, d.M, p->dx, p->dy, s))) return rc;
+            K.lin_tab = tab;
+        }
+        if ((rc = residual_enqueue(p, u_io, F, BIM_FP64, pl64, K.rw, s, nullptr, 1, K.lin_tab))) return rc;
         if ((rc = axpby_enqueue(-1.0, F, 0.0, nullptr, rhs, n, s))) return rc;
         K.u = u_io;
         K.Fin = F;

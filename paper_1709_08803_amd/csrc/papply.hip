@@ -13,7 +13,7 @@
 // another 0.34 GB for G = P33^-1 (P32 - P31 E)), and products with the stored
 // blocks are bound by reading them (250 of the 422 us of an apply at 181 x 61).
 // Formed from the tables the same products read a few MB and are bound by FP64
-// FMAs, LDS reads and launches: 422 -> 245 us per apply at 181 x 61, of which
+// FMAs, LDS reads and launches: 422 -> 244 us per apply at 181 x 61, of which
 // 172 us are the two triangular products of the Schur inverse.  The tables
 // hold the exact mesh offsets, where the blocks were formed from rounded node
 // coordinates (a difference of 1e-14 relative next to the target).  (The lockstep
@@ -60,7 +60,7 @@ inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 // one, so a lane reads one new entry per node and table and keeps the other
 // R - 1 in registers (R FMAs per LDS read; with one target per lane the LDS
 // reads bound the loop).  The weighted sources are uniform: scalar loads, the
-// next two batches in flight during the current one.  The four waves' sums are added in
+// next batch in flight during the current one.  The four waves' sums are added in
 // LDS and the chunks' by the reader, in a fixed order.
 // Nodes per scalar-load batch (a multiple of R): 12, with two sources half of it,
 // as the current and the next batch of both fill the scalar registers.
@@ -92,7 +92,6 @@ __global__ __launch_bounds__(256) void k_pc_conv(PcDesc D) {
     const int c = b % D.chunks, rest = b / D.chunks;
     const int kb = rest % kbs, l = rest / kbs;
     if (l >= M) return;  // uniform in the workgroup
-    __shared__ double red[3][NA * R][64];
     const int LT = conv_window(N, R);
     double *tw = tabs + (size_t)wave * NT * LT;
     // table order: mode 0: K7, K5; mode 1: K6; mode 2: K6, K7
@@ -152,65 +151,66 @@ __global__ __launch_bounds__(256) void k_pc_conv(PcDesc D) {
         for (int q = 0; q < NT; ++q)
 #pragma unroll
             for (int x = 1; x < R; ++x) old[q][x] = tl[q * LT - x];
-        // the sources of this batch and of the next two (loads past the piece read
-        // the spare entries; the values are not used)
-        double cur[NQ][KB], nx1[NQ][KB], nx2[NQ][KB];
-#pragma unroll
-        for (int j = 0; j < KB; ++j) {
-            cur[0][j] = s1[j];
-            nx1[0][j] = s1[KB + j];
-            if (NQ == 2) {
-                cur[NQ - 1][j] = s2[j];
-                nx1[NQ - 1][j] = s2[KB + j];
-            }
-        }
-        for (int i = 0; i < len; i += KB) {
+        // A batch: its table entries and sources, loaded during the batch before (both
+        // count on the wave's one LDS and scalar-load counter, so one wait at the
+        // hand-over covers them; loads past the piece read spare entries, not used).
+        struct Batch {
+            double t[NT][KB], s[NQ][KB];
+        };
+        auto fetch = [&](Batch &b, int i) {
+            i = min(i, len - 1);
 #pragma unroll
             for (int j = 0; j < KB; ++j) {
-                nx2[0][j] = s1[i + 2 * KB + j];
-                if (NQ == 2) nx2[NQ - 1][j] = s2[i + 2 * KB + j];
+                b.s[0][j] = s1[i + j];
+                if (NQ == 2) b.s[NQ - 1][j] = s2[i + j];
             }
+#pragma unroll
+            for (int q = 0; q < NT; ++q)
+#pragma unroll
+                for (int j = 0; j < KB; ++j) b.t[q][j] = tl[q * LT + i + j];
+        };
+        auto batch = [&](Batch &b, Batch &next, int i) {
+            fetch(next, i + KB);
             if (i + KB > len) {  // nodes past the piece count zero
 #pragma unroll
                 for (int j = 0; j < KB; ++j)
 #pragma unroll
-                    for (int q = 0; q < NQ; ++q) cur[q][j] = i + j < len ? cur[q][j] : 0.0;
+                    for (int q = 0; q < NQ; ++q) b.s[q][j] = i + j < len ? b.s[q][j] : 0.0;
             }
-            __builtin_amdgcn_sched_barrier(0);
-            double tb[NT][KB];  // the batch's table entries, all in flight together
-#pragma unroll
-            for (int q = 0; q < NT; ++q)
-#pragma unroll
-                for (int j = 0; j < KB; ++j) tb[q][j] = tl[q * LT + i + j];
+            __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the FMAs
 #pragma unroll
             for (int g = 0; g < KB; g += R) {
 #pragma unroll
                 for (int j = 0; j < R; ++j)
 #pragma unroll
                     for (int r = 0; r < R; ++r) {
-                        const double v0 = j >= r ? tb[0][j >= r ? g + j - r : 0] : old[0][j >= r ? 0 : r - j];
-                        acc[0][r] = fma(v0, cur[0][g + j], acc[0][r]);
+                        const double v0 = j >= r ? b.t[0][j >= r ? g + j - r : 0] : old[0][j >= r ? 0 : r - j];
+                        acc[0][r] = fma(v0, b.s[0][g + j], acc[0][r]);
                         if (NT == 2) {
-                            const double v1 = j >= r ? tb[NT - 1][j >= r ? g + j - r : 0] : old[NT - 1][j >= r ? 0 : r - j];
-                            if (MODE == 0) acc[NA - 1][r] = fma(v1, cur[0][g + j], acc[NA - 1][r]);
-                            else acc[0][r] = fma(-v1, cur[NQ - 1][g + j], acc[0][r]);
+                            const double v1 =
+                                j >= r ? b.t[NT - 1][j >= r ? g + j - r : 0] : old[NT - 1][j >= r ? 0 : r - j];
+                            if (MODE == 0) acc[NA - 1][r] = fma(v1, b.s[0][g + j], acc[NA - 1][r]);
+                            else acc[0][r] = fma(-v1, b.s[NQ - 1][g + j], acc[0][r]);
                         }
                     }
 #pragma unroll
                 for (int q = 0; q < NT; ++q)
 #pragma unroll
-                    for (int x = 1; x < R; ++x) old[q][x] = tb[q][g + R - x];
+                    for (int x = 1; x < R; ++x) old[q][x] = b.t[q][g + R - x];
             }
-#pragma unroll
-            for (int j = 0; j < KB; ++j)
-#pragma unroll
-                for (int q = 0; q < NQ; ++q) {
-                    cur[q][j] = nx1[q][j];
-                    nx1[q][j] = nx2[q][j];
-                }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        Batch b0, b1;
+        fetch(b0, 0);
+        for (int i = 0; i < len; i += 2 * KB) {
+            batch(b0, b1, i);
+            if (i + KB < len) batch(b1, b0, i + KB);
         }
         __builtin_amdgcn_wave_barrier();  // the next piece overwrites the window
     }
+    // the four waves' sums through the windows' memory (no longer read)
+    __syncthreads();
+    double(*red)[NA * R][64] = reinterpret_cast<double(*)[NA * R][64]>(conv_lds);
     if (wave > 0) {
 #pragma unroll
         for (int a = 0; a < NA; ++a)
@@ -432,7 +432,9 @@ template <int MODE>
 int conv_launch(const PcDesc &D, hipStream_t st) {
     const int R = pc_conv_targets(D.N);
     const dim3 grid(D.M * cdiv(D.N - 1, 64 * R) * D.chunks);
-    const size_t lds = sizeof(double) * 4 * (MODE == 1 ? 1 : 2) * conv_window(D.N, R);
+    // the windows; at least the reduction's 3 R x 64 values per accumulator
+    const size_t lds =
+        sizeof(double) * std::max(4 * (MODE == 1 ? 1 : 2) * conv_window(D.N, R), 3 * (MODE == 0 ? 2 : 1) * R * 64);
     switch (R) {
         case 1: hipLaunchKernelGGL((k_pc_conv<MODE, 1>), grid, dim3(256), lds, st, D); break;
         case 2: hipLaunchKernelGGL((k_pc_conv<MODE, 2>), grid, dim3(256), lds, st, D); break;
@@ -475,11 +477,14 @@ int pc_after_schur(const PcDesc &D, hipStream_t st) {
     return hip_check(hipGetLastError(), "preconditioner apply launch");
 }
 
-int pc_tables_enqueue(double *tab, const double *rowsum, const double *I5, double *corr, int N, int M, double dx,
-                      double dy, hipStream_t st) {
+int kernel_tables_enqueue(double *tab, int N, int M, double dx, double dy, hipStream_t st) {
     hipLaunchKernelGGL(k_pc_tables, dim3(cdiv((2L * M - 1) * (N - 1), 256)), dim3(256), 0, st, tab, N, M, dx, dy);
+    return hip_check(hipGetLastError(), "kernel tables launch");
+}
+
+int pc_corr_enqueue(const double *rowsum, const double *I5, double *corr, int N, int M, hipStream_t st) {
     hipLaunchKernelGGL(k_pc_corr, dim3(cdiv((long)(N - 1) * M, 256)), dim3(256), 0, st, rowsum, I5, corr, (N - 1) * M);
-    return hip_check(hipGetLastError(), "preconditioner tables launch");
+    return hip_check(hipGetLastError(), "preconditioner correction launch");
 }
 
 int pc_stack_enqueue(const double *A, double *out, int N, double dx, hipStream_t st) {

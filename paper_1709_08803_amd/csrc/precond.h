@@ -67,9 +67,11 @@ const void *precond_array(const Precond *pc, int which);
 int pc_before_schur(const PcDesc &d, hipStream_t st);
 int pc_after_schur(const PcDesc &d, hipStream_t st);
 int pc_conv_chunks(int N, int M, int h);
-// Setup: the kernel tables and the halved K5 correction; [A; T].
-int pc_tables_enqueue(double *tab, const double *rowsum, const double *I5, double *corr, int N, int M, double dx,
-                      double dy, hipStream_t st);
+// tab[3][2M - 1][N - 1]: K5 = 1/r, K6 = (r^2 + 1)^(-3/2), K7 = (r^2 + 1)^(-1/2) at the
+// mesh offsets ((e + 1/2) dx, o dy).
+int kernel_tables_enqueue(double *tab, int N, int M, double dx, double dy, hipStream_t st);
+// Setup: the halved K5 correction; [A; T].
+int pc_corr_enqueue(const double *rowsum, const double *I5, double *corr, int N, int M, hipStream_t st);
 int pc_stack_enqueue(const double *A, double *out, int N, double dx, hipStream_t st);
 
 }  // namespace bim

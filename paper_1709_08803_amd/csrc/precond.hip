@@ -516,9 +516,10 @@ int precond_build(const bim_problem *p, int hb, int storage, Precond **out, hipS
     hipLaunchKernelGGL(band_rows, dim3(M * (2 * h + 1) * (N - 1)), dim3(64), 0, st, pc->B21, pc->B23, pc->B31, rowsum,
                        I5, N, M, h, p->x1, p->dx, p->y1, p->dy, d.nimg);
     RUN(hip_check(hipGetLastError(), "band assembly launch"));
-    if (tables)
-        RUN(pc_tables_enqueue(const_cast<double *>(pc->d.tab), rowsum, I5, const_cast<double *>(pc->d.corr), N, M,
-                              p->dx, p->dy, st));
+    if (tables) {
+        RUN(kernel_tables_enqueue(const_cast<double *>(pc->d.tab), N, M, p->dx, p->dy, st));
+        RUN(pc_corr_enqueue(rowsum, I5, const_cast<double *>(pc->d.corr), N, M, st));
+    }
 
     {
         // E (one block) then replicated

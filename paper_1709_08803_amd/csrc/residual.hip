@@ -872,10 +872,12 @@ PairDesc make_desc(const bim_problem *p, const Dims &d, const PairLaunch &pl, co
 }  // namespace
 
 int residual_enqueue(const bim_problem *p, const double *u, double *F, int prec, const PairLaunch &pl,
-                     const ResidualWork &w, hipStream_t s, hipEvent_t *ev_pair, int linear) {
+                     const ResidualWork &w, hipStream_t s, hipEvent_t *ev_pair, int linear,
+                     const double *lin_tables) {
     const Dims d(p);
     const int N = d.N, M = d.M;
-    const PairDesc D = make_desc(p, d, pl, w, u, F, prec, linear);
+    PairDesc D = make_desc(p, d, pl, w, u, F, prec, linear);
+    if (lin_tables) D.chunks = lin_conv_chunks(d, pl.chunks);
     hipLaunchKernelGGL(k_integrate, dim3(3 * M), dim3(64), 0, s, D);
     if (prec == BIM_FP64)
         hipLaunchKernelGGL(k_records<double>, dim3(record_blocks(N, M)), dim3(256), 0, s, D);
@@ -888,7 +890,9 @@ int residual_enqueue(const bim_problem *p, const double *u, double *F, int prec,
                        p->y1, p->dx, p->dy, pl.tiles_per_bnd, pl.row_groups, pl.target_tiles, pl.chunks, \
                        w.part)
     const int vsel = (pl.tpl == 2 ? 3 : 0) + (pl.unroll == 2 ? 0 : pl.unroll == 4 ? 1 : 2);
-    if (linear) {
+    if (lin_tables) {
+        if (int rc = lin_conv_enqueue(D, lin_tables, s)) return rc;
+    } else if (linear) {
         // the same source chunks (the partial-sum buffer and the finalize use
         // pl.chunks), one target row per lane and the default unroll
         const PairLaunch ll = pair_launch(d, 1, prec == BIM_FP64 ? 4 : 2, pl.chunks);

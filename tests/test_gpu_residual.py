@@ -302,3 +302,22 @@ def test_linear_residual_matches_oracle(bim, name, mk, seed, prec, tol):
     err = np.abs(F.cpu().numpy() - F_ref) / scale
     print(name, prec, "linear residual max rel err", err.max())
     assert err.max() <= tol
+
+
+# The FP64 linear sums are convolutions with kernel tables: R = 1 .. 4 targets per lane (N - 1
+# at and past multiples of 64), two blocks of targets, slices of more than one table window
+# (N > 256), the smallest mesh, one and several source chunks, both domains
+@pytest.mark.parametrize("N,M,half", [(3, 3, True), (65, 3, True), (66, 5, False), (129, 4, True), (130, 3, False),
+                                      (193, 3, True), (194, 3, True), (257, 3, False), (300, 3, True)])
+def test_linear_convolutions_match_oracle(bim, N, M, half):
+    from oracle import linear as Lin
+    x, y = (N - 1) / 6.0, (M - 1) / 3.0
+    p = W.make_problem(N, M, -x, x, 0.0 if half else -y, y, 0.8, [W.Bump(0.2, 1.1, 0.9, cx=0.3)], half_domain=half)
+    u = W.perturbed_state(p, 3)
+    F_ref = Lin.F_lin(p, u)
+    scale = R.term_magnitude_rows(p, u)
+    F = bim.residual_linear(bim.DeviceProblem(p), torch.as_tensor(u, device="cuda"))
+    torch.cuda.synchronize()
+    err = (np.abs(F.cpu().numpy() - F_ref) / scale).max()
+    print(f"{N}x{M}", err)
+    assert err <= 1e-12
