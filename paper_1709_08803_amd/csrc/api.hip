@@ -323,7 +323,7 @@ extern "C" int bim_residual_batched(const bim_problem *probs, int count, const d
     int big = 0;
     for (int i = 1; i < count; ++i)
         if ((long)probs[i].N * probs[i].M > (long)probs[big].N * probs[big].M) big = i;
-    const PairLaunch ref = pair_launch_for(&probs[big], prec);
+    const PairLaunch ref = pair_launch_batch(&probs[big], prec);
     std::vector<PairLaunch> pls(count);
     std::vector<ResidualWork> ws(count);
     size_t total = 0;

@@ -65,6 +65,7 @@ struct PairLaunch {
     int src_rows;        // 2 M source-row visits (both images of a row in one visit)
     int chunks;          // source chunks, 1 .. 2 M N
     int blocks;          // workgroups of 4 waves
+    bool s2_with_pairs = false;  // FP64: S2 sums pair by pair in the pair sums' loop
 };
 // tpl/unroll outside the supported set fall back to 1/4; chunks is clamped to
 // [1, 2 M N].
@@ -77,6 +78,12 @@ int chunks_for_waves(const Dims &d, int tpl, int unroll, long want_waves);
 // The launch used by the public entry points: the autotuned choice for this
 // (mesh, precision) if bim_tune_residual has run, else the default.
 PairLaunch pair_launch_for(const bim_problem *p, int prec);
+// The same for the kernels that form the S2 sums with the pairs: a batch's, and the
+// FP64 residuals of a solve whose inner iterations are FP32C.  Such a solve answers
+// a rounding difference of 1e-14 in the outer residual with 1e-9 in its solution, so
+// the single solve and the lockstep one share that arithmetic; it evaluates
+// the outer residual a handful of times (181 x 61: 0.1 ms of 75 each).
+PairLaunch pair_launch_batch(const bim_problem *p, int prec);
 // Chunks giving every work item about pairs_target pairs per collocation
 // point (node ranges of pairs_target / nimg nodes), to even out work items
 // across the meshes of a batch.

@@ -314,14 +314,15 @@ int solve_impl(const bim_problem *p, const bim_precond *P, double *u_io, const b
     K.n = n;
     K.m = m;
     // one workspace sized for the larger chunk count of the two precisions
-    const PairLaunch pl64 = pair_launch_for(p, BIM_FP64), pl32 = pair_launch_for(p, BIM_FP32C);
+    const bool lin_conv = linear_start_only && o->inner_prec == BIM_FP64;
+    const PairLaunch pl64 = o->inner_prec == BIM_FP64 ? pair_launch_for(p, BIM_FP64) : pair_launch_batch(p, BIM_FP64);
+    const PairLaunch pl32 = pair_launch_for(p, BIM_FP32C);
     PairLaunch plw = pl64.chunks >= pl32.chunks ? pl64 : pl32;
     size_t bytes = residual_work_bytes(d, plw);
     const size_t vb = al256(sizeof(double) * n);
     bytes += vb * ((size_t)(m + 1) + m + 8);                        // V, Z, w, ut, Ft, r, x, F, Fin, delta
     bytes += al256(sizeof(double) * (size_t)reduce_parts() * (m + 1));  // part
     bytes += al256(sizeof(double) * 3 * (m + 1)) + al256(sizeof(double) * 8) + al256(sizeof(double) * (m + 1));
-    const bool lin_conv = linear_start_only && o->inner_prec == BIM_FP64;
     if (lin_conv) bytes += lin_table_bytes(d);
     Workspace ws;
     ws.s = s;

@@ -109,7 +109,7 @@ int solve_batched_impl(const bim_problem *probs, int count, bim_precond *const *
     int big = 0;
     for (int i = 1; i < count; ++i)
         if ((long)probs[i].N * probs[i].M > (long)probs[big].N * probs[big].M) big = i;
-    const PairLaunch ref = pair_launch_for(&probs[big], o->inner_prec);
+    const PairLaunch ref = pair_launch_batch(&probs[big], o->inner_prec);
     // memory: per problem residual workspace + Krylov vectors; shared staging
     std::vector<size_t> off(count);
     size_t bytes = 0;

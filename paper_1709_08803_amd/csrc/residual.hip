@@ -28,6 +28,8 @@ namespace {
 
 constexpr double kTwoPi = 6.283185307179586476925286766559;
 
+inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
+
 // ------------------------------------------------------------------ rsqrt
 // FP32: the hardware reciprocal square root (about 1 ulp).
 __device__ __forceinline__ float rsq(float x) { return __builtin_amdgcn_rsqf(x); }
@@ -228,6 +230,106 @@ __global__ __launch_bounds__(256) void k_records_batched(const PairDesc *__restr
     records_body<T>(D, blockIdx.x - D.blk_rec);
 }
 
+// ------------------------------------------------------------------ A1 and records in one launch
+// Inclusive scan over a wave of 64 in DPP steps (shifts within rows of 16 lanes,
+// then the row broadcasts): about a tenth of the latency of six FP64 shuffles.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, ROWS, 0xf, false);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, ROWS, 0xf, false);
+    return v + __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ double wave_scan(double v) {
+    v = dpp_add<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);  // lane 15 of each row to the next (rows 1, 3)
+    return dpp_add<0x143, 0xc>(v);  // lane 31 to rows 2, 3
+}
+
+// FP64, one problem: what k_integrate and k_records do, one workgroup per mesh row
+// l.  Its y-differences need the node values of three rows of zeta and phi; each
+// workgroup integrates those (7 slices with psi's) into LDS itself, which takes less
+// than a second launch (bound by latency; 31 x 11: 2.8 + 3.9 -> 5.0 us; 181 x 61: 5.1 + 5.5 ->
+// 9.3 us, and the gap between the launches).
+__global__ __launch_bounds__(256) void k_prepare64(PairDesc D) {
+    extern __shared__ double val[];  // [7][N]: zeta and phi on rows base .. base + 2, psi on row l
+    const int N = D.N, M = D.M, l = blockIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int base = l == 0 ? 0 : l == M - 1 ? M - 3 : l - 1, here = l - base;
+    const double dx = D.dx, hdx = 0.5 * D.dx;
+    for (int q = wave; q < 7; q += 4) {
+        const int f = q < 3 ? 0 : q < 6 ? 1 : 2, j = q < 6 ? base + q % 3 : l;
+        const double *s = D.u + ((size_t)f * M + j) * (N + 1);
+        double carry = s[0];
+        for (int b0 = 0; b0 < N; b0 += 64) {
+            const int i = b0 + lane;
+            const double v = wave_scan((i > 0 && i < N) ? hdx * (s[i] + s[i + 1]) : 0.0);
+            if (i < N) {
+                val[q * N + i] = carry + v;
+                if (q == here || q == 3 + here || q == 6) D.nodes[((size_t)f * M + l) * N + i] = carry + v;
+            }
+            carry += __shfl(v, 63, 64);
+        }
+    }
+    __syncthreads();
+    // y-derivative at node i of the rows from q0: as ddy
+    const double inv2 = 0.5 / D.dy;
+    auto dydiff = [&](int q0, int i) {
+        const double a = val[q0 * N + i], b = val[(q0 + 1) * N + i], c = val[(q0 + 2) * N + i];
+        if (l > 0 && l < M - 1) return (c - a) * inv2;
+        if (l == M - 1) return (3.0 * c - 4.0 * b + a) * inv2;
+        return D.half ? 0.0 : (-3.0 * a + 4.0 * b - c) * inv2;
+    };
+    const double *zeta = val + here * N, *phi = val + (3 + here) * N, *psi = val + 6 * N;
+    const double *zx = D.u + (size_t)l * (N + 1) + 1;
+    const size_t nl = (size_t)l * N;
+    const double *beta = D.beta + nl, *beta_x = D.beta_x + nl, *beta_y = D.beta_y + nl;
+    const bool linear = D.linear;  // the planes z = 0 and z = -1; the layer densities are unchanged
+    for (int i = threadIdx.x; i < N; i += 256) {
+        const double zy = dydiff(0, i);
+        D.ydiv[nl + i] = zy;
+        D.ydiv[(size_t)N * M + nl + i] = dydiff(3, i);
+        const double x = D.x1 + i * dx;
+        const double w = dx * D.dy * ((i == 0 || i == N - 1) ? 0.5 : 1.0) * ((l == 0 || l == M - 1) ? 0.5 : 1.0);
+        ((SrcRec<double> *)D.srcS)[nl + i] = {x,  linear ? 0.0 : zeta[i], linear ? 0.0 : zx[i], linear ? 0.0 : zy,
+                                              w * (phi[i] - x), w * zx[i], w, 0.0};
+        // bottom: outward normal points down, so both layers enter with -w
+        ((SrcRec<double> *)D.srcB)[nl + i] = {x,  linear ? -1.0 : beta[i], linear ? 0.0 : beta_x[i],
+                                              linear ? 0.0 : beta_y[i], -w * (psi[i] - x), -w * beta_x[i], -w, 0.0};
+    }
+    const size_t ntg = (size_t)(N - 1) * M, T2 = 2 * ntg;
+    const double ys = D.y1 + l * D.dy;
+    for (int e = threadIdx.x; e < 2 * (N - 1); e += 256) {
+        const int st = e >= N - 1, k = e - st * (N - 1);
+        const size_t t = st * ntg + (size_t)l * (N - 1) + k;
+        const double xs = D.x1 + (k + 0.5) * dx;
+        double d, Dst, ax, ay, sig;
+        if (st == 0) {
+            d = 0.5 * (zeta[k] + zeta[k + 1]);
+            Dst = 0.5 * (phi[k] + phi[k + 1]) - xs;
+            ax = 0.5 * (zx[k] + zx[k + 1]);
+            ay = 0.5 * (dydiff(0, k) + dydiff(0, k + 1));
+            sig = ax;
+        } else {
+            d = 0.5 * (beta[k] + beta[k + 1]);
+            Dst = 0.5 * (psi[k] + psi[k + 1]) - xs;
+            ax = 0.5 * (beta_x[k] + beta_x[k + 1]);
+            ay = 0.5 * (beta_y[k] + beta_y[k + 1]);
+            sig = -ax;
+        }
+        if (linear) {
+            d = st ? -1.0 : 0.0;
+            ax = ay = 0.0;
+        }
+        const double v[8] = {xs, ys, d, Dst, 1.0 + ax * ax, 2.0 * ax * ay, 1.0 + ay * ay, sig};
+        for (int q = 0; q < 8; ++q) D.tg64[q * T2 + t] = v[q];
+    }
+}
+constexpr size_t kPrepareLds = 64 << 10;  // rows of up to 1170 nodes; longer ones take the two launches
+
 // ------------------------------------------------------------------ A2: all-pairs sums (hot loop)
 // The sums read through address-space qualified pointers.  Per-lane arrays are
 // global memory.  Node records are read-only for a whole launch; the batched
@@ -395,7 +497,9 @@ __device__ __forceinline__ void row_end(TargetState<T, NI> &g) {
 // w sigma / R, and the S2 radicand is exactly s^2 + t^2; on the other plane the
 // numerator is exactly the plane separation.  The LIN bodies drop those zero
 // terms and give bit-identical sums.
-template <typename T, bool COMP, int TPL, int UNROLL, int NI, bool CREC, bool LIN = false>
+// S2SUM: the item also forms the S2 sum (and writes both sums per target); without
+// it, the single-problem FP64 sums, whose S2 sums s2_item forms.
+template <typename T, bool COMP, int TPL, int UNROLL, int NI, bool CREC, bool LIN = false, bool S2SUM = true>
 __device__ __forceinline__ void pair_item(const SrcRec<T> *__restrict__ srcS, const SrcRec<T> *__restrict__ srcB,
                                           const T *__restrict__ tg, const double *__restrict__ tg64, int N, int M,
                                           double y1, double dx, double dy, int tiles_per_bnd, int row_groups,
@@ -502,7 +606,7 @@ __device__ __forceinline__ void pair_item(const SrcRec<T> *__restrict__ srcS, co
 #pragma unroll
                     for (int i = 0; i < NI; ++i) {
                         ri[q][i] = rsq((NI == 2) ? base + e.t2[i] : fma(dz, dz, base));
-                        rq[q][i] = rsq(fma(s, fma(e.A, s, e.Bt[i]), e.Ct2[i]));
+                        if constexpr (S2SUM) rq[q][i] = rsq(fma(s, fma(e.A, s, e.Bt[i]), e.Ct2[i]));
                     }
                 }
                 return [&, p, nb0, coef, ri, rq]() {
@@ -514,7 +618,7 @@ __device__ __forceinline__ void pair_item(const SrcRec<T> *__restrict__ srcS, co
                             const T num = fma(-e.ti[i], p.zy, nb0[q]);
                             const T bsum = fma(coef[q] * num, ri[q][i] * ri[q][i], p.ws);
                             e.acc[a] = fma(bsum, ri[q][i], e.acc[a]);
-                            e.acc2[a] = fma(p.w, rq[q][i], e.acc2[a]);
+                            if constexpr (S2SUM) e.acc2[a] = fma(p.w, rq[q][i], e.acc2[a]);
                         }
                     }
                 };
@@ -548,13 +652,17 @@ __device__ __forceinline__ void pair_item(const SrcRec<T> *__restrict__ srcS, co
             });
         }
 #pragma unroll
-        for (int q = 0; q < TPL; ++q) row_end<T, COMP, NI>(ts[q]);
+        for (int q = 0; q < TPL; ++q) row_end<T, COMP, NI, S2SUM>(ts[q]);
     }
 #pragma unroll
     for (int q = 0; q < TPL; ++q) {
         const int l = lg * TPL + q;
         if (valid && l < M) {
             const int tid = st * ntg + l * (N - 1) + k;
+            if constexpr (!S2SUM) {
+                ((GlobalPtr<double>)part)[(size_t)c * T2 + tid] = ts[q].sum;
+                continue;
+            }
             const GlobalPtr<double> o = (GlobalPtr<double>)part + ((size_t)c * T2 + tid) * 2;
             o[0] = (double)ts[q].sum + (double)ts[q].comp;
             o[1] = ((double)ts[q].s2sum + (double)ts[q].s2comp) * ((sizeof(T) == 4) ? dx : 1.0);
@@ -602,6 +710,287 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<T
                                                     row_groups, chunks, part, tt, c, lane);
 }
 
+// ------------------------------------------------------------------ S2 sums in FP64
+// The trapezoidal sum of w S2 over every node and image, S2 = (A s^2 + B s t + C
+// t^2)^(-1/2), depends on a target's (A, B, C) and its mesh indices only, and away
+// from the target a row of it is its integral plus Euler-Maclaurin corrections at
+// the ends:
+//   sum' f(s_i) dx = int f ds + sum_m B_2m / (2m)! dx^2m [f^(2m-1)]
+// up to e^(-2 pi eta / dx), eta the distance of f's branch points s_c +- i eta from
+// the real axis (s_c = -B t / 2A, eta = |t| sqrt(4AC - B^2) / 2A), and the
+// derivatives of Q^(-1/2) are Legendre polynomials:
+//   f^(n) = n! P_n(c) (A/Q)^(n/2) Q^(-1/2),  c = -(2As + Bt) / (2 sqrt(A Q)).
+// In units of dx, a row with eta >= 8 takes its two ends, any other row also the
+// nodes within sqrt(8^2 - eta^2) of s_c one by one (about 200 of them in all rows),
+// with a segment of the corrected integral on each side: every end then lies 8 or
+// more from the branch points (or the sum runs to the mesh edge node by node), where
+// six corrections leave 1e-13 of one end's term and 1.5e-15 of the sum, and three
+// suffice from 32 on.  The segments' integrals are (1/sqrt A) ln of a ratio; a
+// wave multiplies the ratios of 16 rows before it takes a logarithm.
+// A target costs about 15 thousand FP64 instructions instead of the 220 thousand of
+// its 22082 pairs at 181 x 61 (all-pairs launch 613 -> S2TIME us).
+constexpr double kS2Reach = 8.0;   // node-by-node distance, in dx
+constexpr int kS2Flush = 16;       // rows per logarithm (their product stays in range)
+constexpr int kS2Chunks = 16;      // most row chunks per tile of targets (rows c, c + chunks, ..)
+
+// Closed form of the integral of (A s^2 + B s t + C t^2)^(-1/2) over a rectangle
+// from the antiderivative of Section 3.1; a term with a zero prefactor is its
+// limit, zero.
+__device__ double s2_antideriv(double A, double B, double C, double s, double t) {
+    const double Q = A * s * s + B * s * t + C * t * t;
+    double g = 0.0;
+    if (t != 0.0) g += t / sqrt(A) * log(2.0 * A * s + B * t + 2.0 * sqrt(A * Q));
+    if (s != 0.0) g += s / sqrt(C) * log(2.0 * C * t + B * s + 2.0 * sqrt(C * Q));
+    return g;
+}
+
+// The same without the cancellation in the logarithm: with p = 2 A s + B t and
+// q = 2 sqrt(A Q), q^2 - p^2 = (4 A C - B^2) t^2, so p + q = (q^2 - p^2) / (q - p) where
+// p < 0 (3 x 900: the row's error 5e-12 -> 1e-15 of its terms).
+__device__ double s2_antideriv_stable(double A, double B, double C, double s, double t) {
+    const double Q = A * s * s + B * s * t + C * t * t, det = 4.0 * A * C - B * B;
+    const double p = 2.0 * A * s + B * t, q = 2.0 * sqrt(A * Q);
+    const double p2 = 2.0 * C * t + B * s, q2 = 2.0 * sqrt(C * Q);
+    double g = 0.0;
+    if (t != 0.0) g += t / sqrt(A) * log(p < 0.0 ? det * t * t / (q - p) : p + q);
+    if (s != 0.0) g += s / sqrt(C) * log(p2 < 0.0 ? det * s * s / (q2 - p2) : p2 + q2);
+    return g;
+}
+
+// The part of the closed-form integral that row chunk c of `chunks` subtracts from
+// its sum: corners c, c + chunks, .. of the rectangle [x_1, x_N] x [y_lo, y_M] relative
+// to point (k, l), from mesh indices: the offset to an edge through the target is
+// exactly zero (y_lo = -y_M on a half domain, where y_1 = 0; y_1 on a full one).
+__device__ __forceinline__ double s2_corners(double A, double B, double C, int N, int M, int nimg, double dx, double dy,
+                                             int k, int l, int c, int chunks) {
+    double g = 0.0;
+    for (int w = c; w < 4; w += chunks) {
+        const double sc = (w & 1) ? -(k + 0.5) * dx : (N - 1.5 - k) * dx;
+        const double tc = (w & 2) ? (nimg == 2 ? -(double)(M - 1 + l) * dy : -(double)l * dy) : (double)(M - 1 - l) * dy;
+        const double v = s2_antideriv_stable(A, B, C, sc, tc);
+        g += (w == 0 || w == 3) ? v : -v;
+    }
+    return g;
+}
+
+// 1/sqrt(x) to rounding: the estimate refined twice
+__device__ __forceinline__ double rsq_full(double x) {
+    double y = (double)__builtin_amdgcn_rsqf((float)x);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const double e = fma(-x * y, y, 1.0);
+        y = fma(0.5 * y, e, y);
+    }
+    return y;
+}
+
+// Coefficients of one target's form (in units of dx) at one row: B t and C t^2.
+struct S2Row {
+    double A, sqA, Bt, Ct2;  // sqA: sqrt(A)
+};
+
+// One end of a segment: g = |u| + 2 sqrt(A Q), u = 2 A s + B t, and the corrections
+// of the first K orders as they enter at an upper end:
+//   sum_m (B_2m / 2m) eps^(2m-1) P_2m-1(c) / sqrt(Q),  eps = sqrt(A / Q).
+// With X = eps c = -u / 2Q and y = eps^2, eps^n P_n(c) is a polynomial in X and y;
+// the sum is X times a polynomial of degree K - 1 in (X^2, y), by Horner in both.
+template <int K>
+__device__ __forceinline__ double s2_end(const S2Row &r, double s, double &g, double &u) {
+    // row j: the coefficients of y^j, by powers of X^2
+    constexpr double q[6][6] = {
+        {1.0 / 12, -1.0 / 48, 1.0 / 32, -143.0 / 1280, 1105.0 / 1536, -223193.0 / 30720},
+        {1.0 / 80, -5.0 / 144, 231.0 / 1280, -195.0 / 128, 2455123.0 / 129024},
+        {5.0 / 672, -21.0 / 256, 273.0 / 256, -129217.0 / 7168},
+        {7.0 / 768, -35.0 / 128, 7601.0 / 1024},
+        {105.0 / 5632, -7601.0 / 6144},
+        {7601.0 / 133120}};
+    const double Q = fma(s, fma(r.A, s, r.Bt), r.Ct2), rq = rsq(Q), rq2 = rq * rq;
+    u = fma(2.0 * r.A, s, r.Bt);
+    g = fma(2.0 * r.sqA, Q * rq, fabs(u));
+    const double X = -0.5 * u * rq2, y = r.A * rq2, z = X * X;
+    double sum = 0.0;
+#pragma unroll
+    for (int j = K - 1; j >= 0; --j) {
+        double h = q[j][K - 1 - j];
+#pragma unroll
+        for (int i = K - 2 - j; i >= 0; --i) h = fma(h, z, q[j][i]);
+        sum = j == K - 1 ? h : fma(sum, y, h);
+    }
+    return sum * X * rq;
+}
+
+// Ratio num / den whose logarithm over sqrt(A) is the integral between two ends.
+__device__ __forceinline__ void s2_ratio(double g1, double u1, double g2, double u2, double w2, double &num,
+                                         double &den) {
+    const bool cross = u1 < 0.0 && u2 >= 0.0;
+    num = cross ? g1 * g2 : u1 >= 0.0 ? g2 : g1;
+    den = cross ? w2 : u1 >= 0.0 ? g1 : g2;
+}
+
+// The S2 sums of 64 targets (tile tt of the flattened points of both boundaries)
+// over the lattice rows c, c + chunks, ..: rows -(M-1) .. M-1 on a half domain (the
+// images; the doubled row on the symmetry line counts once whole), less this
+// chunk's part of the closed-form integral.
+__device__ __forceinline__ void s2_item(const double *__restrict__ tg64, int N, int M, int nimg, double dx, double dy,
+                                        int tiles_per_bnd, int tt, int c, int chunks, double *__restrict__ out,
+                                        int lane) {
+    const GlobalPtr<const double> tg = (GlobalPtr<const double>)tg64;
+    const int ntg = (N - 1) * M;
+    const size_t T2 = (size_t)2 * ntg;
+    const int st = tt / tiles_per_bnd, idx = (tt - st * tiles_per_bnd) * 64 + lane;
+    const int ic = min(idx, ntg - 1), l = ic / (N - 1), k = ic - l * (N - 1);
+    const int tid = st * ntg + ic;
+    const double B = tg[5 * T2 + tid], C = tg[6 * T2 + tid];
+    S2Row r;
+    r.A = tg[4 * T2 + tid];
+    const double isqA = rsq_full(r.A);
+    r.sqA = r.A * isqA;
+    const double D4 = fma(4.0 * r.A, C, -B * B);
+    const double cen = -0.5 * B / r.A, et2 = D4 / (4.0 * r.A * r.A);  // s_c / t, eta^2 / t^2
+    const int rows = nimg == 2 ? 2 * M - 1 : M, off = nimg == 2 ? M - 1 + l : l;
+    const double ry = dy / dx, s0 = -(k + 0.5), sN = N - 1.5 - k, last = N - 1;
+    constexpr double H2 = kS2Reach * kS2Reach, far3 = 32.0 * 32.0;
+    double acc = 0.0, logs = 0.0, num = 1.0, den = 1.0;
+    int pending = 0;
+    for (int jr = c; jr < rows; jr += chunks) {
+        const double t = (jr - off) * ry, t2 = t * t;
+        const bool edge = jr == 0 || jr == rows - 1;
+        const double wy = edge ? 0.5 : 1.0;
+        r.Bt = B * t;
+        r.Ct2 = C * t2;
+        const double eta2 = et2 * t2, w2 = D4 * t2;
+        double rn = 1.0, rd = 1.0;  // the row's ratio
+        if (__all(eta2 >= H2)) {
+            // the whole row as one segment
+            const double Q0 = fma(s0, fma(r.A, s0, r.Bt), r.Ct2), Q1 = fma(sN, fma(r.A, sN, r.Bt), r.Ct2);
+            double g1, g2, u1, u2, e1, e2;
+            if (__all(Q0 >= far3 * r.A && Q1 >= far3 * r.A)) {
+                e1 = s2_end<3>(r, s0, g1, u1);
+                e2 = s2_end<3>(r, sN, g2, u2);
+            } else {
+                e1 = s2_end<6>(r, s0, g1, u1);
+                e2 = s2_end<6>(r, sN, g2, u2);
+            }
+            acc = fma(wy, e2 - e1, acc);
+            s2_ratio(g1, u1, g2, u2, w2, rn, rd);
+        } else {
+            // nodes a .. b one by one (a trapezoid of its own), segments 0 .. a and b .. N-1
+            const double W = sqrt(fmax(H2 - eta2, 0.0)), sc = cen * t - s0;
+            const bool far = eta2 >= H2;
+            double fa = floor(sc - W), fb = ceil(sc + W);
+            fa = far ? last : fa < 1.0 ? 0.0 : fmin(fa, last);
+            fb = far || fb > last - 1.0 ? last : fmax(fb, 0.0);
+#pragma unroll 1
+            for (int side = 0; side < 2; ++side) {
+                const double e1 = side ? fb : 0.0, e2 = side ? last : fa;
+                double g1, g2, u1, u2, n1, d1;
+                const double c1 = s2_end<6>(r, s0 + e1, g1, u1), c2 = s2_end<6>(r, s0 + e2, g2, u2);
+                s2_ratio(g1, u1, g2, u2, w2, n1, d1);
+                const bool there = e2 > e1;
+                rn *= there ? n1 : 1.0;
+                rd *= there ? d1 : 1.0;
+                acc = fma(there ? wy : 0.0, c2 - c1, acc);
+            }
+            const int cnt = (int)(fb - fa);
+            double sa = s0 + fa;
+            for (int j = 0; __any(j <= cnt && cnt > 0); ++j) {
+                const double f = rsq(fma(sa, fma(r.A, sa, r.Bt), r.Ct2));
+                const double wj = (j > cnt || cnt <= 0) ? 0.0 : (j == 0 || j == cnt) ? 0.5 * wy : wy;
+                acc = fma(wj, f, acc);
+                sa += j < cnt ? 1.0 : 0.0;
+            }
+        }
+        if (edge) {  // half weight: half the logarithm
+            rn = sqrt(rn);
+            rd = sqrt(rd);
+        }
+        num *= rn;
+        den *= rd;
+        if (++pending == kS2Flush) {
+            logs += log(num / den);
+            num = den = 1.0;
+            pending = 0;
+        }
+    }
+    if (pending) logs += log(num / den);
+    const double sum = dy * fma(logs, isqA, acc) - s2_corners(r.A, B, C, N, M, nimg, dx, dy, k, l, c, chunks);
+    if (idx < ntg) ((GlobalPtr<double>)out)[(size_t)c * T2 + tid] = sum;
+}
+
+// The same (rows c, c + chunks, ..; less the closed-form integral's part) node by node.
+__device__ __forceinline__ void s2_nodes_item(const double *__restrict__ tg64, int N, int M, int nimg, double dx,
+                                              double dy, int tiles_per_bnd, int tt, int c, int chunks,
+                                              double *__restrict__ out, int lane) {
+    const GlobalPtr<const double> tg = (GlobalPtr<const double>)tg64;
+    const int ntg = (N - 1) * M;
+    const size_t T2 = (size_t)2 * ntg;
+    const int st = tt / tiles_per_bnd, idx = (tt - st * tiles_per_bnd) * 64 + lane;
+    const int ic = min(idx, ntg - 1), l = ic / (N - 1), k = ic - l * (N - 1);
+    const int tid = st * ntg + ic;
+    const double A = tg[4 * T2 + tid], B = tg[5 * T2 + tid], C = tg[6 * T2 + tid];
+    const int rows = nimg == 2 ? 2 * M - 1 : M, off = nimg == 2 ? M - 1 + l : l;
+    const double ry = dy / dx, s0 = -(k + 0.5);
+    double acc = 0.0;
+    for (int jr = c; jr < rows; jr += chunks) {
+        const double t = (jr - off) * ry, Bt = B * t, Ct2 = C * (t * t);
+        const double wy = (jr == 0 || jr == rows - 1) ? 0.5 : 1.0;
+        double row = 0.0;
+#pragma unroll 4
+        for (int i = 0; i < N; ++i) {
+            const double sn = s0 + i, f = rsq(fma(sn, fma(A, sn, Bt), Ct2));
+            row = fma((i == 0 || i == N - 1) ? 0.5 : 1.0, f, row);
+        }
+        acc = fma(wy, row, acc);
+    }
+    const double sum = dy * acc - s2_corners(A, B, C, N, M, nimg, dx, dy, k, l, c, chunks);
+    if (idx < ntg) ((GlobalPtr<double>)out)[(size_t)c * T2 + tid] = sum;
+}
+
+__global__ __launch_bounds__(256) void k_s2_sums(const double *__restrict__ tg, int N, int M, int nimg, double dx,
+                                                 double dy, int s2_chunks, double *__restrict__ out) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = blockIdx.x * 4 + wave, tpb = ((N - 1) * M + 63) / 64;
+    const int tt = g / s2_chunks, c = g - tt * s2_chunks;
+    if (tt >= 2 * tpb) return;
+    s2_item(tg, N, M, nimg, dx, dy, tpb, tt, c, s2_chunks, out, lane);
+}
+
+// The single-problem FP64 pair sums, one wave per (target tile, source chunk);
+// part: [chunks][targets].  NODES: the first s2_blocks workgroups form the S2 sums
+// node by node, behind the pair sums; otherwise k_s2_sums does (whose segments need
+// twice the registers of the pair sums: in one launch they cost these a third of
+// their resident waves, 506 -> 552 us at 181 x 61).
+template <int TPL, int UNROLL, bool NODES>
+__global__ __launch_bounds__(256) void k_allpairs64(const SrcRec<double> *__restrict__ srcS,
+                                                    const SrcRec<double> *__restrict__ srcB,
+                                                    const double *__restrict__ tg, int N, int M, int nimg, double y1,
+                                                    double dx, double dy, int tiles_per_bnd, int row_groups,
+                                                    int target_tiles, int chunks, double *__restrict__ part,
+                                                    int s2_blocks, int s2_chunks) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int g = blockIdx.x * 4 + wave;
+    if constexpr (NODES) {
+        if ((int)blockIdx.x < s2_blocks) {
+            const int tpb = ((N - 1) * M + 63) / 64, t2 = g / s2_chunks;
+            if (t2 < 2 * tpb)
+                s2_nodes_item(tg, N, M, nimg, dx, dy, tpb, t2, g - t2 * s2_chunks, s2_chunks,
+                              part + (size_t)chunks * 2 * (N - 1) * M, lane);
+            return;
+        }
+        g -= 4 * s2_blocks;
+    }
+    const int tt = g % target_tiles, c = g / target_tiles;
+    if (c >= chunks) return;
+    if (nimg == 2)
+        pair_item<double, false, TPL, UNROLL, 2, false, false, false>(srcS, srcB, tg, tg, N, M, y1, dx, dy, tiles_per_bnd,
+                                                                      row_groups, chunks, part, tt, c, lane);
+    else
+        pair_item<double, false, TPL, UNROLL, 1, false, false, false>(srcS, srcB, tg, tg, N, M, y1, dx, dy, tiles_per_bnd,
+                                                                      row_groups, chunks, part, tt, c, lane);
+}
+
 // Many problems in one persistent launch: the work items (target tile, source
 // chunk) of all active problems form one list; every wave walks it with a fixed
 // stride, so the schedule (and each problem's fixed-order reduction) is
@@ -626,16 +1015,6 @@ __global__ __launch_bounds__(256) void k_allpairs_batched(const PairDesc *__rest
 }
 
 // ------------------------------------------------------------------ A3 + A4: finalize
-// Closed form of the integral of (A s^2 + B s t + C t^2)^(-1/2) over a rectangle
-// from the antiderivative of Section 3.1; a term with a zero prefactor is its
-// limit, zero.
-__device__ double s2_antideriv(double A, double B, double C, double s, double t) {
-    const double Q = A * s * s + B * s * t + C * t * t;
-    double g = 0.0;
-    if (t != 0.0) g += t / sqrt(A) * log(2.0 * A * s + B * t + 2.0 * sqrt(A * Q));
-    if (s != 0.0) g += s / sqrt(C) * log(2.0 * C * t + B * s + 2.0 * sqrt(C * Q));
-    return g;
-}
 
 // Workgroups [0, bie_blocks) hold 64 boundary-integral rows each (4 waves: wave
 // w sums a quarter of the source chunks' partial sums and the w-th corner term
@@ -784,6 +1163,58 @@ __device__ __forceinline__ void finalize_rows(const PairDesc &D, int r) {
     D.F[row] = f1;
 }
 
+// The boundary-integral rows from the single-problem FP64 sums: pair sums [chunks]
+// [targets] and, behind them, [s2_chunks][targets] (at most 16) S2 sums less the
+// closed-form integral.  64 rows per workgroup, a quarter of the chunks per wave; the
+// logarithms of the closed form are taken in the S2 sums, where other waves hide
+// them (12.2 -> 4.8 us at 31 x 11, 8.0 -> 5.3 at 181 x 61).
+__device__ __forceinline__ void finalize_bie64(const PairDesc &D, int b, int s2_chunks, double (*red)[2][64]) {
+    const int N = D.N, M = D.M;
+    const int ntg = (N - 1) * M;
+    const size_t T2 = (size_t)2 * ntg;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int tid = b * 64 + lane;
+    const bool valid = tid < 2 * ntg;
+    const int t = valid ? tid : 2 * ntg - 1;
+    const int chunks = D.chunks;
+    const int c0 = (w * chunks) >> 2, c1 = ((w + 1) * chunks) >> 2;
+    const double *pp = D.part + t, *p2 = D.part + (size_t)chunks * T2 + t;
+    const double Dst = D.tg64[3 * T2 + t], sig = D.tg64[7 * T2 + t];
+    // this wave's four S2 chunks, then its quarter of the pair sums, eight loads in flight
+    double q2[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) q2[q] = 4 * w + q < s2_chunks ? p2[(size_t)(4 * w + q) * T2] : 0.0;
+    double acc = 0.0;
+    int c = c0;
+    for (; c + 8 <= c1; c += 8) {
+        double v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = pp[(size_t)(c + q) * T2];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc += v[q];
+    }
+    for (; c < c1; ++c) acc += pp[(size_t)c * T2];
+    double acc2 = (q2[0] + q2[1]) + (q2[2] + q2[3]);
+    if (w > 0) {
+        red[w - 1][0][lane] = acc;
+        red[w - 1][1][lane] = acc2;
+    }
+    __syncthreads();
+    if (w > 0 || !valid) return;
+    acc = ((acc + red[0][0][lane]) + red[1][0][lane]) + red[2][0][lane];
+    acc2 = ((acc2 + red[0][1][lane]) + red[1][1][lane]) + red[2][1][lane];
+    const int st = t / ntg, r = t - st * ntg;
+    const int l = r / (N - 1), k = r - l * (N - 1);
+    const int row = (st + 1) * (N + 1) * M + l * (N + 1) + k + 2;
+    D.F[row] = acc - sig * acc2 - kTwoPi * Dst;
+}
+__global__ __launch_bounds__(256) void k_finalize64(PairDesc D, int s2_chunks) {
+    __shared__ double red[3][2][64];
+    const int nb = bie_blocks(D.N, D.M), b = blockIdx.x;
+    if (b < nb) finalize_bie64(D, b, s2_chunks, red);
+    else finalize_rows(D, (b - nb) * 256 + threadIdx.x);
+}
+
 __device__ __forceinline__ void finalize_body(const PairDesc &D, int b) {
     __shared__ double red[3][3][64];
     const int nb = bie_blocks(D.N, D.M);
@@ -796,8 +1227,6 @@ __global__ __launch_bounds__(256) void k_finalize_batched(const PairDesc *__rest
     if (!D.active) return;  // uniform over the workgroup
     finalize_body(D, blockIdx.x - D.blk_fin);
 }
-
-inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 
 }  // namespace
 
@@ -871,6 +1300,13 @@ PairDesc make_desc(const bim_problem *p, const Dims &d, const PairLaunch &pl, co
 
 }  // namespace
 
+// Meshes whose S2 sums are formed node by node, in the pair sums' launch: up to about
+// 10^7 targets times lattice nodes the segments' own launch and latency cost more
+// (whole evaluation, nodes / segments in us: 31 x 11 22 / 28, 61 x 21 34 / 36, 76 x 26 45 /
+// 48, 91 x 31 70 / 68, 121 x 41 156 / 137, 181 x 61 660 / 511; full 51 x 51 51 / 55,
+// 61 x 61 74.5 / 72.5, 101 x 101 358 / 302).
+static bool s2_by_nodes(const Dims &d) { return (double)d.nnode * d.nnode * d.nimg < 1.1e7; }
+
 int residual_enqueue(const bim_problem *p, const double *u, double *F, int prec, const PairLaunch &pl,
                      const ResidualWork &w, hipStream_t s, hipEvent_t *ev_pair, int linear,
                      const double *lin_tables) {
@@ -878,11 +1314,19 @@ int residual_enqueue(const bim_problem *p, const double *u, double *F, int prec,
     const int N = d.N, M = d.M;
     PairDesc D = make_desc(p, d, pl, w, u, F, prec, linear);
     if (lin_tables) D.chunks = lin_conv_chunks(d, pl.chunks);
-    hipLaunchKernelGGL(k_integrate, dim3(3 * M), dim3(64), 0, s, D);
-    if (prec == BIM_FP64)
-        hipLaunchKernelGGL(k_records<double>, dim3(record_blocks(N, M)), dim3(256), 0, s, D);
-    else
-        hipLaunchKernelGGL(k_records<float>, dim3(record_blocks(N, M)), dim3(256), 0, s, D);
+    // FP64 with its own sums (not pair by pair with S2's)
+    const bool pairs64 = prec == BIM_FP64 && !linear && !pl.s2_with_pairs;
+    const bool own64 = pairs64 || lin_tables;
+    const size_t prep_lds = sizeof(double) * 7 * (size_t)N;
+    if (own64 && prep_lds <= kPrepareLds) {
+        hipLaunchKernelGGL(k_prepare64, dim3(M), dim3(256), prep_lds, s, D);
+    } else {
+        hipLaunchKernelGGL(k_integrate, dim3(3 * M), dim3(64), 0, s, D);
+        if (prec == BIM_FP64)
+            hipLaunchKernelGGL(k_records<double>, dim3(record_blocks(N, M)), dim3(256), 0, s, D);
+        else
+            hipLaunchKernelGGL(k_records<float>, dim3(record_blocks(N, M)), dim3(256), 0, s, D);
+    }
     if (ev_pair) BIM_HIP(hipEventRecord(ev_pair[0], s));
 #define BIM_LAUNCH_PAIRS(T, COMP, TPL, UNR, TG)                                                         \
     hipLaunchKernelGGL((k_allpairs<T, COMP, TPL, UNR>), dim3(pl.blocks), dim3(256), 0, s,               \
@@ -890,6 +1334,12 @@ int residual_enqueue(const bim_problem *p, const double *u, double *F, int prec,
                        p->y1, p->dx, p->dy, pl.tiles_per_bnd, pl.row_groups, pl.target_tiles, pl.chunks, \
                        w.part)
     const int vsel = (pl.tpl == 2 ? 3 : 0) + (pl.unroll == 2 ? 0 : pl.unroll == 4 ? 1 : 2);
+    // FP64: the S2 sums' row chunks share the partial-sum buffer (two values per chunk
+    // and target) with the pair sums; on small meshes they are summed node by node in
+    // the same launch (s2_by_nodes)
+    const bool by_nodes = s2_by_nodes(d);
+    const int s2_chunks = std::min(kS2Chunks, pl.chunks);
+    const int s2_blocks = cdiv((long)2 * cdiv((long)(N - 1) * M, 64) * s2_chunks, 4);
     if (lin_tables) {
         if (int rc = lin_conv_enqueue(D, lin_tables, s)) return rc;
     } else if (linear) {
@@ -906,6 +1356,33 @@ int residual_enqueue(const bim_problem *p, const double *u, double *F, int prec,
                                (const SrcRec<float> *)w.srcS, (const SrcRec<float> *)w.srcB, w.tg32, w.tg, N, M,
                                d.nimg, p->y1, p->dx, p->dy, ll.tiles_per_bnd, ll.row_groups, ll.target_tiles,
                                ll.chunks, w.part);
+    } else if (pairs64) {
+#define BIM_LAUNCH_PAIRS64(TPL, UNR, NODES)                                                                       \
+    hipLaunchKernelGGL((k_allpairs64<TPL, UNR, NODES>), dim3(pl.blocks + (NODES ? s2_blocks : 0)), dim3(256), 0, s,    \
+                       (const SrcRec<double> *)w.srcS, (const SrcRec<double> *)w.srcB, w.tg, N, M, d.nimg, p->y1, p->dx, \
+                       p->dy, pl.tiles_per_bnd, pl.row_groups, pl.target_tiles, pl.chunks, w.part, s2_blocks, s2_chunks)
+        if (by_nodes) {
+            switch (vsel) {
+                case 0: BIM_LAUNCH_PAIRS64(1, 2, true); break;
+                case 1: BIM_LAUNCH_PAIRS64(1, 4, true); break;
+                case 2: BIM_LAUNCH_PAIRS64(1, 8, true); break;
+                case 3: BIM_LAUNCH_PAIRS64(2, 2, true); break;
+                case 4: BIM_LAUNCH_PAIRS64(2, 4, true); break;
+                default: BIM_LAUNCH_PAIRS64(2, 8, true); break;
+            }
+        } else {
+            hipLaunchKernelGGL(k_s2_sums, dim3(s2_blocks), dim3(256), 0, s, w.tg, N, M, d.nimg, p->dx, p->dy, s2_chunks,
+                               w.part + (size_t)pl.chunks * 2 * d.ntg);
+            switch (vsel) {
+                case 0: BIM_LAUNCH_PAIRS64(1, 2, false); break;
+                case 1: BIM_LAUNCH_PAIRS64(1, 4, false); break;
+                case 2: BIM_LAUNCH_PAIRS64(1, 8, false); break;
+                case 3: BIM_LAUNCH_PAIRS64(2, 2, false); break;
+                case 4: BIM_LAUNCH_PAIRS64(2, 4, false); break;
+                default: BIM_LAUNCH_PAIRS64(2, 8, false); break;
+            }
+        }
+#undef BIM_LAUNCH_PAIRS64
     } else if (prec == BIM_FP64) {
         switch (vsel) {
             case 0: BIM_LAUNCH_PAIRS(double, false, 1, 2, w.tg); break;
@@ -927,7 +1404,10 @@ int residual_enqueue(const bim_problem *p, const double *u, double *F, int prec,
     }
 #undef BIM_LAUNCH_PAIRS
     if (ev_pair) BIM_HIP(hipEventRecord(ev_pair[1], s));
-    hipLaunchKernelGGL(k_finalize, dim3(finalize_blocks(N, M)), dim3(256), 0, s, D);
+    if (pairs64)
+        hipLaunchKernelGGL(k_finalize64, dim3(finalize_blocks(N, M)), dim3(256), 0, s, D, s2_chunks);
+    else
+        hipLaunchKernelGGL(k_finalize, dim3(finalize_blocks(N, M)), dim3(256), 0, s, D);
     return hip_check(hipGetLastError(), "residual kernel launch");
 }
 

@@ -42,25 +42,51 @@ int chunks_for_waves(const Dims &d, int tpl, int unroll, long want_waves) {
 PairLaunch pair_launch_cfg(const Dims &d, int prec, const bim_pair_config &cfg) {
     int chunks = cfg.chunks;
     if (chunks <= 0 && cfg.rows_per_chunk > 0) chunks = cdiv(2 * d.M, cfg.rows_per_chunk);
-    // default: about 24 (FP64) or 32 (FP32C) waves per SIMD (1024 SIMDs), the
-    // best counts measured at 181 x 61 (fewer waves hide less latency; many
-    // more only add partial sums)
-    if (chunks <= 0)
-        chunks = chunks_for_waves(d, cfg.targets_per_lane, cfg.unroll, prec == BIM_FP64 ? 24576 : 32768);
+    // default wave count.  FP32C: about 32 waves per SIMD (1024 SIMDs), the best
+    // count measured at 181 x 61.  FP64: 3 per mesh node, between 1 and 48 per SIMD
+    // (fewer hide less latency, more cost the reduction of their partial sums;
+    // measured optima: 31 x 11 1.7 thousand waves, 61 x 21 4.1, 91 x 31 8.2, 121 x 41
+    // 16, 181 x 61 33, full 71 x 71 16, full 151 x 151 49 thousand)
+    if (chunks <= 0) {
+        const long want = prec == BIM_FP64 ? std::max(1024L, std::min(49152L, 3L * d.nnode)) : 32768;
+        chunks = chunks_for_waves(d, cfg.targets_per_lane, cfg.unroll, want);
+    }
     return pair_launch(d, cfg.targets_per_lane, cfg.unroll, chunks);
+}
+
+static bool tuned_launch(const bim_problem *p, int prec, bim_pair_config *cfg) {
+    std::lock_guard<std::mutex> lk(g_mu);
+    auto it = g_best.find(Key(p->N, p->M, p->half_domain ? 1 : 0, prec));
+    if (it == g_best.end()) return false;
+    *cfg = it->second;
+    return true;
 }
 
 PairLaunch pair_launch_for(const bim_problem *p, int prec) {
     const Dims d(p);
-    {
-        std::lock_guard<std::mutex> lk(g_mu);
-        auto it = g_best.find(Key(p->N, p->M, p->half_domain ? 1 : 0, prec));
-        if (it != g_best.end()) return pair_launch_cfg(d, prec, it->second);
+    bim_pair_config cfg;
+    if (tuned_launch(p, prec, &cfg)) return pair_launch_cfg(d, prec, cfg);
+    // untuned defaults, the fastest shapes measured: FP64 4-way unroll, two rows per
+    // lane on a full domain of some size, where the shared record work is half of a
+    // pair's (151 x 151: 1242 us with one row, 1119 with two; 71 x 71: 109 / 106; 41 x 41:
+    // 44 / 44; on a half domain the images share it already: 488 / 489 at 181 x 61);
+    // FP32C 2-way unroll
+    const bool two = prec == BIM_FP64 && d.nimg == 1 && d.nnode >= 4096;
+    cfg = {two ? 2 : 1, prec == BIM_FP32C ? 2 : 4, 0, 0};
+    return pair_launch_cfg(d, prec, cfg);
+}
+
+PairLaunch pair_launch_batch(const bim_problem *p, int prec) {
+    const Dims d(p);
+    bim_pair_config cfg;
+    if (!tuned_launch(p, prec, &cfg)) {
+        cfg = {1, prec == BIM_FP32C ? 2 : 4, 0, 0};
+        // about 24 waves per SIMD in FP64, the best count of these kernels at 181 x 61
+        if (prec == BIM_FP64) cfg.chunks = chunks_for_waves(d, 1, 4, 24576);
     }
-    // untuned defaults: the fastest shapes measured at 181 x 61 (FP64: 4-way
-    // unroll; FP32C: 2-way unroll; about 24 and 32 waves per SIMD)
-    const bim_pair_config def = {1, prec == BIM_FP32C ? 2 : 4, 0, 0};
-    return pair_launch_cfg(d, prec, def);
+    PairLaunch pl = pair_launch_cfg(d, prec, cfg);
+    pl.s2_with_pairs = true;
+    return pl;
 }
 
 }  // namespace bim
@@ -77,12 +103,14 @@ extern "C" int bim_tune_residual(const bim_problem *prob, const double *u, int p
     hipStream_t s = (hipStream_t)stream;
     double *F = nullptr;
     if ((rc = hip_check(hipMallocAsync((void **)&F, sizeof(double) * d.nvec, s), "hipMallocAsync"))) return rc;
-    // every variant at chunk counts giving 8 to 48 waves per SIMD (1024 SIMDs)
+    // every variant at its default chunk count and those giving 8 to 48 waves per SIMD
+    // (1024 SIMDs)
     std::vector<bim_pair_config> cands;
     for (int tpl : {1, 2})
         for (int unr : {2, 4, 8})
-            for (long want : {8192L, 16384L, 24576L, 32768L, 49152L}) {
-                const int chunks = pair_launch(d, tpl, unr, chunks_for_waves(d, tpl, unr, want)).chunks;
+            for (long want : {0L, 8192L, 16384L, 24576L, 32768L, 49152L}) {
+                const int chunks = want ? pair_launch(d, tpl, unr, chunks_for_waves(d, tpl, unr, want)).chunks
+                                        : pair_launch_cfg(d, prec, {tpl, unr, 0, 0}).chunks;
                 bim_pair_config c{tpl, unr, 0, chunks};
                 bool dup = false;
                 for (auto &o : cands)

@@ -57,6 +57,51 @@ def test_residual_fp64_matches_oracle(bim, name, mk, seed):
     assert err.max() <= 1e-12
 
 
+# The FP64 S2 sums in segments and node by node (from about 10^7 targets times lattice
+# nodes on: segments), rows shorter than the segments' reach and too long for the
+# fused records, whole and partly filled tiles, two rows per lane; slopes up to ~2.
+S2_CASES = [
+    (91, 31, True, 1.0), (91, 31, True, 12.0),   # segments, gentle and steep
+    (81, 27, True, 12.0),                        # node by node, just below the line
+    (65, 45, True, 3.0),                         # rows of 64 targets
+    (67, 67, False, 8.0),                        # full domain, two rows per lane, odd row count
+    (60, 59, False, 1.0),                        # full domain, one row per lane
+    (3, 900, True, 3.0), (3, 700, True, 3.0),    # shortest rows
+    (1200, 3, True, 3.0),                        # fewest rows, longer than the fused records take
+]
+
+
+def _s2_integral_extended(A, B, C, s1, s2, t1, t2):
+    """The oracle's closed form in extended precision: on strips far longer than wide
+    its logarithms cancel (5e-12 of the row's terms at 3 x 900 in FP64)."""
+    A, B, C, s1, s2, t1, t2 = (np.asarray(v, dtype=np.longdouble) for v in (A, B, C, s1, s2, t1, t2))
+
+    def G(s, t):
+        with np.errstate(divide="ignore", invalid="ignore"):
+            Q = A * s * s + B * s * t + C * t * t
+            a1 = t / np.sqrt(A) * np.log(2 * A * s + B * t + 2 * np.sqrt(A * Q))
+            a2 = s / np.sqrt(C) * np.log(2 * C * t + B * s + 2 * np.sqrt(C * Q))
+        return np.where(t == 0, 0, a1) + np.where(s == 0, 0, a2)
+
+    return (G(s2, t2) - G(s1, t2) - G(s2, t1) + G(s1, t1)).astype(np.float64)
+
+
+@pytest.mark.parametrize("N,M,half,steep", S2_CASES)
+def test_residual_fp64_s2_routes_match_oracle(bim, monkeypatch, N, M, half, steep):
+    monkeypatch.setattr(R, "s2_integral", _s2_integral_extended)
+    L, Ly = 0.25 * (N - 1) / 2, 0.3 * (M - 1)
+    p = W.make_problem(N, M, -L, L, 0 if half else -0.4 * Ly, Ly if half else 0.6 * Ly, 0.9,
+                       [W.Bump(0.2, 1.0, 1.0, cy=0.0 if half else 0.5)], half_domain=half)
+    u = W.perturbed_state(p, 21)
+    nb = (N + 1) * M
+    u[:nb] *= steep  # elevation and its slopes
+    err = np.abs(_gpu_F(bim, p, u, "fp64") - R.residual(p, u)) / R.term_magnitude_rows(p, u)
+    print(N, M, "max slope", np.abs(u[:nb]).max(), "max rel err", err.max())
+    # as the tolerance of the other FP64 cases: rounding of the row's terms, each a few
+    # units in the last place, over sums of up to 10^4
+    assert err.max() <= 1e-12
+
+
 @pytest.mark.parametrize("name,mk,seed", CASES[:4], ids=[c[0] for c in CASES[:4]])
 def test_residual_fp32c_matches_oracle(bim, name, mk, seed):
     p = mk()
