@@ -728,7 +728,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<T
 // suffice from 32 on.  The segments' integrals are (1/sqrt A) ln of a ratio; a
 // wave multiplies the ratios of 16 rows before it takes a logarithm.
 // A target costs about 15 thousand FP64 instructions instead of the 220 thousand of
-// its 22082 pairs at 181 x 61 (all-pairs launch 613 -> S2TIME us).
+// its 22082 pairs at 181 x 61 (launches of the sums 613 -> 486 us; full 151 x 151
+// 1570 -> 1120).
 constexpr double kS2Reach = 8.0;   // node-by-node distance, in dx
 constexpr int kS2Flush = 16;       // rows per logarithm (their product stays in range)
 constexpr int kS2Chunks = 16;      // most row chunks per tile of targets (rows c, c + chunks, ..)

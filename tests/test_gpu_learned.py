@@ -216,3 +216,77 @@ def test_network_within_bf16_bound_of_plain_fp64(bim, N, M, B, lin):
             assert e <= 4 * BF16_U
         else:
             assert cos >= 0.98 and e <= 0.25
+
+
+def _bf16(x):
+    return x.to(torch.float32).to(torch.bfloat16).to(torch.float64)
+
+
+def _rounded_step(params, X, f, T):
+    """The network's training step in FP64 with its operands rounded to bf16 where the
+    kernels round them: loss, output and the parameter gradients."""
+    F = torch.nn.functional
+    Ws = [_bf16(torch.as_tensor(w)) for w, _ in params]
+    bs = [torch.as_tensor(b, dtype=torch.float64) for _, b in params]
+
+    def kernel(W, cin):  # [(ky, kx, c)][n] -> torch's [n][c][ky][kx]
+        return W.reshape(3, 3, cin, -1).permute(3, 2, 0, 1)
+
+    x0 = _bf16(torch.as_tensor(X)).permute(0, 3, 1, 2)
+    k1, k2 = kernel(Ws[0], x0.shape[1]), kernel(Ws[1], Ws[0].shape[1])
+    a1 = _bf16(F.relu(F.conv2d(x0, k1, bs[0], stride=2, padding=1)))
+    y2 = _bf16(F.relu(F.conv2d(a1, k2, bs[1], stride=2, padding=1)))
+    a2 = torch.cat([y2.permute(0, 2, 3, 1).reshape(len(f), -1), _bf16(torch.as_tensor(f))[:, None]], 1)
+    a3 = _bf16(F.relu(a2 @ Ws[2] + bs[2]))
+    Y = a3 @ Ws[3] + bs[3]
+    d4 = (Y - torch.as_tensor(T, dtype=torch.float64)) / Y.numel()
+    loss = 0.5 * float((d4 * d4).sum()) * Y.numel()
+    d3 = (_bf16(d4) @ Ws[3].T) * (a3 > 0)
+    d2 = ((_bf16(d3) @ Ws[2].T)[:, :-1] * (a2[:, :-1] > 0)).reshape(len(f), *y2.shape[2:], -1).permute(0, 3, 1, 2)
+    d1 = torch.nn.grad.conv2d_input(a1.shape, k2, _bf16(d2), stride=2, padding=1) * (a1 > 0)
+    g1 = torch.nn.grad.conv2d_weight(x0, k1.shape, _bf16(d1), stride=2, padding=1)
+    g2 = torch.nn.grad.conv2d_weight(a1, k2.shape, _bf16(d2), stride=2, padding=1)
+    back = lambda g: g.permute(2, 3, 1, 0).reshape(-1)
+    return Y, loss, [(back(g1), d1.sum((0, 2, 3))), (back(g2), d2.sum((0, 2, 3))),
+                     ((a2.T @ _bf16(d3)).reshape(-1), d3.sum(0)), ((a3.T @ _bf16(d4)).reshape(-1), d4.sum(0))]
+
+
+# Batches around 32 and 64 rows, K around the steps of 32 and 8 x 32, channel counts that
+# are not multiples of 4 or 16 (element loads), one pixel left after the convolutions,
+# long weight-gradient sums, misaligned input.
+@pytest.mark.parametrize("N,M,C1,C2,D3,lin,batches,shift", [
+    (3, 3, 5, 7, 9, 0, (1, 2), 0),
+    (4, 4, 4, 16, 33, 1, (40, 3), 0),
+    (31, 11, 16, 32, 300, 1, (33, 32, 31), 0),
+    (31, 11, 16, 32, 64, 1, (65,), 1),
+    (45, 13, 18, 33, 50, 0, (17,), 0),
+    (61, 21, 16, 32, 512, 1, (9, 1), 0),
+])
+def test_training_step_edges_match_rounded_reference(bim, N, M, C1, C2, D3, lin, batches, shift):
+    net = bim.LearnedNet(N, M, seed=11, max_batch=max(batches), C1=C1, C2=C2, D3=D3, in_linear=lin)
+    fan_out = [C1, C2, D3, 2 * M * N]
+    params = []
+    for l in range(4):
+        W_, b, _, _ = net.get(l)
+        b = np.random.default_rng(l).normal(0, 0.05, b.shape).astype(np.float32)
+        net.set(l, None, b)
+        params.append((W_.reshape(-1, fan_out[l]), b))
+    for B in batches:  # on one network: what a larger batch left behind must not show
+        X, f, T = _inputs(N, M, B, 12 + B, net.in_channels)
+        Xd = _bf16_tensor(X)
+        if shift:
+            Xd = torch.cat([Xd.new_zeros(shift), Xd.reshape(-1)])[shift:].view(Xd.shape)
+        fd = torch.as_tensor(f, device="cuda")
+        Y, loss, grads = _rounded_step(params, X, f, T)
+        got = net.train_step(Xd, fd, torch.as_tensor(T, device="cuda"), lr=0.0, update=False)
+        Yd = net.forward(Xd, fd).cpu().double()
+        # FP32 sums of up to 2e4 products (1e-6), and a value that falls on the other side of a
+        # bf16 rounding by them moves by 2^-8: 1e-3 of the largest entry allows several
+        assert float((Yd - Y).abs().max() / Y.abs().max()) < 1e-3
+        assert abs(got - loss) < 1e-3 * loss
+        for l in range(4):
+            _, _, gw, gb = net.get(l)
+            for g, r in ((gw, grads[l][0]), (gb, grads[l][1])):
+                e = float((torch.as_tensor(g).double() - r).abs().max() / (r.abs().max() + 1e-30))
+                print(N, M, B, "layer", l, e)
+                assert e < 2e-3
