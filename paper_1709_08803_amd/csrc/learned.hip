@@ -23,9 +23,11 @@
 //   Y4  [B][2 H W]        fully connected, linear: (dzeta_x, dphi_x) / out_scale, [2][H][W]
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <mutex>
 #include <random>
 #include <vector>
 
@@ -480,6 +482,11 @@ __global__ void k_pack_weights(const float *__restrict__ w, uint16_t *__restrict
     wC[pk(n, m, pad32(fan))] = v;
     if (wR) wR[pk(m, n, pad32(outs))] = v;
 }
+// to mapped host memory, n 16-byte words
+__global__ void k_to_host(const uint4 *__restrict__ src, uint4 *__restrict__ dst, int n) {
+    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += gridDim.x * blockDim.x) dst[e] = src[e];
+}
+
 // network input from a problem: NHWC [H = M][W = N][C0]; C0 = 4 adds the
 // linear start's x-derivative planes (u_lin in the unknown vector's order)
 __global__ void k_make_input(const double *__restrict__ beta, double froude, const double *__restrict__ ulin,
@@ -531,7 +538,57 @@ struct LgNet {
     float *Y4, *dY4, *dY3, *dY2, *dcols2, *dY1, *lossp, *ffeat;
     void *mem = nullptr;
     int step = 0;
+    // pinned staging of what goes back to the host: two halves of kStage bytes
+    char *stage = nullptr;
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    std::mutex stage_mu;
 };
+constexpr size_t kStage = 1 << 20;
+
+static void lg_free(LgNet *net) {
+    if (net->mem) (void)hipFree(net->mem);
+    if (net->stage) (void)hipHostFree(net->stage);
+    for (hipEvent_t e : net->ev)
+        if (e) (void)hipEventDestroy(e);
+    delete net;
+}
+
+// Consecutive device arrays (256-byte aligned, one allocation) to pageable host
+// memory: pieces of kStage bytes into the pinned halves in turn, the previous one copied
+// on by the host meanwhile.  A kernel writes them; the runtime's copies to pageable
+// memory, one per array, took longer (the arrays of the four layers at 31 x 11, 512 hidden
+// units: 64 + 254 + 237 + 220 us, here 24 + 252 + 183 + 128; pieces of 256 KB, 512 KB and 2 MB
+// are slower by 50, 20 and 5 us).
+struct HostPart {
+    const char *dev;
+    char *host;
+    size_t bytes;
+};
+static int stage_out(LgNet *net, const HostPart *part, int n, hipStream_t s) {
+    std::lock_guard<std::mutex> lock(net->stage_mu);
+    const char *lo = part[0].dev, *hi = part[n - 1].dev + part[n - 1].bytes;
+    const size_t total = hi - lo;
+    const int pieces = (int)((total + kStage - 1) / kStage);
+    for (int i = 0; i <= pieces; ++i) {
+        int rc;
+        if (i < pieces) {
+            const size_t at = (size_t)i * kStage, len = std::min(kStage, total - at);
+            const int words = (int)((len + 15) / 16);  // arrays are padded to 256 bytes
+            hipLaunchKernelGGL(k_to_host, dim3(std::min(cdiv(words, 256), 256)), dim3(256), 0, s, (const uint4 *)(lo + at),
+                               (uint4 *)(net->stage + (i & 1) * kStage), words);
+            if ((rc = hip_check(hipEventRecord(net->ev[i & 1], s), "hipEventRecord"))) return rc;
+        }
+        if (i == 0) continue;
+        const int h = (i - 1) & 1;
+        if ((rc = hip_check(hipEventSynchronize(net->ev[h]), "copy"))) return rc;
+        const char *from = lo + (size_t)(i - 1) * kStage, *to = std::min(from + kStage, hi);
+        for (int q = 0; q < n; ++q) {
+            const char *a = std::max(from, part[q].dev), *b = std::min(to, part[q].dev + part[q].bytes);
+            if (a < b) std::memcpy(part[q].host + (a - part[q].dev), net->stage + h * kStage + (a - from), b - a);
+        }
+    }
+    return BIM_OK;
+}
 
 static int lg_alloc(LgNet *net, int maxB) {
     const lg_arch &a = net->a;
@@ -589,6 +646,9 @@ static int lg_alloc(LgNet *net, int maxB) {
         p += al(q.second);
     }
     net->maxB = maxB;
+    if ((rc = hip_check(hipHostMalloc((void **)&net->stage, 2 * kStage), "hipHostMalloc"))) return rc;
+    for (hipEvent_t &e : net->ev)
+        if ((rc = hip_check(hipEventCreateWithFlags(&e, hipEventDisableTiming), "hipEventCreate"))) return rc;
     return hip_check(hipMemset(net->mem, 0, bytes), "hipMemset");
 }
 
@@ -729,8 +789,7 @@ int lg_create(const lg_arch *arch, uint64_t seed, int max_batch, lg_net **out) {
     }
     int rc = lg_alloc(net, max_batch);
     if (rc) {
-        if (net->mem) (void)hipFree(net->mem);
-        delete net;
+        lg_free(net);
         return rc;
     }
     // He-normal initialisation from a seeded host generator (weights [fan_in][fan_out])
@@ -745,8 +804,7 @@ int lg_create(const lg_arch *arch, uint64_t seed, int max_batch, lg_net **out) {
     }
     if (!rc) rc = hip_check(hipDeviceSynchronize(), "sync");
     if (rc) {
-        (void)hipFree(net->mem);
-        delete net;
+        lg_free(net);
         return rc;
     }
     *out = (lg_net *)net;
@@ -755,9 +813,7 @@ int lg_create(const lg_arch *arch, uint64_t seed, int max_batch, lg_net **out) {
 
 void lg_destroy(lg_net *n) {
     LgNet *net = (LgNet *)n;
-    if (!net) return;
-    if (net->mem) (void)hipFree(net->mem);
-    delete net;
+    if (net) lg_free(net);
 }
 
 int lg_num_params(const lg_net *n, int layer, int64_t *weights, int64_t *biases) {
@@ -790,10 +846,15 @@ int lg_get_params(const lg_net *n, int layer, float *w_host, float *b_host, floa
     int rc = hip_check(hipDeviceSynchronize(), "sync");
     if (rc) return rc;
     const size_t nw = 4 * net->nparam[layer], nb = 4 * net->nbias[layer];
-    if (w_host && (rc = hip_check(hipMemcpy(w_host, net->w[layer], nw, hipMemcpyDeviceToHost), "copy"))) return rc;
-    if (b_host && (rc = hip_check(hipMemcpy(b_host, net->b[layer], nb, hipMemcpyDeviceToHost), "copy"))) return rc;
-    if (gw_host && (rc = hip_check(hipMemcpy(gw_host, net->gw[layer], nw, hipMemcpyDeviceToHost), "copy"))) return rc;
-    if (gb_host && (rc = hip_check(hipMemcpy(gb_host, net->gb[layer], nb, hipMemcpyDeviceToHost), "copy"))) return rc;
+    // in the order of the allocation; neighbours that are wanted go in one run
+    const HostPart all[4] = {{(const char *)net->w[layer], (char *)w_host, nw}, {(const char *)net->b[layer], (char *)b_host, nb},
+                             {(const char *)net->gw[layer], (char *)gw_host, nw}, {(const char *)net->gb[layer], (char *)gb_host, nb}};
+    for (int i = 0; i < 4;) {
+        int j = i;
+        while (j < 4 && all[j].host) ++j;
+        if (j > i && (rc = stage_out(const_cast<LgNet *>(net), all + i, j - i, 0))) return rc;
+        i = j + 1;
+    }
     return BIM_OK;
 }
 
@@ -820,9 +881,8 @@ int lg_train_step(lg_net *n, const uint16_t *X0, const float *ffeat, const float
     if ((rc = step_impl(net, T, B, h, s))) return rc;
     if (loss_out) {
         std::vector<float> lp(B);
-        if ((rc = hip_check(hipMemcpyAsync(lp.data(), net->lossp, sizeof(float) * B, hipMemcpyDeviceToHost, s), "copy")))
-            return rc;
-        if ((rc = hip_check(hipStreamSynchronize(s), "sync"))) return rc;
+        const HostPart part{(const char *)net->lossp, (char *)lp.data(), sizeof(float) * B};
+        if ((rc = stage_out(net, &part, 1, s))) return rc;
         double L = 0.0;
         for (float v : lp) L += v;
         *loss_out = (float)L;
