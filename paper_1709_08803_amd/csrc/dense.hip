@@ -546,7 +546,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_tri(const GemmTriItemT<T> *__r
 
 // In-place Gauss-Jordan inversion of one s x s block (s <= 192) per 1024-thread
 // workgroup, with the matrix held in registers: wave ty (= tid / 64, uniform in
-// the wave) owns rows ty + 16 i (i < 12) and lane tx columns tx + 64 j (j < 3).
+// the wave) owns rows ty + 16 i (i < ROWS) and lane tx columns tx + 64 j (j < COLS).
 // Rows are eliminated in their natural order k = 0 .. s-1 with partial
 // pivoting over the columns (the pivot of row k is its largest entry among the
 // columns not yet used: partial pivoting of the transpose), so that the row
@@ -554,21 +554,25 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_tri(const GemmTriItemT<T> *__r
 // of lane q % 64 with wave-uniform lane reads.  A column that has served as a
 // pivot column is kept in its own scale: its true values are the stored ones
 // times sc[q] = -1/p (row operations commute with column scaling), so that
-// no step has to rescale it.  Step k:
-//   wave k % 16 (row k is its register row k / 16) finds q (a DPP maximum of
-//   packed pivot keys) and stages row k, scaled by 1/p and with 0 at column q,
-//   in one of two LDS buffers (one barrier per step);
+// no step has to rescale it.  Step k, between two barriers:
+//   the wave that owns row k + 1 updates that row first, finds its pivot column (a
+//   DPP maximum of packed pivot keys) and stages it, scaled by 1/p and with 0 at
+//   that column, in the other of two LDS buffers;
 //   every row r: a[r][c] -= a[r][q] * rowk[c] (column q keeps a[r][q], which
 //   is its new value -a[r][q]/p in the scale sc[q]);
 //   row k becomes the staged row with -1 (= 1/p in that scale) at column q.
 // After s steps the registers hold the inverse with rows and columns permuted
 // by the pivot columns, storage[r][q_c] sc[q_c] = inverse[q_r][c]; the
-// write-out applies the scales and undoes the permutation.  Only the owner
-// wave indexes its registers by k / 16 (a switch); the update of all rows uses
-// constant register indices.
-constexpr int kRegTy = 16, kRegRows = 12, kRegCols = 3;
-constexpr int kRegThreads = 64 * kRegTy;
-constexpr int kRegMaxS = kRegTy * kRegRows;  // = 64 kRegCols = 192
+// write-out applies the scales and undoes the permutation.  The loop over k / 16 is
+// unrolled, so that every register index is constant (a switch over the rows costs a
+// chain of branches in every step).
+// Bound by the step (about 2100 cycles at s = 182, 1000 at s = 32): the four waves of a
+// SIMD issue some 95 instructions each (36 FMAs, 24 lane reads), the next pivot's chain
+// (key maximum, reciprocal, staging: 500 cycles) runs beside them at a higher wave
+// priority, the barrier costs 250.  Registers of the block's own size, the chain
+// before the barrier instead of after it, no switch (s = 182: 193 -> 184 us; 122: 103 -> 94;
+// 92: 102 -> 64; 62: 102 -> 33; 32: 37 -> 15).  Eight waves instead of 16: 190 us and 93.
+constexpr int kRegMaxS = 192;
 
 // Largest value over the wave (unsigned): DPP shifts within rows of 16 lanes,
 // then the row broadcasts of lanes 15 and 31; lane 63 ends with the maximum.
@@ -598,121 +602,138 @@ __device__ __forceinline__ double readlane_f64(double v, int lane) {
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-#define BIM_ROW_CASES(X) X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11)
-
-__global__ __launch_bounds__(kRegThreads) void k_invert_reg(const InvItem *__restrict__ items, int s,
+// ROWS >= s / TY, COLS >= s / 64
+template <int TY, int ROWS, int COLS>
+__global__ __launch_bounds__(64 * TY) void k_invert_reg(const InvItem *__restrict__ items, int s,
                                                             int *__restrict__ info) {
-    static_assert(kRegRows == 12, "BIM_ROW_CASES lists 12 register rows");
     const InvItem it = items[blockIdx.x];
     const int tx = threadIdx.x & 63;
     const int ty = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    __shared__ double rowk[2][kRegMaxS], sc[kRegMaxS];
-    __shared__ int qcol[kRegMaxS], qinv[kRegMaxS];
-    __shared__ int s_bad;
-    double a[kRegRows][kRegCols];
+    __shared__ double rowk[2][64 * COLS], sc[64 * COLS];
+    __shared__ int qcol[64 * COLS], qinv[64 * COLS];  // qcol: -1 where no pivot was found
+    double a[ROWS][COLS];
 #pragma unroll
-    for (int i = 0; i < kRegRows; ++i)
+    for (int i = 0; i < ROWS; ++i)
 #pragma unroll
-        for (int j = 0; j < kRegCols; ++j) {
-            const int r = ty + kRegTy * i, c = tx + 64 * j;
+        for (int j = 0; j < COLS; ++j) {
+            const int r = ty + TY * i, c = tx + 64 * j;
             a[i][j] = (r < s && c < s) ? it.A[(size_t)r * it.lda + c] : 0.0;
         }
     unsigned used = 0;  // bit j: column tx + 64 j is a pivot column already (or lies beyond s)
 #pragma unroll
-    for (int j = 0; j < kRegCols; ++j)
+    for (int j = 0; j < COLS; ++j)
         if (tx + 64 * j >= s) used |= 1u << j;
-    if (threadIdx.x == 0) s_bad = 0;
-    for (int c = threadIdx.x; c < kRegMaxS; c += kRegThreads) sc[c] = 1.0;
+    for (int c = threadIdx.x; c < 64 * COLS; c += (64 * TY)) sc[c] = 1.0;
     __syncthreads();
-    for (int k = 0; k < s; ++k) {
-        const int w = k & (kRegTy - 1), ik = k / kRegTy;
-        if (ty == w) {  // owner of row k: pivot column and the staged row
-            double r0 = 0.0, r1 = 0.0, r2 = 0.0;
-            switch (ik) {
-#define BIM_GET(I)      \
-    case I:             \
-        r0 = a[I][0];   \
-        r1 = a[I][1];   \
-        r2 = a[I][2];   \
-        break;
-                BIM_ROW_CASES(BIM_GET)
-#undef BIM_GET
+    // the pivot column of row k, whose elements are r, and the staged row
+    auto stage = [&](int k, const double (&r)[COLS]) {
+        // each lane's own candidate and its reciprocal (beside the maximum over the wave)
+        unsigned key = pivot_key(r[0], tx, !(used & 1u));
+        double best = r[0];
+#pragma unroll
+        for (int j = 1; j < COLS; ++j) {
+            const unsigned kj = pivot_key(r[j], tx + 64 * j, !(used & (1u << j)));
+            best = kj > key ? r[j] : best;
+            key = max(key, kj);
+        }
+        const double binv = 1.0 / best;
+        const int q = 255 - (int)(wave_max_u32(key) & 0xffu);
+        const bool inrange = q >= 0 && q < s;
+        const int lq = inrange ? (q & 63) : 0;
+        const double piv = readlane_f64(best, lq), pinv = readlane_f64(binv, lq);
+        const bool ok = inrange && fabs(piv) > 0.0 && fabs(piv) <= 1.79e308;
+        double *rk = rowk[k & 1];
+#pragma unroll
+        for (int j = 0; j < COLS; ++j) rk[tx + 64 * j] = (tx + 64 * j == q) ? 0.0 : r[j] * pinv;
+        if (tx == 0) {
+            qcol[k] = ok ? q : -1;
+            if (ok) sc[q] = -pinv;
+        }
+    };
+    if (ty == 0) stage(0, a[0]);
+    if (ty == 1) __builtin_amdgcn_s_setprio(3);
+    int failed = 0;
+#pragma unroll
+    for (int I = 0; I < ROWS; ++I) {
+        if (TY * I >= s || failed) break;
+        const int wn = min(TY, s - TY * I);
+#pragma unroll 1
+        for (int w = 0; w < wn; ++w) {
+            const int k = TY * I + w;
+            __syncthreads();
+            const double *rk = rowk[k & 1];
+            double p[COLS];
+            const int qk = qcol[k];
+#pragma unroll
+            for (int j = 0; j < COLS; ++j) p[j] = rk[tx + 64 * j];
+            const int q = __builtin_amdgcn_readfirstlane(qk);
+            if (q < 0) {  // the same for every wave
+                failed = k + 1;
+                break;
             }
-            unsigned key = pivot_key(r0, tx, !(used & 1u));
-            key = max(key, pivot_key(r1, tx + 64, !(used & 2u)));
-            key = max(key, pivot_key(r2, tx + 128, !(used & 4u)));
-            const int q = 255 - (int)(wave_max_u32(key) & 0xffu);
-            const bool inrange = q >= 0 && q < s;
-            const int jq = inrange ? (q >> 6) : 0, lq = inrange ? (q & 63) : 0;
-            const double piv = readlane_f64(jq == 0 ? r0 : (jq == 1 ? r1 : r2), lq);
-            const bool ok = inrange && fabs(piv) > 0.0 && fabs(piv) <= 1.79e308;
-            const double pinv = 1.0 / piv;
-            double *rk = rowk[k & 1];
-            rk[tx] = (tx == q) ? 0.0 : r0 * pinv;
-            rk[tx + 64] = (tx + 64 == q) ? 0.0 : r1 * pinv;
-            rk[tx + 128] = (tx + 128 == q) ? 0.0 : r2 * pinv;
-            if (tx == 0) {
-                qcol[k] = ok ? q : 0;
-                sc[ok ? q : 0] = -pinv;
-                if (!ok) s_bad = k + 1;
+            const int jq = q >> 6, lq = q & 63;
+            if (tx == lq) used |= 1u << jq;
+            if (k + 1 < s && ty == ((k + 1) & (TY - 1))) {
+                double r[COLS], rq;
+#pragma unroll
+                for (int j = 0; j < COLS; ++j) r[j] = w < TY - 1 ? a[I][j] : a[I + 1 < ROWS ? I + 1 : I][j];
+                rq = r[0];
+#pragma unroll
+                for (int j = 1; j < COLS; ++j) rq = jq == j ? r[j] : rq;
+                const double f = readlane_f64(rq, lq);
+#pragma unroll
+                for (int j = 0; j < COLS; ++j) r[j] = fma(-f, p[j], r[j]);
+                stage(k + 1, r);
+                __builtin_amdgcn_s_setprio(0);
             }
-        }
-        __syncthreads();
-        if (s_bad) break;
-        const int q = __builtin_amdgcn_readfirstlane(qcol[k]);
-        const int jq = q >> 6, lq = q & 63;
-        const double *rk = rowk[k & 1];
-        const double p0 = rk[tx], p1 = rk[tx + 64], p2 = rk[tx + 128];
-        if (tx == lq) used |= 1u << jq;
-        // factors a[r][q] of this wave's rows, from lane lq (wave-uniform)
-        double f[kRegRows];
-        if (jq == 0) {
+            // factors a[r][q] of this wave's rows, from lane lq (wave-uniform)
+            double f[ROWS];
 #pragma unroll
-            for (int r = 0; r < kRegRows; ++r) f[r] = readlane_f64(a[r][0], lq);
-        } else if (jq == 1) {
+            for (int j = 0; j < COLS; ++j)
+                if (jq == j) {
 #pragma unroll
-            for (int r = 0; r < kRegRows; ++r) f[r] = readlane_f64(a[r][1], lq);
-        } else {
+                    for (int r = 0; r < ROWS; ++r) f[r] = readlane_f64(a[r][j], lq);
+                }
 #pragma unroll
-            for (int r = 0; r < kRegRows; ++r) f[r] = readlane_f64(a[r][2], lq);
-        }
+            for (int r = 0; r < ROWS; ++r)
 #pragma unroll
-        for (int r = 0; r < kRegRows; ++r) {
-            a[r][0] = fma(-f[r], p0, a[r][0]);
-            a[r][1] = fma(-f[r], p1, a[r][1]);
-            a[r][2] = fma(-f[r], p2, a[r][2]);
-        }
-        if (ty == w) {  // row k: the staged row, -1 (1/p in the column's scale) at column q
-            const double n0 = (tx == q) ? -1.0 : p0, n1 = (tx + 64 == q) ? -1.0 : p1,
-                         n2 = (tx + 128 == q) ? -1.0 : p2;
-            switch (ik) {
-#define BIM_SET(I)      \
-    case I:             \
-        a[I][0] = n0;   \
-        a[I][1] = n1;   \
-        a[I][2] = n2;   \
-        break;
-                BIM_ROW_CASES(BIM_SET)
-#undef BIM_SET
+                for (int j = 0; j < COLS; ++j) a[r][j] = fma(-f[r], p[j], a[r][j]);
+            if (ty == w) {  // row k: the staged row, -1 (1/p in the column's scale) at column q
+#pragma unroll
+                for (int j = 0; j < COLS; ++j) a[I][j] = (tx + 64 * j == q) ? -1.0 : p[j];
             }
+            // the next step's stage starts first on its SIMD
+            if (ty == ((k + 2) & (TY - 1))) __builtin_amdgcn_s_setprio(3);
+            // one barrier per step: buffer k % 2 is staged anew (by the owner of
+            // row k + 2) only after the next barrier, which every wave reaches
+            // with its reads of this step done
         }
-        // no barrier here: the next step stages its row in the other buffer, and
-        // this buffer is rewritten only after every wave has passed the next
-        // step's barrier, i.e. has finished this step
     }
     __syncthreads();
-#undef BIM_ROW_CASES
-    if (threadIdx.x == 0 && info) info[blockIdx.x] = s_bad;
-    if (s_bad) return;
-    for (int c = threadIdx.x; c < s; c += kRegThreads) qinv[qcol[c]] = c;
+    if (threadIdx.x == 0 && info) info[blockIdx.x] = failed;
+    if (failed) return;
+    for (int c = threadIdx.x; c < s; c += (64 * TY)) qinv[qcol[c]] = c;
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kRegRows; ++i)
+    for (int i = 0; i < ROWS; ++i)
 #pragma unroll
-        for (int j = 0; j < kRegCols; ++j) {
-            const int r = ty + kRegTy * i, c = tx + 64 * j;
+        for (int j = 0; j < COLS; ++j) {
+            const int r = ty + TY * i, c = tx + 64 * j;
             if (r < s && c < s) it.Ainv[(size_t)qcol[r] * it.ldinv + qinv[c]] = a[i][j] * sc[c];
         }
+}
+
+// registers by the size: rows in steps of 32, columns of 64
+void invert_reg_launch(const InvItem *items, int batch, int s, int *info, hipStream_t st) {
+    const dim3 g(batch);
+#define BIM_INVERT(TY, R, C) hipLaunchKernelGGL((k_invert_reg<TY, R, C>), g, dim3(64 * TY), 0, st, items, s, info)
+    if (s <= 32) BIM_INVERT(16, 2, 1);
+    else if (s <= 64) BIM_INVERT(16, 4, 1);
+    else if (s <= 96) BIM_INVERT(16, 6, 2);
+    else if (s <= 128) BIM_INVERT(16, 8, 2);
+    else if (s <= 160) BIM_INVERT(16, 10, 3);
+    else BIM_INVERT(16, 12, 3);
+#undef BIM_INVERT
 }
 
 // Gauss-Jordan inversion with partial pivoting of an s x s matrix per
@@ -1019,7 +1040,7 @@ int invert_enqueue(const InvItem *items_dev, int batch, int s_dim, double *work,
     if (s_dim > kMaxS) return fail(BIM_EINVAL, "block too large to invert");
     if (batch <= 0) return BIM_OK;
     if (s_dim <= kRegMaxS)
-        hipLaunchKernelGGL(k_invert_reg, dim3(batch), dim3(kRegThreads), 0, s, items_dev, s_dim, info);
+        invert_reg_launch(items_dev, batch, s_dim, info, s);
     else
         hipLaunchKernelGGL(k_invert, dim3(batch), dim3(kInvThreads), 0, s, items_dev, s_dim, work, info);
     return hip_check(hipGetLastError(), "invert launch");
@@ -1056,12 +1077,12 @@ int split_invert_enqueue(const SplitInv &P, const SplitInv *D, int s_dim, int *i
     const int s1 = kSplitS1, r = s_dim - s1;
     const int lda = (int)P.inv11.lda, ldx = (int)P.inv11.ldinv;
     int rc;
-    hipLaunchKernelGGL(k_invert_reg, dim3(1), dim3(kRegThreads), 0, st, &D->inv11, s1, info);
+    invert_reg_launch(&D->inv11, 1, s1, info, st);
     if ((rc = gemm_enqueue(&D->T, 1, s1, r, s1, ldx, lda, r, 1.0, 0.0, st))) return rc;
     if ((rc = copy2d_enqueue(P.inv11.A + (size_t)s1 * lda + s1, lda, const_cast<double *>(P.invS.A), r, r, r, st)))
         return rc;
     if ((rc = gemm_enqueue(&D->Sc, 1, r, r, s1, lda, r, r, -1.0, 1.0, st))) return rc;
-    hipLaunchKernelGGL(k_invert_reg, dim3(1), dim3(kRegThreads), 0, st, &D->invS, r, info + 1);
+    invert_reg_launch(&D->invS, 1, r, info + 1, st);
     if ((rc = gemm_enqueue(&D->W, 1, r, s1, s1, lda, ldx, s1, 1.0, 0.0, st))) return rc;
     if ((rc = gemm_enqueue(&D->B21, 1, r, s1, r, ldx, s1, ldx, -1.0, 0.0, st))) return rc;
     if ((rc = gemm_enqueue(&D->B12, 1, s1, r, r, r, ldx, ldx, -1.0, 0.0, st))) return rc;
