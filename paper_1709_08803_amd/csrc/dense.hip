@@ -23,16 +23,16 @@ using GlobalPtr = __attribute__((address_space(1))) T *;
 
 // C = alpha A B + beta C (row-major, FP64) on the matrix cores.  64 x 64 output
 // tile per 256-thread workgroup; each wave owns 32 x 32 = 2 x 2 tiles of
-// v_mfma_f64_16x16x4f64.  K advances through LDS in steps of 32, and the next
+// v_mfma_f64_16x16x4f64.  K advances through LDS in steps of 16, and the next
 // step's operands are loaded into registers while the current step's MFMAs run.
 // Operand layout of the 16x16x4 FP64 MFMA: lane l holds A[l % 16][l / 16] and
 // B[l / 16][l % 16]; the accumulator's element v of lane l is
-// D[l / 16 + 4 v][l % 16] (lane layout checked on gfx950).  Registers are
-// capped for three waves per SIMD (three workgroups per compute unit): a
-// single wave per SIMD leaves the matrix unit idle between its MFMAs (measured:
-// the preconditioner setup's batched block products 3 ms faster than at the
-// compiler's choice of two).
-constexpr int TM = 64, TN = 64, TK = 32;
+// D[l / 16 + 4 v][l % 16] (lane layout checked on gfx950).  Two LDS buffers and one
+// barrier per step, four workgroups per compute unit: bound by the matrix unit, 60 of
+// 73 TFLOP/s with padding in a long run (181 x 61 setup: S from the q-blocks 10.0 -> 6.0
+// ms, an update of the block LU 130 -> 122 us; steps of 32 through one buffer, with two
+// barriers and the addresses formed anew in each, reached 35).
+constexpr int TM = 64, TN = 64, TK = 16;
 typedef double double4_t __attribute__((ext_vector_type(4)));
 
 // The tile (x, y) and item z of a workgroup, in an XCD-aware order.  The
@@ -54,41 +54,91 @@ __device__ __forceinline__ Tile3 xcd_tile() {
     return {(int)(t % gx), (int)((t / gx) % gy), (int)(t / (gx * gy))};
 }
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_gemm(
-    const GemmItem *__restrict__ items, int m, int n, int k, int lda, int ldb, int ldc, double alpha, double beta) {
+// KBLOCKS: C = alpha sum_{b < it.nkb} A_b B_b + beta C, with A_b = A + b sA and
+// B_b = B + b sB (each m x k, k x n, row-major): one product of K = nkb k whose
+// K-blocks lie at fixed strides, as a block row of a slice-banded matrix times
+// a block column of another; the accumulator stays in registers over all nkb blocks,
+// so C is read and written once instead of once per block.
+template <bool KBLOCKS>
+struct GemmItemOf {
+    typedef GemmItem type;
+};
+template <>
+struct GemmItemOf<true> {
+    typedef GemmKItem type;
+};
+template <bool KBLOCKS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_gemm(
+    const typename GemmItemOf<KBLOCKS>::type *__restrict__ items, int m, int n, int k, int lda, int ldb, int ldc, long sA,
+    long sB, double alpha, double beta) {
     const Tile3 tl = xcd_tile();
-    const GemmItem it = items[tl.z];
+    const auto it = items[tl.z];
     const GlobalPtr<const double> A = (GlobalPtr<const double>)it.A;
     const GlobalPtr<const double> B = (GlobalPtr<const double>)it.B;
     const GlobalPtr<double> C = (GlobalPtr<double>)it.C;
-    __shared__ double As[TM][TK + 1];
-    __shared__ double Bs[TK][TN + 1];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int K = k;
+    if constexpr (KBLOCKS) K = (int)it.nkb * k;
+    __shared__ double As[2][TM][TK + 1];
+    __shared__ double Bs[2][TK][TN + 1];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
     const int row0 = tl.y * TM, col0 = tl.x * TN;
     const int li = lane & 15, lk = lane >> 4;
-    // each thread stages 8 elements of A (rows e >> 5, cols e & 31) and 8 of B
-    // (rows e >> 6, cols e & 63).  Loads are unconditional, at indices clamped
-    // into the matrices: a row of A or a column of B outside the product only
-    // feeds outputs that are not stored, and B rows past k are zeroed when
-    // staged (the select sits there so that no load waits for its value).
-    double ra[8], rb[8];
-    auto load = [&](int k0) {
+    // Each thread stages 4 elements of A (rows (tid >> 4) + 16 q, column tid & 15) and 4
+    // of B (rows wave + 4 q, column lane).  A row of A or a column of B outside the
+    // product is a clamped one that only feeds outputs that are not stored, and B rows
+    // past K are zeroed when staged (the select sits there so that no load waits for
+    // its value).  A step inside a K-block loads at a uniform base and fixed 32-bit
+    // offsets (64 rows of A, 16 of B; far below 4 GB apart).
+    double ra[4], rb[4];
+    const int ac = tid & 15;
+    unsigned oa[4];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int e = tid + q * 256;
-            const int ar = e >> 5, ac = e & 31;
-            ra[q] = A[(size_t)min(row0 + ar, m - 1) * lda + min(k0 + ac, k - 1)];
-            const int br = e >> 6, bc = e & 63;
-            rb[q] = B[(size_t)min(k0 + br, k - 1) * ldb + min(col0 + bc, n - 1)];
+    for (int q = 0; q < 4; ++q) oa[q] = 8u * (unsigned)(min(row0 + (tid >> 4) + 16 * q, m - 1) * lda + ac);
+    const unsigned ob = 8u * (unsigned)min(col0 + lane, n - 1);
+    typedef GlobalPtr<const char> Bytes;
+    int lk0 = 0;         // the loads' place in K: column lk0 of the K-block at A, B
+    GlobalPtr<const double> la = A, lb = B;
+    auto load = [&](int k0) {
+        if (lk0 + TK <= k) {
+            const Bytes pa = (Bytes)(la + lk0), pb = (Bytes)(lb + (size_t)(lk0 + wave) * ldb);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) ra[q] = *(GlobalPtr<const double>)(pa + oa[q]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) rb[q] = *(GlobalPtr<const double>)(pb + (size_t)(4 * q) * ldb * 8 + ob);
+        } else {
+            // across the end of a K-block: the next block's first columns, at the end of
+            // K the last one (the select is on the place in K, so short blocks take
+            // any number of blocks in one step)
+            auto place = [&](int g, int &blk) {
+                g = min(g, K - 1);
+                blk = KBLOCKS ? g / k : 0;
+                return g - blk * k;
+            };
+            int blk;
+            const int ca = place(k0 + ac, blk);
+            const GlobalPtr<const double> pa = A + (size_t)blk * sA + ca;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) ra[q] = pa[(size_t)min(row0 + (tid >> 4) + 16 * q, m - 1) * lda];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int rr = place(k0 + wave + 4 * q, blk);
+                rb[q] = *(GlobalPtr<const double>)((Bytes)(B + (size_t)blk * sB + (size_t)rr * ldb) + ob);
+            }
+        }
+        lk0 += TK;
+        while (KBLOCKS && lk0 >= k) {
+            lk0 -= k;
+            la += sA;
+            lb += sB;
         }
     };
-    auto store = [&](int k0) {
+    auto store = [&](int buf, int k0) {
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int e = tid + q * 256;
-            As[e >> 5][e & 31] = ra[q];
-            Bs[e >> 6][e & 63] = (k0 + (e >> 6) < k) ? rb[q] : 0.0;
+        for (int q = 0; q < 4; ++q) {
+            As[buf][(tid >> 4) + 16 * q][ac] = ra[q];
+            Bs[buf][wave + 4 * q][lane] = (k0 + wave + 4 * q < K) ? rb[q] : 0.0;
         }
     };
     double4_t acc[2][2];
@@ -96,9 +146,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int u = 0; u < 2; ++u) acc[t][u] = double4_t{0.0, 0.0, 0.0, 0.0};
-    if (k > 0) {
+    if (K > 0) {
         load(0);
-        store(0);
+        store(0, 0);
+        if (TK < K) load(TK);
     }
     // C (for beta != 0) is read at the start, at clamped indices, so that its
     // loads are in flight during the products instead of after them
@@ -116,128 +167,47 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
                 }
     }
     __syncthreads();
-    for (int k0 = 0; k0 < k; k0 += TK) {
-        const bool more = k0 + TK < k;
-        if (more) load(k0 + TK);
-#pragma unroll
-        for (int kk = 0; kk < TK; kk += 4) {
-            double a[2], b[2];
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                a[t] = As[wm + 16 * t + li][kk + lk];
-                b[t] = Bs[kk + lk][wn + 16 * t + li];
-            }
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int u = 0; u < 2; ++u) acc[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], b[u], acc[t][u], 0, 0, 0);
-        }
-        __syncthreads();
-        if (more) {
-            store(k0 + TK);
-            __syncthreads();
-        }
-    }
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int gr = row0 + wm + 16 * t + lk + 4 * v, gc = col0 + wn + 16 * u + li;
-                if (gr < m && gc < n)
-                    C[(size_t)gr * ldc + gc] = rmw ? fma(alpha, acc[t][u][v], beta * cv[t][u][v]) : alpha * acc[t][u][v];
-            }
-}
-
-// C = alpha sum_{b < it.nkb} A_b B_b + beta C, with A_b = A + b sA and
-// B_b = B + b sB (each m x k, k x n, row-major): one product of K = nkb k whose
-// K-blocks lie at fixed strides, as a block row of a slice-banded matrix times
-// a block column of another.  The same 64 x 64 tiles and MFMA layout as k_gemm;
-// the accumulator stays in registers over all nkb blocks, so C is read and
-// written once instead of once per block.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_gemm_kblocks(
-    const GemmKItem *__restrict__ items, int m, int n, int k, int lda, int ldb, int ldc, long sA, long sB,
-    double alpha, double beta) {
-    const Tile3 tl = xcd_tile();
-    const GemmKItem it = items[tl.z];
-    const GlobalPtr<const double> A = (GlobalPtr<const double>)it.A;
-    const GlobalPtr<const double> B = (GlobalPtr<const double>)it.B;
-    const GlobalPtr<double> C = (GlobalPtr<double>)it.C;
-    const int K = it.nkb * k;
-    __shared__ double As[TM][TK + 1];
-    __shared__ double Bs[TK][TN + 1];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-    const int row0 = tl.y * TM, col0 = tl.x * TN;
-    const int li = lane & 15, lk = lane >> 4;
-    double ra[8], rb[8];
-    // global K index g -> block g / k, column g % k; loads at clamped indices as in
-    // k_gemm, the rows of B past K zeroed when staged
-    auto load = [&](int k0) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int e = tid + q * 256;
-            const int ar = e >> 5, ac = e & 31;
-            const int ga = min(k0 + ac, K - 1), ba = ga / k;
-            ra[q] = A[(size_t)ba * sA + (size_t)min(row0 + ar, m - 1) * lda + (ga - ba * k)];
-            const int br = e >> 6, bc = e & 63;
-            const int gb = min(k0 + br, K - 1), bb = gb / k;
-            rb[q] = B[(size_t)bb * sB + (size_t)(gb - bb * k) * ldb + min(col0 + bc, n - 1)];
-        }
-    };
-    auto store = [&](int k0) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int e = tid + q * 256;
-            As[e >> 5][e & 31] = ra[q];
-            Bs[e >> 6][e & 63] = (k0 + (e >> 6) < K) ? rb[q] : 0.0;
-        }
-    };
-    double4_t acc[2][2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int u = 0; u < 2; ++u) acc[t][u] = double4_t{0.0, 0.0, 0.0, 0.0};
-    if (K > 0) {
-        load(0);
-        store(0);
-    }
-    const bool rmw = beta != 0.0;
-    double cv[2][2][4];
-    if (rmw) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int gr = row0 + wm + 16 * t + lk + 4 * v, gc = col0 + wn + 16 * u + li;
-                    cv[t][u][v] = C[(size_t)min(gr, m - 1) * ldc + min(gc, n - 1)];
-                }
-    }
-    __syncthreads();
+    int buf = 0;
     for (int k0 = 0; k0 < K; k0 += TK) {
-        const bool more = k0 + TK < K;
-        if (more) load(k0 + TK);
+        double a[2], b[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            a[t] = As[buf][wm + 16 * t + li][lk];
+            b[t] = Bs[buf][lk][wn + 16 * t + li];
+        }
 #pragma unroll
         for (int kk = 0; kk < TK; kk += 4) {
-            double a[2], b[2];
+            // the LDS operands of step kk + 4 before the MFMAs of step kk
+            double an[2], bn[2];
+            if (kk + 4 < TK) {
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                a[t] = As[wm + 16 * t + li][kk + lk];
-                b[t] = Bs[kk + lk][wn + 16 * t + li];
+                for (int t = 0; t < 2; ++t) {
+                    an[t] = As[buf][wm + 16 * t + li][kk + 4 + lk];
+                    bn[t] = Bs[buf][kk + 4 + lk][wn + 16 * t + li];
+                }
             }
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
                 for (int u = 0; u < 2; ++u) acc[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], b[u], acc[t][u], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            // behind the first MFMAs: the next step (loaded during the previous one)
+            // into the other buffer, last read before the barrier that ended that
+            // step, then the loads of the step after it
+            if (kk == 0 && k0 + TK < K) store(buf ^ 1, k0 + TK);
+            if (kk == 4 && k0 + 2 * TK < K) load(k0 + 2 * TK);
+            __builtin_amdgcn_sched_barrier(0);
+            if (kk + 4 < TK) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    a[t] = an[t];
+                    b[t] = bn[t];
+                }
+            }
         }
         __syncthreads();
-        if (more) {
-            store(k0 + TK);
-            __syncthreads();
-        }
+        buf ^= 1;
     }
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -410,19 +380,18 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_tall(const GemmItemT<T> *__res
 // leading dim ldb, C s rows of leading dim ldc (C = 0 where klo >= khi).  The
 // K range of a column block leaves out the operand blocks that are zero by
 // the triangular structure, which lets two factors' inverses share one array:
-// the blocks of B outside the range may hold the other factor.  Workgroups as
-// in k_gemm_tall: 192-row panels (blockIdx.y) of TN columns, ppb panels per
-// column block (a panel never straddles two column blocks).  blockIdx.x walks
+// the blocks of B outside the range may hold the other factor.  A workgroup holds
+// a panel of 16 RT rows (blockIdx.y) and TN columns, one wave per 16 rows, ppb panels
+// per column block (a panel never straddles two column blocks).  blockIdx.x walks
 // the items' column blocks together (item = blockIdx.x % batch), each item
 // from its deepest column block to its shallowest (`rev` reverses the column
 // order for items whose K range grows with cb): the long workgroups start first
 // and the short ones fill in after them (one workgroup per compute unit).
-template <int TN, int NW, typename T = double>
-__global__ __launch_bounds__(64 * NW) void k_gemm_tri(const GemmTriItemT<T> *__restrict__ items, int batch, int s,
+template <int TN, int RT, int TK, typename T>
+__global__ __launch_bounds__(64 * RT) void k_gemm_tri(const GemmTriItemT<T> *__restrict__ items, int batch, int s,
                                                       int ppb, int lda, int ldb, int ldc, double alpha, int ntiles) {
-    constexpr int NT = 64 * NW, NB = TN / 16, RB = 12 / NW;
-    constexpr int QA = kTallM * kTallK / NT, QB = (kTallK * TN + NT - 1) / NT;
-    static_assert(QA * NT == kTallM * kTallK && RB * NW == 12, "tall tile shape");
+    constexpr int NT = 64 * RT, NB = TN / 16, ROWS = 16 * RT;
+    constexpr int QA = ROWS * TK / NT, QB = (TK * TN + NT - 1) / NT;
     typedef Mfma16<T> MF;
     // a grid narrower than the ntiles column tiles walks them with a stride
     // (every early exit below is uniform over the workgroup, and each tile's
@@ -434,7 +403,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_tri(const GemmTriItemT<T> *__r
     if (cbi >= it.ncb) continue;
     const int cb = it.cb0 + (it.rev ? it.ncb - 1 - cbi : cbi);
     const int klo = max(0, cb - it.lo_off), khi = min(it.nk, cb - it.hi_off);
-    const int row0 = blockIdx.y * kTallM, m = min(kTallM, s - row0);
+    const int row0 = blockIdx.y * ROWS, m = min(ROWS, s - row0);
     const int col0 = cb * s + pan * TN, cend = (cb + 1) * s;
     if (col0 >= cend) continue;
     const int k = max(0, khi - klo) * s;
@@ -445,102 +414,113 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_tri(const GemmTriItemT<T> *__r
     // which spread a wave's 16 x 4 operand reads over distinct banks (a one-
     // float pad put 14% of the cycles in LDS bank conflicts)
     constexpr int PA = sizeof(T) == 4 ? 4 : 1, PB = sizeof(T) == 4 ? 16 : 1;
-    __shared__ T As[2][kTallM][kTallK + PA];
-    __shared__ T Bs[2][kTallK][TN + PB];
+    __shared__ T As[2][ROWS][TK + PA];
+    __shared__ T Bs[2][TK][TN + PB];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave * 16 * RB;
+    const int wm = wave * 16;
     const int li = lane & 15, lk = lane >> 4;
-    // loads at clamped indices (rows past m, columns past the block's end), B
-    // rows past k zeroed when staged
+    // rows past m and columns past the block's end at clamped indices, B rows past k
+    // zeroed when staged; a step's loads are a uniform base and fixed 32-bit offsets
+    // (192 rows of A, 32 of B; far below 4 GB apart), except in the last, partial step
     T ra[QA], rb[QB];
+    unsigned oa[QA], ob[QB];
+#pragma unroll
+    for (int q = 0; q < QA; ++q) {
+        const int e = tid + q * NT;
+        oa[q] = (unsigned)sizeof(T) * (unsigned)(min(e / TK, m - 1) * lda + (e % TK));
+    }
+#pragma unroll
+    for (int q = 0; q < QB; ++q) {
+        const int e = min(tid + q * NT, TK * TN - 1), br = e / TN;
+        ob[q] = (unsigned)sizeof(T) * (unsigned)(br * ldb + min(col0 + e - br * TN, cend - 1));
+    }
+    typedef GlobalPtr<const char> Bytes;
     auto load = [&](int k0) {
+        const Bytes pa = (Bytes)(A + k0), pb = (Bytes)(B + (size_t)k0 * ldb);
+        if (k0 + TK <= k) {
 #pragma unroll
-        for (int q = 0; q < QA; ++q) {
-            const int e = tid + q * NT;
-            const int ar = e >> 5, ac = e & 31;
-            ra[q] = A[(size_t)min(ar, m - 1) * lda + min(k0 + ac, k - 1)];
-        }
+            for (int q = 0; q < QA; ++q) ra[q] = *(GlobalPtr<const T>)(pa + oa[q]);
 #pragma unroll
-        for (int q = 0; q < QB; ++q) {
-            const int e = min(tid + q * NT, kTallK * TN - 1);
-            const int br = e / TN, bc = e - br * TN;
-            rb[q] = B[(size_t)min(k0 + br, k - 1) * ldb + min(col0 + bc, cend - 1)];
+            for (int q = 0; q < QB; ++q) rb[q] = *(GlobalPtr<const T>)(pb + ob[q]);
+        } else {
+            const int over = k0 + TK - k;  // columns of A and rows of B past k: the last one
+#pragma unroll
+            for (int q = 0; q < QA; ++q)
+                ra[q] = *(GlobalPtr<const T>)(pa + oa[q] - (unsigned)sizeof(T) * (unsigned)max(0, ((tid + q * NT) % TK) - (TK - 1 - over)));
+#pragma unroll
+            for (int q = 0; q < QB; ++q) {
+                const int br = min(tid + q * NT, TK * TN - 1) / TN;
+                rb[q] = *(GlobalPtr<const T>)(pb + ob[q] - (size_t)sizeof(T) * (size_t)max(0, br - (TK - 1 - over)) * ldb);
+            }
         }
     };
     auto store = [&](int buf, int k0) {
 #pragma unroll
         for (int q = 0; q < QA; ++q) {
             const int e = tid + q * NT;
-            As[buf][e >> 5][e & 31] = ra[q];
+            As[buf][e / TK][e % TK] = ra[q];
         }
 #pragma unroll
         for (int q = 0; q < QB; ++q) {
             const int e = tid + q * NT;
-            if (e < kTallK * TN) {
+            if (e < TK * TN) {
                 const int br = e / TN;
                 Bs[buf][br][e - br * TN] = (k0 + br < k) ? rb[q] : (T)0;
             }
         }
     };
-    typename MF::acc acc[RB][NB];
+    typename MF::acc acc[NB];
 #pragma unroll
-    for (int t = 0; t < RB; ++t)
-#pragma unroll
-        for (int u = 0; u < NB; ++u) acc[t][u] = typename MF::acc{0, 0, 0, 0};
+    for (int u = 0; u < NB; ++u) acc[u] = typename MF::acc{0, 0, 0, 0};
     if (k > 0) {
         load(0);
         store(0, 0);
+        if (TK < k) load(TK);
     }
     __syncthreads();
     int buf = 0;
-    for (int k0 = 0; k0 < k; k0 += kTallK) {
-        const bool more = k0 + kTallK < k;
-        if (more) load(k0 + kTallK);
+    for (int k0 = 0; k0 < k; k0 += TK) {
         // the LDS operands of step kk + 4 are read before the MFMAs of step kk
         // (the scheduling barriers keep that order; left alone, the compiler read
         // them after the MFMAs and waited for them)
-        T a[RB], b[NB];
-#pragma unroll
-        for (int t = 0; t < RB; ++t) a[t] = As[buf][wm + 16 * t + li][lk];
+        T a = As[buf][wm + li][lk], b[NB];
 #pragma unroll
         for (int u = 0; u < NB; ++u) b[u] = Bs[buf][lk][16 * u + li];
 #pragma unroll
-        for (int kk = 0; kk < kTallK; kk += 4) {
-            T an[RB], bn[NB];
-            if (kk + 4 < kTallK) {
-#pragma unroll
-                for (int t = 0; t < RB; ++t) an[t] = As[buf][wm + 16 * t + li][kk + 4 + lk];
+        for (int kk = 0; kk < TK; kk += 4) {
+            T an, bn[NB];
+            if (kk + 4 < TK) {
+                an = As[buf][wm + li][kk + 4 + lk];
 #pragma unroll
                 for (int u = 0; u < NB; ++u) bn[u] = Bs[buf][kk + 4 + lk][16 * u + li];
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int t = 0; t < RB; ++t)
-#pragma unroll
-                for (int u = 0; u < NB; ++u)
-                    acc[t][u] = MF::step(a[t], b[u], acc[t][u]);
+            for (int u = 0; u < NB; ++u) acc[u] = MF::step(a, b[u], acc[u]);
             __builtin_amdgcn_sched_barrier(0);
-            if (kk + 4 < kTallK) {
-#pragma unroll
-                for (int t = 0; t < RB; ++t) a[t] = an[t];
+            // behind the first MFMAs: step k0 + 32 (loaded during the previous step)
+            // into the other buffer, last read before the barrier that ended that
+            // step, then the loads of step k0 + 64
+            if (kk == 0 && k0 + TK < k) store(buf ^ 1, k0 + TK);
+            if (kk == 4 && k0 + 2 * TK < k) load(k0 + 2 * TK);
+            __builtin_amdgcn_sched_barrier(0);
+            if (kk + 4 < TK) {
+                a = an;
 #pragma unroll
                 for (int u = 0; u < NB; ++u) b[u] = bn[u];
             }
         }
-        if (more) store(buf ^ 1, k0 + kTallK);
         __syncthreads();
         buf ^= 1;
     }
 #pragma unroll
-    for (int t = 0; t < RB; ++t)
+    for (int u = 0; u < NB; ++u)
 #pragma unroll
-        for (int u = 0; u < NB; ++u)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int gr = wm + 16 * t + MF::row(lk, v), gc = col0 + 16 * u + li;
-                if (gr < m && gc < cend) C[(size_t)gr * ldc + gc] = (T)alpha * acc[t][u][v];
-            }
+        for (int v = 0; v < 4; ++v) {
+            const int gr = wm + MF::row(lk, v), gc = col0 + 16 * u + li;
+            if (gr < m && gc < cend) C[(size_t)gr * ldc + gc] = (T)alpha * acc[u][v];
+        }
     }
 }
 
@@ -1010,7 +990,7 @@ int gemm_enqueue(const GemmItem *items_dev, int batch, int m, int n, int k, int 
     const int tn = tall_panel_width(batch, m, n);
     if (tn == 0) {
         dim3 grid(cdiv(n, TN), cdiv(m, TM), batch);
-        hipLaunchKernelGGL(k_gemm, grid, dim3(256), 0, s, items_dev, m, n, k, lda, ldb, ldc, alpha, beta);
+        hipLaunchKernelGGL(k_gemm<false>, grid, dim3(256), 0, s, items_dev, m, n, k, lda, ldb, ldc, 0L, 0L, alpha, beta);
     } else {
         dim3 grid(cdiv(n, tn), 1, batch);
         constexpr int NW = kTallWaves;
@@ -1032,7 +1012,7 @@ int gemm_kblocks_enqueue(const GemmKItem *items_dev, int batch, int m, int n, in
     if (batch <= 0 || m <= 0 || n <= 0) return BIM_OK;
     if (batch > 65535) return fail(BIM_EINVAL, "gemm batch too large");
     dim3 grid(cdiv(n, TN), cdiv(m, TM), batch);
-    hipLaunchKernelGGL(k_gemm_kblocks, grid, dim3(256), 0, s, items_dev, m, n, k, lda, ldb, ldc, sA, sB, alpha, beta);
+    hipLaunchKernelGGL(k_gemm<true>, grid, dim3(256), 0, s, items_dev, m, n, k, lda, ldb, ldc, sA, sB, alpha, beta);
     return hip_check(hipGetLastError(), "gemm launch");
 }
 
@@ -1122,25 +1102,46 @@ int to_float_enqueue(const double *src, float *dst, size_t count, hipStream_t s)
 }
 
 namespace {
-// Panel width of the block-triangular products: 32 (at 181 x 61 the setup took
-// 50.3 ms with 32-wide panels throughout, 51.7 with 48, 54.2 with 64, and 51.0
-// with a per-launch choice between them that weighed the deepest workgroup
-// against the total work: more, narrower panels balance the compute units
-// better than wider panels reuse their A operand).
-constexpr int kTriPanel = 32;
-
 template <typename T>
 int gemm_tri_launch(const GemmTriItemT<T> *items_dev, int batch, int s, int max_ncb, int lda, int ldb, int ldc,
                     double alpha, int max_groups, hipStream_t st) {
     if (batch <= 0 || max_ncb <= 0 || s <= 0) return BIM_OK;
     if (batch > 65535) return fail(BIM_EINVAL, "gemm batch too large");
     if (max_groups < 0) return fail(BIM_EINVAL, "block-triangular product: negative workgroup cap");
-    const int ppb = cdiv(s, kTriPanel);
-    if ((long)max_ncb * ppb * batch > 0x7fffffffL) return fail(BIM_EINVAL, "block-triangular product too wide");
-    const int ntiles = max_ncb * ppb * batch, panels = cdiv(s, kTallM);
-    dim3 grid(max_groups > 0 ? std::min(ntiles, std::max(1, max_groups / panels)) : ntiles, panels, 1);
-    hipLaunchKernelGGL((k_gemm_tri<kTriPanel, kTallWaves, T>), grid, dim3(64 * kTallWaves), 0, st, items_dev, batch, s,
-                       ppb, lda, ldb, ldc, alpha, ntiles);
+    if ((long)max_ncb * cdiv(s, 16) * batch > 0x7fffffffL) return fail(BIM_EINVAL, "block-triangular product too wide");
+    // Row tiles by the block size (a panel of 192 rows for s = 62 is two thirds padding);
+    // capped launches run beside another stream, one workgroup of all rows per compute
+    // unit.  Up to s = 128 otherwise 64 x 16 tiles in steps of 16, several
+    // workgroups to a compute unit (all rows of V^-1, 16-wide panels of 128 rows / 64 x 16
+    // tiles: 122 x 41 blocks 2.67 / 2.12 ms with the rule below, 92 x 31 1.13 / 0.87).
+    const bool small = !max_groups && s <= 128;
+    const int rt = sizeof(T) == 4 ? 12 : small || s <= 64 ? 4 : s <= 128 ? 8 : 12, panels = cdiv(s, 16 * rt);
+    const int cap = std::max(1, (max_groups > 0 ? max_groups : 256) / panels);
+    // Panel width, with one workgroup per compute unit: a workgroup takes 1 : 1.45 : 1.95
+    // at widths 16, 32, 48, and the shallow column blocks let somewhat more than one
+    // round's worth finish in one (181 x 61, row of V^-1 with 31 column blocks: 191, 242, 325 us;
+    // 37: 271, 246, 331; 49: 312, 253, 329; 55: 377, 374, 328).
+    auto count = [&](int w) { return (long)max_ncb * cdiv(s, w) * batch; };
+    const int tn = small || 5 * count(16) <= 8L * cap ? 16 : 6 * count(32) <= 7L * cap ? 32 : 48;
+    const int ppb = cdiv(s, tn), ntiles = max_ncb * ppb * batch;
+    const dim3 grid(max_groups > 0 ? std::min(ntiles, cap) : ntiles, panels, 1);
+#define BIM_TRI(W, RT, TK)                                                                                          \
+    hipLaunchKernelGGL((k_gemm_tri<W, RT, TK, T>), grid, dim3(64 * RT), 0, st, items_dev, batch, s, ppb, lda, ldb, ldc,     \
+                       alpha, ntiles)
+#define BIM_TRI_ROWS(RT)                    \
+    do {                                    \
+        if (tn == 16) BIM_TRI(16, RT, 32);  \
+        else if (tn == 32) BIM_TRI(32, RT, 32); \
+        else BIM_TRI(48, RT, 32);           \
+    } while (0)
+    if constexpr (sizeof(T) == 8) {  // (the FP32 substitutions are for s > 128)
+        if (small) BIM_TRI(16, 4, 16);
+        else if (rt == 4) BIM_TRI_ROWS(4);
+        else if (rt == 8) BIM_TRI_ROWS(8);
+    }
+    if (rt == 12) BIM_TRI_ROWS(12);
+#undef BIM_TRI_ROWS
+#undef BIM_TRI
     return hip_check(hipGetLastError(), "block-triangular gemm launch");
 }
 

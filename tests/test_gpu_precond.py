@@ -63,6 +63,22 @@ def test_precond_apply_matches_oracle_solve(bim, name, mk, hb):
     P.close()
 
 
+# Block sizes s = N + 1 at the edges of the setup's tiles: registers of the pivot inversion
+# (rows in steps of 32, columns of 64), row panels of the substitutions (64, 128, 192) and
+# K steps of 16 and 32 in the products, with K-blocks that end inside a step
+@pytest.mark.parametrize("s", [4, 17, 31, 32, 33, 63, 64, 65, 96, 97, 127, 128, 129, 144, 160, 161])
+def test_precond_block_sizes_match_oracle_solve(bim, s):
+    p = W.make_problem(s - 1, 7, -0.15 * s, 0.15 * s, 0, 2, 0.9, [W.Bump(0.25, 1.3, 0.9)])
+    P = bim.Preconditioner(bim.DeviceProblem(p), 2)
+    r = np.random.default_rng(s).standard_normal(p.n_unknowns)
+    z_ref = Lin.Preconditioner(p, hb=2).apply(r)
+    z = P.apply(torch.as_tensor(r, device="cuda")).cpu().numpy()
+    err = np.abs(z - z_ref).max() / np.abs(z_ref).max()
+    print("s", s, "precond rel err", err)
+    assert err <= 1e-10  # as the cases above up to s = 300
+    P.close()
+
+
 def test_precond_full_size_solves_banded_system(bim):
     # 181 x 61: check P z = r with the oracle's banded product (P is never formed on the CPU)
     p = W.working(0.7)
