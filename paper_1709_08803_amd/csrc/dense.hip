@@ -4,6 +4,8 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "bim_common.h"
@@ -524,34 +526,36 @@ __global__ __launch_bounds__(64 * RT) void k_gemm_tri(const GemmTriItemT<T> *__r
     }
 }
 
-// In-place Gauss-Jordan inversion of one s x s block (s <= 192) per 1024-thread
-// workgroup, with the matrix held in registers: wave ty (= tid / 64, uniform in
-// the wave) owns rows ty + 16 i (i < ROWS) and lane tx columns tx + 64 j (j < COLS).
+// In-place Gauss-Jordan inversion of one s x s block (s <= 192) per workgroup, with the
+// matrix held in matrix-core accumulators: wave w < NT owns rows 16 w .. 16 w + 15 as NT
+// tiles of 16 x 16 (element v of lane l: row l / 16 + 4 v, column l % 16).
 // Rows are eliminated in their natural order k = 0 .. s-1 with partial
 // pivoting over the columns (the pivot of row k is its largest entry among the
 // columns not yet used: partial pivoting of the transpose), so that the row
-// being eliminated is known to every wave, and the pivot column q is read out
-// of lane q % 64 with wave-uniform lane reads.  A column that has served as a
+// being eliminated is known to every wave.  A column that has served as a
 // pivot column is kept in its own scale: its true values are the stored ones
 // times sc[q] = -1/p (row operations commute with column scaling), so that
-// no step has to rescale it.  Step k, between two barriers:
-//   the wave that owns row k + 1 updates that row first, finds its pivot column (a
-//   DPP maximum of packed pivot keys) and stages it, scaled by 1/p and with 0 at
-//   that column, in the other of two LDS buffers;
-//   every row r: a[r][c] -= a[r][q] * rowk[c] (column q keeps a[r][q], which
+// no step has to rescale it.  Step k:
+//   row k, scaled by 1/p and with 0 at its pivot column q, is staged;
+//   every row r: a[r][c] -= a[r][q] * staged[c] (column q keeps a[r][q], which
 //   is its new value -a[r][q]/p in the scale sc[q]);
 //   row k becomes the staged row with -1 (= 1/p in that scale) at column q.
-// After s steps the registers hold the inverse with rows and columns permuted
+// After s steps the accumulators hold the inverse with rows and columns permuted
 // by the pivot columns, storage[r][q_c] sc[q_c] = inverse[q_r][c]; the
-// write-out applies the scales and undoes the permutation.  The loop over k / 16 is
-// unrolled, so that every register index is constant (a switch over the rows costs a
-// chain of branches in every step).
-// Bound by the step (about 2100 cycles at s = 182, 1000 at s = 32): the four waves of a
-// SIMD issue some 95 instructions each (36 FMAs, 24 lane reads), the next pivot's chain
-// (key maximum, reciprocal, staging: 500 cycles) runs beside them at a higher wave
-// priority, the barrier costs 250.  Registers of the block's own size, the chain
-// before the barrier instead of after it, no switch (s = 182: 193 -> 184 us; 122: 103 -> 94;
-// 92: 102 -> 64; 62: 102 -> 33; 32: 37 -> 15).  Eight waves instead of 16: 190 us and 93.
+// write-out applies the scales and undoes the permutation.
+//
+// Four steps to a block, one barrier to a block.  A wave of its own (NT) takes the four
+// rows of the next block (accumulator element v of one wave's tiles, handed over in
+// LDS before this block's update), updates them, finds their pivots and stages
+// them; meanwhile the others update their rows by this block: factors a[r][q_j] out of
+// the accumulators through LDS, corrected for the steps before j, and one
+// 16x16x4 MFMA per tile, which is the chain of the four steps' fused multiply-adds
+// (bit for bit; checked on gfx950).
+// Bound by the block: about 4000 cycles for the four pivots (key maximum, reciprocal,
+// staging, the other three rows: 750 to 850 each) and, from s = 100 on, the waves that update
+// (s = 182: 3072 cycles of MFMA on each of three SIMDs, which hold up the vector
+// instructions beside them).  One pivot to a barrier, lane reads and vector multiply-adds
+// took 184 us at s = 182, 88 at 122, 60 at 92, 16.6 at 32; now 151, 64, 44, 14.2.
 constexpr int kRegMaxS = 192;
 
 // Largest value over the wave (unsigned): DPP shifts within rows of 16 lanes,
@@ -566,15 +570,6 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
     return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-// Pivot key of column c with value v: the upper 24 bits of the upper word of
-// |v| (a non-negative double orders like its bit pattern; 12 mantissa bits
-// are ample to choose a pivot), then 255 - c, so that ties go to the lowest
-// column.  Columns already used (or beyond s) have key 0.
-__device__ __forceinline__ unsigned pivot_key(double v, int c, bool usable) {
-    const unsigned hi = (unsigned)((unsigned long long)__double_as_longlong(fabs(v)) >> 32);
-    return usable ? ((hi & 0xffffff00u) | (unsigned)(255 - c)) : 0u;
-}
-
 __device__ __forceinline__ double readlane_f64(double v, int lane) {
     const unsigned long long b = (unsigned long long)__double_as_longlong(v);
     const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b & 0xffffffffull), lane);
@@ -582,137 +577,274 @@ __device__ __forceinline__ double readlane_f64(double v, int lane) {
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// ROWS >= s / TY, COLS >= s / 64
-template <int TY, int ROWS, int COLS>
-__global__ __launch_bounds__(64 * TY) void k_invert_reg(const InvItem *__restrict__ items, int s,
-                                                            int *__restrict__ info) {
-    const InvItem it = items[blockIdx.x];
-    const int tx = threadIdx.x & 63;
-    const int ty = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    __shared__ double rowk[2][64 * COLS], sc[64 * COLS];
-    __shared__ int qcol[64 * COLS], qinv[64 * COLS];  // qcol: -1 where no pivot was found
-    double a[ROWS][COLS];
-#pragma unroll
-    for (int i = 0; i < ROWS; ++i)
-#pragma unroll
-        for (int j = 0; j < COLS; ++j) {
-            const int r = ty + TY * i, c = tx + 64 * j;
-            a[i][j] = (r < s && c < s) ? it.A[(size_t)r * it.lda + c] : 0.0;
-        }
-    unsigned used = 0;  // bit j: column tx + 64 j is a pivot column already (or lies beyond s)
-#pragma unroll
-    for (int j = 0; j < COLS; ++j)
-        if (tx + 64 * j >= s) used |= 1u << j;
-    for (int c = threadIdx.x; c < 64 * COLS; c += (64 * TY)) sc[c] = 1.0;
-    __syncthreads();
-    // the pivot column of row k, whose elements are r, and the staged row
-    auto stage = [&](int k, const double (&r)[COLS]) {
-        // each lane's own candidate and its reciprocal (beside the maximum over the wave)
-        unsigned key = pivot_key(r[0], tx, !(used & 1u));
-        double best = r[0];
-#pragma unroll
-        for (int j = 1; j < COLS; ++j) {
-            const unsigned kj = pivot_key(r[j], tx + 64 * j, !(used & (1u << j)));
-            best = kj > key ? r[j] : best;
-            key = max(key, kj);
-        }
-        const double binv = 1.0 / best;
-        const int q = 255 - (int)(wave_max_u32(key) & 0xffu);
-        const bool inrange = q >= 0 && q < s;
-        const int lq = inrange ? (q & 63) : 0;
-        const double piv = readlane_f64(best, lq), pinv = readlane_f64(binv, lq);
-        const bool ok = inrange && fabs(piv) > 0.0 && fabs(piv) <= 1.79e308;
-        double *rk = rowk[k & 1];
-#pragma unroll
-        for (int j = 0; j < COLS; ++j) rk[tx + 64 * j] = (tx + 64 * j == q) ? 0.0 : r[j] * pinv;
-        if (tx == 0) {
-            qcol[k] = ok ? q : -1;
-            if (ok) sc[q] = -pinv;
-        }
-    };
-    if (ty == 0) stage(0, a[0]);
-    if (ty == 1) __builtin_amdgcn_s_setprio(3);
-    int failed = 0;
-#pragma unroll
-    for (int I = 0; I < ROWS; ++I) {
-        if (TY * I >= s || failed) break;
-        const int wn = min(TY, s - TY * I);
-#pragma unroll 1
-        for (int w = 0; w < wn; ++w) {
-            const int k = TY * I + w;
-            __syncthreads();
-            const double *rk = rowk[k & 1];
-            double p[COLS];
-            const int qk = qcol[k];
-#pragma unroll
-            for (int j = 0; j < COLS; ++j) p[j] = rk[tx + 64 * j];
-            const int q = __builtin_amdgcn_readfirstlane(qk);
-            if (q < 0) {  // the same for every wave
-                failed = k + 1;
-                break;
-            }
-            const int jq = q >> 6, lq = q & 63;
-            if (tx == lq) used |= 1u << jq;
-            if (k + 1 < s && ty == ((k + 1) & (TY - 1))) {
-                double r[COLS], rq;
-#pragma unroll
-                for (int j = 0; j < COLS; ++j) r[j] = w < TY - 1 ? a[I][j] : a[I + 1 < ROWS ? I + 1 : I][j];
-                rq = r[0];
-#pragma unroll
-                for (int j = 1; j < COLS; ++j) rq = jq == j ? r[j] : rq;
-                const double f = readlane_f64(rq, lq);
-#pragma unroll
-                for (int j = 0; j < COLS; ++j) r[j] = fma(-f, p[j], r[j]);
-                stage(k + 1, r);
-                __builtin_amdgcn_s_setprio(0);
-            }
-            // factors a[r][q] of this wave's rows, from lane lq (wave-uniform)
-            double f[ROWS];
-#pragma unroll
-            for (int j = 0; j < COLS; ++j)
-                if (jq == j) {
-#pragma unroll
-                    for (int r = 0; r < ROWS; ++r) f[r] = readlane_f64(a[r][j], lq);
-                }
-#pragma unroll
-            for (int r = 0; r < ROWS; ++r)
-#pragma unroll
-                for (int j = 0; j < COLS; ++j) a[r][j] = fma(-f[r], p[j], a[r][j]);
-            if (ty == w) {  // row k: the staged row, -1 (1/p in the column's scale) at column q
-#pragma unroll
-                for (int j = 0; j < COLS; ++j) a[I][j] = (tx + 64 * j == q) ? -1.0 : p[j];
-            }
-            // the next step's stage starts first on its SIMD
-            if (ty == ((k + 2) & (TY - 1))) __builtin_amdgcn_s_setprio(3);
-            // one barrier per step: buffer k % 2 is staged anew (by the owner of
-            // row k + 2) only after the next barrier, which every wave reaches
-            // with its reads of this step done
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0 && info) info[blockIdx.x] = failed;
-    if (failed) return;
-    for (int c = threadIdx.x; c < s; c += (64 * TY)) qinv[qcol[c]] = c;
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < ROWS; ++i)
-#pragma unroll
-        for (int j = 0; j < COLS; ++j) {
-            const int r = ty + TY * i, c = tx + 64 * j;
-            if (r < s && c < s) it.Ainv[(size_t)qcol[r] * it.ldinv + qinv[c]] = a[i][j] * sc[c];
-        }
+// f(0), f(1), .. with constant indices from the start: arrays indexed by the counters of
+// loops that are unrolled later have ended in scratch memory here.
+template <typename F, int... I>
+__device__ __forceinline__ void unrolled_over(F &&f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void unrolled(F &&f) {
+    unrolled_over(f, std::make_integer_sequence<int, N>{});
 }
 
-// registers by the size: rows in steps of 32, columns of 64
+// The accumulators are indexed by wave-uniform values in three places, each a choice of
+// constant indices.  The empty asm statements differ between the choices, which
+// keeps the compiler from merging them into one access with a selected
+// address (the accumulators would then live in scratch memory: 289 us for s = 122).
+template <int I>
+__device__ __forceinline__ double pinned(double v) {
+    asm volatile("; choice %1" : "+v"(v) : "n"(I));
+    return v;
+}
+// the four accumulator elements of tile u (LO <= u < HI) to out[v stride]
+template <int LO, int HI, int NT>
+__device__ __forceinline__ void put_tile(const double4_t (&acc)[NT], int u, double *out, int stride) {
+    if constexpr (HI - LO == 1) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) out[v * stride] = pinned<LO>(acc[LO][v]);
+    } else {
+        constexpr int MID = (LO + HI) / 2;
+        if (u < MID) put_tile<LO, MID, NT>(acc, u, out, stride);
+        else put_tile<MID, HI, NT>(acc, u, out, stride);
+    }
+}
+// element v of every tile, to or from x[16 u] (selects: a branch over v would merge
+// whole accumulators at its end)
+template <int NT>
+__device__ __forceinline__ void put_rows(const double4_t (&acc)[NT], int v, double *x) {
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+        const double a = v & 1 ? acc[u][1] : acc[u][0], b = v & 1 ? acc[u][3] : acc[u][2];
+        x[16 * u] = v & 2 ? b : a;
+    }
+}
+template <int NT>
+__device__ __forceinline__ void get_rows(double4_t (&acc)[NT], int v, const double *x) {
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+        const double d = x[16 * u];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[u][q] = v == q ? d : acc[u][q];
+    }
+}
+
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// NT >= s / 16
+template <int NT>
+__global__ __launch_bounds__(256 * ((NT + 2) / 3)) void k_invert_reg(const InvItem *__restrict__ items, int s,
+                                                              int *__restrict__ info) {
+    constexpr int NC = 16 * NT, COLS = (NC + 63) / 64, LD = 64 * COLS;
+    const InvItem it = items[blockIdx.x];
+    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+    // Waves go to the four SIMDs in turn: the pivot wave gets one of its own (wave 3; the
+    // others of that SIMD end here), as its FP64 instructions would otherwise
+    // wait for the MFMAs of its neighbours (64 cycles each: 6400 cycles for four
+    // pivots at s = 182 instead of 4200).
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int w = (wave & 3) == 3 ? (wave == 3 ? NT : NT + 1) : (wave >> 2) * 3 + (wave & 3);
+    if (w > NT || (w == NT && wave != 3)) return;
+    const int tid = w * 64 + lane;  // of 64 (NT + 1)
+    __shared__ double raw[2][4][LD];   // a block's rows before the previous block's update
+    __shared__ double staged[2][4][LD];
+    __shared__ double done[2][4][LD];  // a block's rows after it
+    __shared__ double fac[NT][16][5];  // a wave's a[r][q_j] (row, j)
+    __shared__ double sc[LD];
+    __shared__ int qcol[LD], qinv[LD];  // qcol: -1 where no pivot was found
+    const int nb = (s + 3) >> 2;
+    for (int c = tid; c < LD; c += 64 * (NT + 1)) sc[c] = 1.0;
+    int failed = 0;
+    if (w < NT) {
+        double4_t acc[NT];
+#pragma unroll
+        for (int u = 0; u < NT; ++u)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int r = 16 * w + lk + 4 * v, c = 16 * u + li;
+                acc[u][v] = (r < s && c < s) ? it.A[(size_t)r * it.lda + c] : 0.0;
+            }
+        // the rows of block b (element b % 4 of wave b / 4) to raw
+        auto hand_over = [&](int b) { put_rows<NT>(acc, b & 3, &raw[b & 1][lk][li]); };
+        if (w == 0) {
+            hand_over(0);
+            hand_over(1);
+        }
+        __syncthreads();
+        for (int b = 0; b < nb; ++b) {
+            __syncthreads();
+            int q[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                q[j] = __builtin_amdgcn_readfirstlane(qcol[4 * b + j]);
+                if (q[j] < 0 && !failed) failed = 4 * b + j + 1;
+            }
+            if (failed) break;  // the same for every wave
+            const double(*st)[LD] = staged[b & 1];
+            // factors of this wave's rows
+            // (once per tile that holds any of the four pivot columns)
+            for (unsigned left = 15; left != 0;) {
+                const int j0 = __builtin_ctz(left);
+                const int u = (j0 == 0 ? q[0] : j0 == 1 ? q[1] : j0 == 2 ? q[2] : q[3]) >> 4;
+                int mine = -1;
+#pragma unroll
+                for (int j = 3; j >= 0; --j)
+                    if ((left >> j & 1) && q[j] >> 4 == u) {
+                        left &= ~(1u << j);
+                        mine = li == (q[j] & 15) ? j : mine;
+                    }
+                if (mine >= 0) put_tile<0, NT, NT>(acc, u, &fac[w][lk][mine], 4 * 5);
+            }
+            wave_lds_sync();
+            double f[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                f[j] = fac[w][li][j];
+#pragma unroll
+                for (int i = 0; i < j; ++i) f[j] = fma(-f[i], st[i][q[j]], f[j]);
+                if (4 * b + j >= s) f[j] = 0.0;  // no such row
+            }
+            double na = lk == 0 ? -f[0] : lk == 1 ? -f[1] : lk == 2 ? -f[2] : -f[3];
+            const bool own = w == b >> 2;  // the block's own rows come from the wave that staged them
+            if (own && (li >> 2) == (b & 3)) na = 0.0;
+#pragma unroll
+            for (int u = 0; u < NT; ++u)
+                acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(na, st[lk][16 * u + li], acc[u], 0, 0, 0);
+            if (own) get_rows<NT>(acc, b & 3, &done[b & 1][lk][li]);
+            if (b + 2 < nb && w == (b + 2) >> 2) hand_over(b + 2);
+        }
+        __syncthreads();
+        if (tid == 0 && info) info[blockIdx.x] = failed;
+        if (failed) return;
+        for (int c = tid; c < s; c += 64 * NT) qinv[qcol[c]] = c;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < NT; ++u)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int r = 16 * w + lk + 4 * v, c = 16 * u + li;
+                if (r < s && c < s) it.Ainv[(size_t)qcol[r] * it.ldinv + qinv[c]] = acc[u][v] * sc[c];
+            }
+    } else {
+        // columns lane + 64 j; the pivot key of a column is the upper 24 bits of the upper
+        // word of |v| (a non-negative double orders like its bit pattern; 12 mantissa
+        // bits are ample to choose a pivot), then 255 - column, so that ties go to the
+        // lowest column, and 0 for columns already used (or beyond s)
+        __builtin_amdgcn_s_setprio(3);
+        unsigned high[COLS], low[COLS];
+        unrolled<COLS>([&](auto j) __attribute__((always_inline)) {
+            const bool usable = lane + 64 * j < s;
+            high[j] = usable ? 0x7fffff00u : 0u;
+            low[j] = usable ? 255u - (lane + 64 * j) : 0u;
+        });
+        double R[4][COLS], p[4][COLS];
+        int q[4] = {0, 0, 0, 0};
+        // row r minus its element f of the pivot column times the staged row i
+        auto subtract = [&](auto r, double f, auto i) __attribute__((always_inline)) {
+            unrolled<COLS>([&](auto j) __attribute__((always_inline)) { R[r][j] = fma(-f, p[i][j], R[r][j]); });
+        };
+        // the other rows of the block minus the staged row i of pivot column c
+        auto eliminate = [&](auto i, auto group, int c) __attribute__((always_inline)) {
+            double f[4];
+            unrolled<4>([&](auto r) __attribute__((always_inline)) {
+                if constexpr (r != i) f[r] = readlane_f64(R[r][group], c & 63);
+            });
+            unrolled<4>([&](auto r) __attribute__((always_inline)) {
+                if constexpr (r != i) subtract(r, f[r], i);
+            });
+        };
+        __syncthreads();
+        for (int b = 0; b <= nb; ++b) {  // stages block b, during the other waves' update by block b - 1
+            if (b > 0) {
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (q[j] < 0 && !failed) failed = 4 * (b - 1) + j + 1;
+                if (failed || b == nb) break;
+            }
+            unrolled<4>([&](auto r) __attribute__((always_inline)) {
+                unrolled<COLS>([&](auto j) __attribute__((always_inline)) { R[r][j] = raw[b & 1][r][lane + 64 * j]; });
+            });
+            if (b > 0) {
+                // factors as the other waves form theirs: row lane % 4 in this lane
+                const double(*prev)[LD] = staged[(b & 1) ^ 1];
+                double f[4];
+                unrolled<4>([&](auto j) __attribute__((always_inline)) {
+                    f[j] = raw[b & 1][lane & 3][q[j]];
+                    unrolled<4>([&](auto i) __attribute__((always_inline)) {
+                        if constexpr (i < j) f[j] = fma(-f[i], prev[i][q[j]], f[j]);
+                    });
+                });
+                unrolled<4>([&](auto i) __attribute__((always_inline)) {
+                    unrolled<4>([&](auto r) __attribute__((always_inline)) { subtract(r, readlane_f64(f[i], r), i); });
+                });
+            }
+            double(*st)[LD] = staged[b & 1];
+            double scale = 0.0;  // lane i: -1/p of step i
+            unrolled<4>([&](auto i) __attribute__((always_inline)) {
+                const int k = 4 * b + i;
+                if (k >= s) {  // no such row: nothing is subtracted, its zeros stay
+                    unrolled<COLS>([&](auto j) __attribute__((always_inline)) { st[i][lane + 64 * j] = p[i][j] = 0.0; });
+                    q[i] = 0;
+                    return;
+                }
+                // each lane's own candidate and its reciprocal (beside the maximum over the wave)
+                unsigned key = 0;
+                double best = 0.0;
+                unrolled<COLS>([&](auto j) __attribute__((always_inline)) {
+                    const unsigned kj =
+                        ((unsigned)((unsigned long long)__double_as_longlong(R[i][j]) >> 32) & high[j]) | low[j];
+                    best = j == 0 || kj > key ? R[i][j] : best;
+                    key = max(key, kj);
+                });
+                const double binv = 1.0 / best;
+                const int c = 255 - (int)(wave_max_u32(key) & 0xffu);
+                const bool inrange = c < s;
+                const int qi = inrange ? c : 0, lq = qi & 63;
+                const double piv = readlane_f64(best, lq), pinv = readlane_f64(binv, lq);
+                const bool ok = inrange && fabs(piv) > 0.0 && fabs(piv) <= 1.79e308;
+                bool at[COLS];
+                unrolled<COLS>([&](auto j) __attribute__((always_inline)) {
+                    at[j] = lane + 64 * j == qi;
+                    st[i][lane + 64 * j] = p[i][j] = at[j] ? 0.0 : R[i][j] * pinv;
+                    high[j] = at[j] ? 0u : high[j];
+                    low[j] = at[j] ? 0u : low[j];
+                });
+                if (COLS == 1 || qi < 64) eliminate(i, std::integral_constant<int, 0>{}, qi);
+                else if (COLS == 2 || qi < 128) eliminate(i, std::integral_constant<int, (COLS > 1)>{}, qi);
+                else eliminate(i, std::integral_constant<int, (COLS > 2 ? 2 : 0)>{}, qi);
+                unrolled<COLS>([&](auto j) __attribute__((always_inline)) { R[i][j] = at[j] ? -1.0 : p[i][j]; });
+                q[i] = ok ? qi : -1;
+                scale = lane == i ? -pinv : scale;
+            });
+            unrolled<4>([&](auto r) __attribute__((always_inline)) {
+                unrolled<COLS>([&](auto j) __attribute__((always_inline)) { done[b & 1][r][lane + 64 * j] = R[r][j]; });
+            });
+            if (lane < 4) {
+                const int ql = lane == 0 ? q[0] : lane == 1 ? q[1] : lane == 2 ? q[2] : q[3];
+                qcol[4 * b + lane] = ql;
+                if (ql >= 0 && 4 * b + lane < s) sc[ql] = scale;
+            }
+        }
+        __syncthreads();
+        if (failed) return;
+        __syncthreads();
+    }
+}
+
+// tiles by the size, in steps of 32
 void invert_reg_launch(const InvItem *items, int batch, int s, int *info, hipStream_t st) {
-    const dim3 g(batch);
-#define BIM_INVERT(TY, R, C) hipLaunchKernelGGL((k_invert_reg<TY, R, C>), g, dim3(64 * TY), 0, st, items, s, info)
-    if (s <= 32) BIM_INVERT(16, 2, 1);
-    else if (s <= 64) BIM_INVERT(16, 4, 1);
-    else if (s <= 96) BIM_INVERT(16, 6, 2);
-    else if (s <= 128) BIM_INVERT(16, 8, 2);
-    else if (s <= 160) BIM_INVERT(16, 10, 3);
-    else BIM_INVERT(16, 12, 3);
+#define BIM_INVERT(NT) hipLaunchKernelGGL(k_invert_reg<NT>, dim3(batch), dim3(256 * ((NT + 2) / 3)), 0, st, items, s, info)
+    if (s <= 32) BIM_INVERT(2);
+    else if (s <= 64) BIM_INVERT(4);
+    else if (s <= 96) BIM_INVERT(6);
+    else if (s <= 128) BIM_INVERT(8);
+    else if (s <= 160) BIM_INVERT(10);
+    else BIM_INVERT(12);
 #undef BIM_INVERT
 }
 
