@@ -404,7 +404,7 @@ typedef struct bim_exact_config {
     double decay;             /* <= 0: 36 (k-cutoff where the transform is exp(-decay) of its scale) */
     double psi_width_max;     /* <= 0: 0.1 */
     double grade_start;       /* <= 0: 1e-10 (first graded psi panel next to psi_0) */
-    int32_t workgroups;       /* <= 0: about 2048 for the contraction */
+    int32_t workgroups;       /* <= 0: whole rounds of 512 for the contraction */
     int32_t timing;           /* 1: time the contraction kernel and the whole call with HIP events */
     int32_t tile_cols;        /* targets along y per workgroup tile: 64, 96 or 128; <= 0: chosen for M */
 } bim_exact_config;

@@ -223,21 +223,32 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 // from node data loaded during step st - 1.
 // Operand generation: thread t takes node gq = t / 16 of the step and the four
 // consecutive rows (and columns) 4 (t % 16) .. + 3 of the tile: one sincos at the
-// first row, then three rotations by exp(+-i a dx) (the sign of the step of |xi|),
-// the same for the columns with exp(i b dy); rows on both sides of the bump
-// centre (|xi| not monotone) take a sincos each.
+// first row, then three rotations by exp(i a dx), the same for the columns with
+// exp(i b dy).
 struct NodeData {
     double a, b, w, ca, sa, cb, sb;
 };
 
+// A place in the node steps: step s of the sq steps of one bump.  Advanced by one, not
+// divided out of the step's number (a 64-bit division is 120 scalar instructions, twice a
+// step).
+struct Place {
+    int bump;
+    long s;
+    __device__ __forceinline__ void next(long sq) {
+        if (++s == sq) {
+            s = 0;
+            ++bump;
+        }
+    }
+};
 __device__ __forceinline__ void load_node(const double *__restrict__ na, const double *__restrict__ nb,
                                           const double *__restrict__ nw, const double *__restrict__ rot, long qpad,
-                                          long sq, long st, int gq, NodeData &nd) {
-    const int bump = (int)(st / sq);
-    const long q = (st - (long)bump * sq) * kStep + gq;
+                                          const Place &at, int gq, NodeData &nd) {
+    const long q = at.s * kStep + gq;
     nd.a = na[q];
     nd.b = nb[q];
-    nd.w = nw[(long)bump * qpad + q];
+    nd.w = nw[(long)at.bump * qpad + q];
     nd.ca = rot[q];
     nd.sa = rot[qpad + q];
     nd.cb = rot[2 * qpad + q];
@@ -252,59 +263,85 @@ struct LdsStride {
     static constexpr int value = W + 16;
 };
 
+// sin and cos in about 35 instructions, to an ulp or so: x - n pi / 2 with pi / 2 in two
+// doubles (the first product is exact in the fused operation), then the Taylor series
+// on |r| <= pi / 4 to r^17 and r^16 (the next terms: 1e-19 and 2e-18).  The library's
+// function takes three times as many, which the FP64 matrix unit has to wait for; it
+// is left the arguments whose n is not small.
+__device__ __forceinline__ void sincos_fast(double x, double *sn, double *cs) {
+    if (!(fabs(x) < 1048576.0)) {
+        sincos(x, sn, cs);
+        return;
+    }
+    const double n = rint(x * 0.63661977236758134308);  // 2 / pi
+    double r = fma(-n, 1.57079632679489661923, x);
+    r = fma(-n, 6.12323399573676588613e-17, r);
+    const double z = r * r;
+    double ps = 1.0 / 355687428096000.0, pc = 1.0 / 20922789888000.0;  // 1 / 17!, 1 / 16!
+    ps = fma(ps, z, -1.0 / 1307674368000.0);
+    pc = fma(pc, z, -1.0 / 87178291200.0);
+    ps = fma(ps, z, 1.0 / 6227020800.0);
+    pc = fma(pc, z, 1.0 / 479001600.0);
+    ps = fma(ps, z, -1.0 / 39916800.0);
+    pc = fma(pc, z, -1.0 / 3628800.0);
+    ps = fma(ps, z, 1.0 / 362880.0);
+    pc = fma(pc, z, 1.0 / 40320.0);
+    ps = fma(ps, z, -1.0 / 5040.0);
+    pc = fma(pc, z, -1.0 / 720.0);
+    ps = fma(ps, z, 1.0 / 120.0);
+    pc = fma(pc, z, 1.0 / 24.0);
+    ps = fma(ps, z, -1.0 / 6.0);
+    const double s = fma(r * z, ps, r), c = fma(z * z, pc, fma(-0.5, z, 1.0));
+    const int q = (int)n;
+    const double a = q & 1 ? c : s, b = q & 1 ? s : c;
+    *sn = q & 2 ? -a : a;
+    *cs = (q + 1) & 2 ? -b : b;
+}
+
 // Generation of one step's operands: thread t takes node gq = t / 16 and the
 // four rows 4 g .. 4 g + 3 (g = t % 16) of L and the JT / 16 columns
 // (JT / 16) g .. of R: one sincos at the first row (column), then rotations by
-// exp(+-i a dx) (the sign of the step of |xi|) and exp(i b dy); rows on both
-// sides of the bump centre (|xi| not monotone) take a sincos each.
+// exp(i a dx) and exp(i b dy).  cos(a |xi|) = cos(a xi) and sin(a |xi|) = sign(xi) sin(a xi),
+// so rows on both sides of the bump centre need nothing of their own.
 template <int JT>
-__device__ __forceinline__ void gen_step(const NodeData &nd, const Bumps &bs, long sq, long st, long q1off,
+__device__ __forceinline__ void gen_step(const NodeData &nd, const Bumps &bs, const Place &at, long q1off,
                                          long q2off, double x0, double y0, double dx, double dy, int gq, int g,
                                          double (*sL)[LdsStride<64>::value], double (*sLx)[LdsStride<64>::value],
                                          double (*sR)[LdsStride<JT>::value]) {
     constexpr int RJ = JT / 16;
     const int r0 = 4 * g, c0 = RJ * g;
-    const int b = (int)(st / sq);
-    const long q0 = (st - (long)b * sq) * kStep;
+    const long q0 = at.s * kStep;
     const int kind = q0 < q1off ? 0 : (q0 < q2off ? 1 : 2);
-    const double xi0 = x0 - bs.b1[b], eta0 = y0 - bs.b2[b];
-    const double a = nd.a, w = nd.w;
-    double sn[4], cs[4];
-    if (xi0 >= 0.0 || xi0 + 3.0 * dx <= 0.0) {
-        // |xi| = |xi0| +- r dx on all four rows
-        const double dir = xi0 >= 0.0 ? 1.0 : -1.0;
-        const double sa = dir * nd.sa;
-        sincos(a * fabs(xi0), &sn[0], &cs[0]);
-#pragma unroll
-        for (int r = 1; r < 4; ++r) {
-            cs[r] = cs[r - 1] * nd.ca - sn[r - 1] * sa;
-            sn[r] = sn[r - 1] * nd.ca + cs[r - 1] * sa;
-        }
-    } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sincos(a * fabs(xi0 + r * dx), &sn[r], &cs[r]);
-    }
+    const double xi0 = x0 - bs.b1[at.bump], eta0 = y0 - bs.b2[at.bump];
+    const double w = nd.w, wa = nd.w * nd.a;
+    double sn, cs;  // of a xi
+    sincos_fast(nd.a * xi0, &sn, &cs);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const double xi = xi0 + r * dx;
         const double sg = (xi > 0.0) ? 1.0 : (xi < 0.0 ? -1.0 : 0.0);
         double f, fx;
         if (kind == 0) {
-            f = cs[r];
-            fx = -a * sg * sn[r];
+            f = w * cs;
+            fx = -wa * sn;
         } else if (kind == 1) {
-            f = sn[r];
-            fx = a * sg * cs[r];
-        } else {  // a |xi| = a xi wherever H(xi) != 0
+            f = w * (sg * sn);
+            fx = wa * (sg * cs);
+        } else {
             const double H = (xi > 0.0) ? 1.0 : (xi == 0.0 ? 0.5 : 0.0);
-            f = -H * sn[r];
-            fx = -H * a * cs[r];
+            f = -w * (H * sn);
+            fx = -wa * (H * cs);
         }
-        sL[gq][r0 + r] = w * f;
-        sLx[gq][r0 + r] = w * fx;
+        sL[gq][r0 + r] = f;
+        sLx[gq][r0 + r] = fx;
+        if (r < 3) {
+            const double c2 = cs * nd.ca - sn * nd.sa;
+            sn = sn * nd.ca + cs * nd.sa;
+            cs = c2;
+        }
     }
     double sy, cy;
-    sincos(nd.b * eta0, &sy, &cy);
+    sincos_fast(nd.b * eta0, &sy, &cy);
     sR[gq][c0] = cy;
 #pragma unroll
     for (int r = 1; r < RJ; ++r) {
@@ -353,16 +390,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     const double y0 = y1 + (double)(tj * JT + (JT / 16) * g) * dy;
     if (s0 < s1) {
         NodeData nd;
-        load_node(na, nb, nw, rot, qpad, sq, s0, gq, nd);
-        gen_step<JT>(nd, bs, sq, s0, q1off, q2off, x0, y0, dx, dy, gq, g, sL[0], sLx[0], sR[0]);
-        if (s0 + 1 < s1) load_node(na, nb, nw, rot, qpad, sq, s0 + 1, gq, nd);
+        Place at{(int)(s0 / sq), 0};
+        at.s = s0 - (long)at.bump * sq;
+        load_node(na, nb, nw, rot, qpad, at, gq, nd);
+        gen_step<JT>(nd, bs, at, q1off, q2off, x0, y0, dx, dy, gq, g, sL[0], sLx[0], sR[0]);
+        at.next(sq);  // the step that is generated next, its nodes loaded already
+        if (s0 + 1 < s1) load_node(na, nb, nw, rot, qpad, at, gq, nd);
         __syncthreads();
         int cur = 0;
         for (long st = s0; st < s1; ++st) {
             if (st + 1 < s1) {
-                gen_step<JT>(nd, bs, sq, st + 1, q1off, q2off, x0, y0, dx, dy, gq, g, sL[cur ^ 1], sLx[cur ^ 1],
-                             sR[cur ^ 1]);
-                if (st + 2 < s1) load_node(na, nb, nw, rot, qpad, sq, st + 2, gq, nd);
+                gen_step<JT>(nd, bs, at, q1off, q2off, x0, y0, dx, dy, gq, g, sL[cur ^ 1], sLx[cur ^ 1], sR[cur ^ 1]);
+                at.next(sq);
+                if (st + 2 < s1) load_node(na, nb, nw, rot, qpad, at, gq, nd);
             }
 #pragma unroll
             for (int ks = 0; ks < kStep / 4; ++ks) {
@@ -407,22 +447,37 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
                 }
 }
 
+// 64 outputs per workgroup, a quarter of the chunks per wave, eight loads in flight (one
+// thread per output over all chunks in turn: 44 us for 137 chunks at 281 x 281, 500 for 1782
+// at 41 x 41; with the chunks of today 12 and 10).
 __global__ __launch_bounds__(256) void k_exact_reduce(const double *__restrict__ part, int chunks, int tiles,
                                                       int tiles_i, int jt, int N, int M, double *__restrict__ zeta,
                                                       double *__restrict__ zeta_x) {
+    __shared__ double sh[3][64];
     const long nm = (long)N * M;
-    const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= 2 * nm) return;
-    const int o = (int)(e / nm);
-    if (o == 1 && !zeta_x) return;
-    const long r = e - o * nm;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const long e = (long)blockIdx.x * 64 + lane, n = zeta_x ? 2 * nm : nm;
+    const long ec = e < n ? e : n - 1;
+    const int o = (int)(ec / nm);
+    const long r = ec - o * nm;
     const int j = (int)(r / N), i = (int)(r % N);
     const int tile = i / 64 + (j / jt) * tiles_i;
-    const long tsz = 2L * 64 * jt;
-    const long loc = (long)o * 64 * jt + (j % jt) * 64 + (i % 64);
+    const long tsz = 2L * 64 * jt, step = (long)tiles * tsz;
+    const double *p = part + tile * tsz + (long)o * 64 * jt + (j % jt) * 64 + (i % 64);
+    int c = (int)((long)w * chunks / 4);
+    const int c1 = (int)((long)(w + 1) * chunks / 4);
     double sum = 0.0;
-    for (int c = 0; c < chunks; ++c) sum += part[((long)c * tiles + tile) * tsz + loc];
-    (o ? zeta_x : zeta)[r] = sum;
+    for (; c + 8 <= c1; c += 8) {
+        double v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = p[(c + q) * step];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) sum += v[q];
+    }
+    for (; c < c1; ++c) sum += p[c * step];
+    if (w > 0) sh[w - 1][lane] = sum;
+    __syncthreads();
+    if (w == 0 && e < n) (o ? zeta_x : zeta)[r] = ((sum + sh[0][lane]) + sh[1][lane]) + sh[2][lane];
 }
 
 // u from the linear solution: zeta_1 and zeta_x from the exact solution; phi_x =
@@ -611,7 +666,7 @@ bim_exact_config resolve(const bim_exact_config *c) {
     r.decay = (c && c->decay > 0) ? c->decay : 36.0;
     r.psi_width_max = (c && c->psi_width_max > 0) ? c->psi_width_max : 0.1;
     r.grade_start = (c && c->grade_start > 0) ? c->grade_start : 1e-10;
-    r.workgroups = (c && c->workgroups > 0) ? c->workgroups : 2048;
+    r.workgroups = (c && c->workgroups > 0) ? c->workgroups : 0;
     r.timing = (c && c->timing) ? 1 : 0;
     r.tile_cols = c ? c->tile_cols : 0;
     return r;
@@ -673,7 +728,24 @@ extern "C" int bim_exact_linear(double froude, const bim_bump *bumps, int nbumps
     }
     const int tiles_i = (N + 63) / 64, tiles_j = (M + jt - 1) / jt, tiles = tiles_i * tiles_j;
     const long steps_total = (long)nbumps * (L.qpad / kStep);
-    long chunks = std::max(1L, std::min(steps_total, (long)(cfg.workgroups + tiles - 1) / tiles));
+    // node chunks: two workgroups to a compute unit, 512 at a time, in whole rounds (281 x
+    // 281, 15 tiles: 34 chunks, one round, 0.96 ms; 35 chunks 1.39; 137 chunks, about 2048
+    // workgroups, 1.07; total with the reduction at 96 x 96, 2 tiles: 255 chunks 0.21 ms, 891 0.40);
+    // few tiles fit one round, many take the number of rounds (up to 4) they fill best
+    long chunks = (cfg.workgroups + tiles - 1) / tiles;
+    if (cfg.workgroups <= 0) {
+        double best = 0.0;
+        chunks = 1;
+        for (int r = 1; r <= 4; ++r) {
+            const long c = std::max(1L, 512L * r / tiles);
+            const double fill = (double)c * tiles / (512.0 * ((c * tiles + 511) / 512));
+            if (fill > best + 0.02) {
+                best = fill;
+                chunks = c;
+            }
+        }
+    }
+    chunks = std::max(1L, std::min(steps_total, chunks));
     const long spc = (steps_total + chunks - 1) / chunks;
     chunks = (steps_total + spc - 1) / spc;
     if (chunks > 65535) return fail(BIM_EINVAL, "exact linear solution: too many node chunks");
@@ -711,8 +783,8 @@ extern "C" int bim_exact_linear(double froude, const bim_bump *bumps, int nbumps
             hipLaunchKernelGGL(k_exact_contract<64>, cgrid, dim3(256), 0, s, na, nb_, nw, rot, L.qpad, L.q1off,
                                L.q2off, bs, x1, dx, y1, dy, tiles_i, steps_total, spc, part);
         if (cfg.timing) BIM_HIP(hipEventRecord(ev[2], s));
-        const long outs = 2L * N * M;
-        hipLaunchKernelGGL(k_exact_reduce, dim3((unsigned)((outs + 255) / 256)), dim3(256), 0, s, part, (int)chunks,
+        const long outs = (zeta_x ? 2L : 1L) * N * M;
+        hipLaunchKernelGGL(k_exact_reduce, dim3((unsigned)((outs + 63) / 64)), dim3(256), 0, s, part, (int)chunks,
                            tiles, tiles_i, jt, N, M, zeta, zeta_x);
         BIM_HIP(hipGetLastError());
         if (cfg.timing) BIM_HIP(hipEventRecord(ev[3], s));

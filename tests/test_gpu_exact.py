@@ -38,6 +38,27 @@ def _cases():
 TOL = 1e-9
 
 
+# tiles of 64 x 64, 96 or 128 with one target, whole and just beyond; node chunks in whole
+# rounds of workgroups, a single chunk, more chunks than fit a round; targets on both
+# sides of the bump centre within one group of four rows
+@pytest.mark.parametrize("N,M,xlo", [(2, 2, -0.1), (64, 64, -3.0), (65, 97, -3.03), (63, 129, 1.0), (130, 33, -9.0)])
+def test_tiles_and_node_chunks_match_oracle(bim, N, M, xlo):
+    F, bumps = 1.3, [(0.2, 0.8, 0.0, 0.1), (-0.1, 1.1, 0.5, 0.0)]
+    mesh = (N, M, xlo, 0.11, -1.7, 0.13)
+    pts = [(0, 0), (N - 1, M - 1), (N // 2, M // 2)]
+    xs, ys = [xlo + 0.11 * i for i, _ in pts], [-1.7 + 0.13 * j for _, j in pts]
+    refs = [Fo.exact_solution(F, bumps, xs, ys, d) for d in (0, 1)]
+    for cfg in (None, dict(workgroups=1), dict(workgroups=3000)):
+        z, zx, _ = bim.exact_linear(F, bumps, *mesh, config=cfg)
+        for got, ref in ((z, refs[0]), (zx, refs[1])):
+            g = got.cpu().numpy()
+            assert np.isfinite(g).all()
+            assert np.abs(np.array([g[j, i] for i, j in pts]) - ref).max() <= TOL * np.abs(ref).max()
+    z0, none, _ = bim.exact_linear(F, bumps, *mesh, derivative=False)
+    z1, _, _ = bim.exact_linear(F, bumps, *mesh)
+    assert none is None and torch.equal(z0, z1)
+
+
 @pytest.mark.parametrize("c", _cases(), ids=[c["name"] for c in _cases()])
 def test_exact_linear_matches_oracle_at_sampled_nodes(bim, c):
     z, zx, info = bim.exact_linear(c["froude"], c["bumps"], c["N"], c["M"], c["x1"], c["dx"], c["y1"], c["dy"])
