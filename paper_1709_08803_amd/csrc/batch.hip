@@ -16,7 +16,7 @@ constexpr int kT = 256;
 
 __device__ double bsum256(double v) {
     __shared__ double sh[kT / 64];
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    v = wave_sum64(v);
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     if (lane == 0) sh[w] = v;
     __syncthreads();
@@ -161,7 +161,7 @@ __device__ __forceinline__ void brows_store(double (&acc)[kBGR], int lane, int n
                                             int row0, double alpha, double beta) {
 #pragma unroll
     for (int r = 0; r < kBGR; ++r)
-        for (int o = 32; o > 0; o >>= 1) acc[r] += __shfl_xor(acc[r], o, 64);
+        acc[r] = wave_sum64(acc[r]);
     if (lane < nvalid) {
         double v = acc[0];
 #pragma unroll
@@ -258,7 +258,7 @@ __global__ __launch_bounds__(256) void k_bgemv_tri(const BGemv *__restrict__ ops
     else bgemv_tri_rows<double>(o, l, r0, wv, lane, acc);
 #pragma unroll
     for (int r = 0; r < kBGR; ++r)
-        for (int off = 32; off > 0; off >>= 1) acc[r] += __shfl_xor(acc[r], off, 64);
+        acc[r] = wave_sum64(acc[r]);
     if (lane == 0)
 #pragma unroll
         for (int r = 0; r < kBGR; ++r) partial[wv][r] = acc[r];

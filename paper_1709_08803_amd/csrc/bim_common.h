@@ -11,6 +11,46 @@
 
 namespace bim {
 
+#if defined(__HIP_DEVICE_COMPILE__)
+// Sum over the 64 lanes, in every lane: the tree of exchanges between lanes 32, 16, 8, 4, 2
+// and 1 apart (each level's sums repeat with that period, so that a rotation by 4
+// within a row reaches the partner 4 apart).  Register exchanges; the shuffles through
+// LDS take 12 LDS instructions a sum, and a workgroup of 16 waves with a few hundred
+// sums was bound by them (31 -> 17 us for the orthogonalisation of n = 1056).
+__device__ __forceinline__ double wave_sum64(double v) {
+    auto bits = [](double x, unsigned &lo, unsigned &hi) __attribute__((always_inline)) {
+        const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+        lo = (unsigned)b;
+        hi = (unsigned)(b >> 32);
+    };
+    auto value = [](unsigned lo, unsigned hi) __attribute__((always_inline)) {
+        return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+    };
+    unsigned lo, hi;
+    bits(v, lo, hi);
+    const auto l32 = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto h32 = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    v = value(l32[0], h32[0]) + value(l32[1], h32[1]);
+    bits(v, lo, hi);
+    const auto l16 = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h16 = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    v = value(l16[0], h16[0]) + value(l16[1], h16[1]);
+#define BIM_DPP_ADD(CTRL)                                                                       \
+    bits(v, lo, hi);                                                                            \
+    v += value((unsigned)__builtin_amdgcn_update_dpp(0, (int)lo, CTRL, 0xf, 0xf, false),        \
+               (unsigned)__builtin_amdgcn_update_dpp(0, (int)hi, CTRL, 0xf, 0xf, false))
+    BIM_DPP_ADD(0x128);  // row_ror:8
+    BIM_DPP_ADD(0x124);  // row_ror:4
+    BIM_DPP_ADD(0x4e);   // quad_perm [2, 3, 0, 1]
+    BIM_DPP_ADD(0xb1);   // quad_perm [1, 0, 3, 2]
+#undef BIM_DPP_ADD
+    return v;
+}
+#else
+__device__ double wave_sum64(double v);
+#endif
+
+
 // Records the message for bim_last_error() and returns `code`.
 int fail(int code, const std::string &msg);
 // Wraps a HIP call: on failure records "<what>: <hip error string>" and returns BIM_EHIP.

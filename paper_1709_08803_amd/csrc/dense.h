@@ -70,6 +70,18 @@ int gemv_tri_enqueue(const float *A, long n, int M, int s, int part, const doubl
 // work: device scratch of batch * s * 2s doubles; info[b] = 0 or (1 + column of a zero pivot).
 int invert_enqueue(const InvItem *items_dev, int batch, int s_dim, double *work, int *info, hipStream_t s);
 
+// y = c - B x for two slice-block-banded matrices (half-widths w) at once; neither y is
+// read by the other product.
+template <typename TA>
+struct BandJob {
+    const TA *band;
+    int w;
+    const double *x, *c;
+    double *y;
+};
+int bandmv_pair_enqueue(const BandJob<double> &a, const BandJob<double> &b, int M, int s, hipStream_t st);
+int bandmv_pair_enqueue(const BandJob<float> &a, const BandJob<float> &b, int M, int s, hipStream_t st);
+
 // Inversion of one s x s block with 192 < s <= 384 as a 2 x 2 block matrix:
 // the leading 192 x 192 block A11 and the Schur complement A22 - A21 A11^-1 A12
 // by the register Gauss-Jordan kernel (partial pivoting within each), the rest

@@ -977,7 +977,7 @@ __global__ __launch_bounds__(256) void k_gemv_tri(const TA *__restrict__ A, long
     }
 #pragma unroll
     for (int r = 0; r < GR; ++r)
-        for (int o = 32; o > 0; o >>= 1) acc[r] += __shfl_xor(acc[r], o, 64);
+        acc[r] = wave_sum64(acc[r]);
     if (lane == 0)
 #pragma unroll
         for (int r = 0; r < GR; ++r) partial[wv][r] = acc[r];
@@ -992,10 +992,10 @@ __global__ __launch_bounds__(256) void k_gemv_tri(const TA *__restrict__ A, long
 // y_l = alpha sum_{m in band} B[l][m] x_m + beta c_l for slice-block-banded B
 // (blocks s x s, half-width w, elements of type TA): one wave per row of y.
 template <typename TA>
-__global__ __launch_bounds__(256) void k_bandmv(const TA *__restrict__ band, int M, int w, int s,
-                                                const double *__restrict__ x, const double *c, double *y,
-                                                double alpha, double beta) {
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+__device__ __forceinline__ void bandmv_row(const TA *__restrict__ band, int M, int w, int s,
+                                           const double *__restrict__ x, const double *c, double *y, double alpha,
+                                           double beta, int block) {
+    const int row = block * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (row >= M * s) return;
     const int l = row / s, r = row - l * s;
@@ -1006,7 +1006,7 @@ __global__ __launch_bounds__(256) void k_bandmv(const TA *__restrict__ band, int
         const double *xm = x + (size_t)m * s;
         for (int j = lane; j < s; j += 64) v = fma((double)b[j], xm[j], v);
     }
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    v = wave_sum64(v);
     if (lane == 0) y[row] = (beta == 0.0) ? alpha * v : fma(alpha, v, beta * c[row]);
 }
 
@@ -1014,13 +1014,13 @@ __global__ __launch_bounds__(256) void k_bandmv(const TA *__restrict__ band, int
 // owns GR consecutive rows of one slice and reads two elements per lane per
 // row, loading every x segment once for its rows.
 template <typename TA>
-__global__ __launch_bounds__(256) void k_bandmv_rows(const TA *__restrict__ band, int M, int w, int s,
-                                                     const double *__restrict__ x, const double *c, double *y,
-                                                     double alpha, double beta) {
+__device__ __forceinline__ void bandmv_rows(const TA *__restrict__ band, int M, int w, int s,
+                                            const double *__restrict__ x, const double *c, double *y, double alpha,
+                                            double beta, int block) {
     typedef double double2_t __attribute__((ext_vector_type(2)));
     typedef TA ta2_t __attribute__((ext_vector_type(2)));
     const int gps = (s + GR - 1) / GR;  // row groups per slice
-    const int wave = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int wave = block * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (wave >= M * gps) return;
     const int l = wave / gps, r0 = (wave - l * gps) * GR;
@@ -1053,7 +1053,7 @@ __global__ __launch_bounds__(256) void k_bandmv_rows(const TA *__restrict__ band
     }
 #pragma unroll
     for (int r = 0; r < GR; ++r)
-        for (int o = 32; o > 0; o >>= 1) acc[r] += __shfl_xor(acc[r], o, 64);
+        acc[r] = wave_sum64(acc[r]);
     if (lane < GR && r0 + lane < s) {
         double v = acc[0];
 #pragma unroll
@@ -1061,6 +1061,29 @@ __global__ __launch_bounds__(256) void k_bandmv_rows(const TA *__restrict__ band
         const int row = l * s + r0 + lane;
         y[row] = (beta == 0.0) ? alpha * v : fma(alpha, v, beta * c[row]);
     }
+}
+
+template <typename TA>
+__global__ __launch_bounds__(256) void k_bandmv(const TA *__restrict__ band, int M, int w, int s,
+                                                const double *__restrict__ x, const double *c, double *y,
+                                                double alpha, double beta) {
+    bandmv_row(band, M, w, s, x, c, y, alpha, beta, blockIdx.x);
+}
+template <typename TA>
+__global__ __launch_bounds__(256) void k_bandmv_rows(const TA *__restrict__ band, int M, int w, int s,
+                                                     const double *__restrict__ x, const double *c, double *y,
+                                                     double alpha, double beta) {
+    bandmv_rows(band, M, w, s, x, c, y, alpha, beta, blockIdx.x);
+}
+// Two independent products (alpha = -1, beta = 1) in one launch: on the meshes whose
+// bands are stored a product takes no longer than its launch (3 to 4 us).
+template <typename TA, bool ROWS>
+__global__ __launch_bounds__(256) void k_bandmv_pair(BandJob<TA> a, BandJob<TA> b, int M, int s, int blocks) {
+    const int i = blockIdx.x;
+    const BandJob<TA> &j = i < blocks ? a : b;
+    const int k = i < blocks ? i : i - blocks;
+    if (ROWS) bandmv_rows(j.band, M, j.w, s, j.x, j.c, j.y, -1.0, 1.0, k);
+    else bandmv_row(j.band, M, j.w, s, j.x, j.c, j.y, -1.0, 1.0, k);
 }
 
 // FP64 -> FP32 element copy (grid-stride)
@@ -1204,6 +1227,20 @@ int split_invert_enqueue(const SplitInv &P, const SplitInv *D, int s_dim, int *i
 
 namespace {
 template <typename TA>
+int bandmv_pair_launch(const BandJob<TA> &a, const BandJob<TA> &b, int M, int s, hipStream_t st) {
+    auto aligned = [&](const BandJob<TA> &j) {
+        return s % 2 == 0 && (uintptr_t)j.band % (2 * sizeof(TA)) == 0 && (uintptr_t)j.x % 16 == 0;
+    };
+    if (aligned(a) && aligned(b)) {
+        const int blocks = cdiv((long)M * ((s + GR - 1) / GR), 4);
+        hipLaunchKernelGGL((k_bandmv_pair<TA, true>), dim3(2 * blocks), dim3(256), 0, st, a, b, M, s, blocks);
+    } else {
+        const int blocks = cdiv((long)M * s, 4);
+        hipLaunchKernelGGL((k_bandmv_pair<TA, false>), dim3(2 * blocks), dim3(256), 0, st, a, b, M, s, blocks);
+    }
+    return hip_check(hipGetLastError(), "bandmv launch");
+}
+template <typename TA>
 int bandmv_launch(const TA *band, int M, int w, int s_dim, const double *x, const double *c, double *y,
                   double alpha, double beta, hipStream_t s) {
     const bool aligned = (s_dim % 2 == 0) && ((uintptr_t)band % (2 * sizeof(TA)) == 0) && ((uintptr_t)x % 16 == 0);
@@ -1217,6 +1254,12 @@ int bandmv_launch(const TA *band, int M, int w, int s_dim, const double *x, cons
 }
 }  // namespace
 
+int bandmv_pair_enqueue(const BandJob<double> &a, const BandJob<double> &b, int M, int s, hipStream_t st) {
+    return bandmv_pair_launch(a, b, M, s, st);
+}
+int bandmv_pair_enqueue(const BandJob<float> &a, const BandJob<float> &b, int M, int s, hipStream_t st) {
+    return bandmv_pair_launch(a, b, M, s, st);
+}
 int bandmv_enqueue(const double *band, int M, int w, int s_dim, const double *x, const double *c, double *y,
                    double alpha, double beta, hipStream_t s) {
     return bandmv_launch(band, M, w, s_dim, x, c, y, alpha, beta, s);

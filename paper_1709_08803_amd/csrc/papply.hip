@@ -274,7 +274,7 @@ __device__ __forceinline__ double rows4(GlobalPtr<const double> A, int s, int ro
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-        for (int o = 32; o > 0; o >>= 1) acc[e] += __shfl_xor(acc[e], o, 64);
+        acc[e] = wave_sum64(acc[e]);
     double v = acc[0];
 #pragma unroll
     for (int e = 1; e < 4; ++e) v = lane == e ? acc[e] : v;

@@ -113,7 +113,7 @@ __global__ __launch_bounds__(64) void k_k5_rowsum(double *rowsum, double *I5, in
             v += dx * dy * ci * cm / sqrt(s * s + tt * tt);
         }
     }
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    v = wave_sum64(v);
     if (lane == 0) {
         rowsum[t] = v;
         auto G = [](double s, double tt) {
@@ -777,16 +777,17 @@ static int precond_apply_blocks(const Precond *pc, const PrecondArrays<const T> 
     double *a1 = pc->scratch, *a3 = a1 + n, *t2 = a3 + n, *t3 = t2 + n;
     int rc;
     if ((rc = bandmv_enqueue(a.Dinv11, M, 0, s, r1, nullptr, a1, 1.0, 0.0, st))) return rc;       // a1
-    if ((rc = bandmv_enqueue(a.B31, M, h, s, a1, r3, t3, -1.0, 1.0, st))) return rc;              // r3 - P31 a1
+    // r3 - P31 a1 and r2 - P21 a1
+    if ((rc = bandmv_pair_enqueue(BandJob<T>{a.B31, h, a1, r3, t3}, BandJob<T>{a.B21, h, a1, r2, t2}, M, s, st)))
+        return rc;
     if ((rc = bandmv_enqueue(a.Dinv22, M, 0, s, t3, nullptr, a3, 1.0, 0.0, st))) return rc;       // a3
-    if ((rc = bandmv_enqueue(a.B21, M, h, s, a1, r2, t2, -1.0, 1.0, st))) return rc;              // r2 - P21 a1
     if ((rc = bandmv_enqueue(a.B23, M, h, s, a3, t2, t2, -1.0, 1.0, st))) return rc;              // - P23 a3
     // z2 = V^-1 D^-1 L^-1 t2 (t3 is free once a3 is formed)
     if ((rc = gemv_tri_enqueue(a.Sinv, n, M, s, 1, t2, t2, t3, 1.0, 1.0, st))) return rc;         // L^-1 t2
     if ((rc = bandmv_enqueue(a.Uinv, M, 0, s, t3, nullptr, t2, 1.0, 0.0, st))) return rc;         // D^-1
     if ((rc = gemv_tri_enqueue(a.Sinv, n, M, s, 2, t2, t2, z2, 1.0, 1.0, st))) return rc;         // V^-1
-    if ((rc = bandmv_enqueue(a.G, M, h, s, z2, a3, z3, -1.0, 1.0, st))) return rc;                // z3
-    return bandmv_enqueue(a.E, M, 0, s, z2, a1, z1, -1.0, 1.0, st);                               // z1
+    // z3 and z1
+    return bandmv_pair_enqueue(BandJob<T>{a.G, h, z2, a3, z3}, BandJob<T>{a.E, 0, z2, a1, z1}, M, s, st);
 }
 
 int precond_apply_enqueue(const Precond *pc, const double *r, double *z, hipStream_t st) {

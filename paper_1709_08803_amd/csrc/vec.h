@@ -15,6 +15,9 @@ int fd_shift_enqueue(const double *u, const double *v, long n, double h, double 
                      double *scal, hipStream_t s);
 // out = x + (*hp) y
 int axpy_dev_enqueue(const double *x, const double *y, const double *hp, double *out, long n, hipStream_t s);
+// both: scal[2] = h (h > 0: given) and out = u + h v
+int shift_axpy_enqueue(const double *u, const double *v, long n, double h, double eps, double *part, double *scal,
+                       double *out, hipStream_t s);
 // out = (Fw - Fu) / (*hp), or 0 when *hp == 0
 int quotient_enqueue(const double *Fw, const double *Fu, const double *hp, double *out, long n, hipStream_t s);
 
@@ -31,6 +34,12 @@ int scale_inv_enqueue(const double *x, const double *den, double *out, long n, h
 int axpby_enqueue(double a, const double *x, double b, const double *y, double *out, long n, hipStream_t s);
 // out[0] = max |a_i| (NaN if any entry is NaN)
 int maxabs_enqueue(const double *a, long n, double *part, double *out, hipStream_t s);
+// The orthogonalisation of an Arnoldi step in one launch, for short vectors and few of
+// them: twice h = V w (h1, then h2), w -= V^T h, norm = |w|, out = w / |w|; w itself is left.
+// The bits of multidot, orth_update, dot and scale_inv.
+bool arnoldi_small_applies(long n, int nv);
+int arnoldi_small_enqueue(const double *V, long ldv, int nv, const double *w, long n, double *h1, double *h2,
+                          double *norm, double *out, hipStream_t s);
 int uniform_stream_enqueue(double *u, int N, int M, double x1, hipStream_t s);
 
 }  // namespace bim

@@ -132,6 +132,23 @@ def test_graph_replay_matches_eager_solve(bim):
     assert torch.equal(ua, ub)
 
 
+# Vectors of n = 3 (N + 1) M entries around 1024, 2048 and 4096, where the orthogonalisation and
+# the step u + h v change between one entry per thread, two, four and many workgroups
+@pytest.mark.parametrize("N,M,n", [(30, 11, 1023), (17, 19, 1026), (21, 31, 2046), (35, 19, 2052), (64, 21, 4095),
+                                   (71, 19, 4104)])
+def test_solves_around_the_one_workgroup_lengths(bim, N, M, n):
+    p = W.make_problem(N, M, -0.25 * N, 0.25 * N, 0, 0.5 * M, 0.7, [W.Bump(0.1, 1.5, 1.5)])
+    assert p.n_unknowns == n
+    dp = bim.DeviceProblem(p)
+    P = bim.Preconditioner(dp)
+    u = bim.linear_start(dp, P)
+    rep = bim.solve(dp, u, P, ftol=1e-10, check=False)
+    F = np.abs(R.residual(p, u.cpu().numpy())).max()
+    print(N, M, rep["gmres_iters"], "max |F| of the oracle", F)
+    # the GPU's |F| <= ftol, and its F equals the oracle's to 1e-12 of the rows' terms (of order 10)
+    assert rep["status"] == 0 and F <= 2e-10
+
+
 GOLDEN = __import__("os").path.join(__import__("os").path.dirname(__file__), "golden")
 
 
