@@ -7,10 +7,10 @@ A timed step is one evaluation of the dense residual F(u) in FP64 through the
 C ABI (unpack and x-integration, node and collocation records, all-pairs sums,
 closed-form singular term, dynamic and radiation rows, assembly).  `value` is
 pair-interactions per second (collocation point x source node x y-image).
-The default warm-up is 100 evaluations (about 70 ms): a GPU that comes out of
+The default warm-up is 100 evaluations (about 50 ms): a GPU that comes out of
 idle runs its first tens of milliseconds of work at lower clocks (measured on
-this workload: 0.720 ms per evaluation over the 50 evaluations after a
-5-evaluation warm-up from idle, 0.670 ms once warm).  With the solver legs (the
+this workload: 0.55 ms per evaluation over the first evaluations from idle,
+0.504 ms once warm).  With the solver legs (the
 default) the GPU is busy for seconds before the warm-up starts.
 
 Also reported: the FP32-compensated evaluation, the all-pairs kernel's
@@ -40,7 +40,11 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 if HERE not in sys.path:
     sys.path.insert(0, HERE)
 
-FLOP_PER_PAIR = 25.5       # algorithmic FLOP per pair (mean over the four boundary pairings)
+# FLOP per pair (+, -, x = 1, FMA = 2, rsqrt = 1).  FP64: K1 and K2, 20 for every
+# pairing (the S2 sums are taken in segments, outside the pairs); FP32C: 31 where
+# target and source share a boundary, S2 included, 20 otherwise
+FLOP_PER_PAIR = 20.0
+FLOP_PER_PAIR_FP32C = 25.5
 PEAK_FP64_VECTOR = 78.6    # TFLOP/s, MI355X
 PEAK_FP32_VECTOR = 157.3   # TFLOP/s, MI355X
 
@@ -73,7 +77,7 @@ def cpu_baseline(p, u, budget_s=15.0):
 
 
 def measured_traffic():
-    """HBM bytes per FP64 all-pairs launch from the committed counter runs, or None
+    """HBM bytes of one evaluation's FP64 sums from the committed counter runs, or None
     if the kernel source has changed since those counters were taken."""
     import hashlib
     path = os.path.join(HERE, "profiles", "k_allpairs_181x61_hbm_traffic.md")
@@ -135,8 +139,11 @@ def time_to_solution(B, W, np, torch, froude, ftol=1e-10, max_newton=15, problem
         ulin = B.linear_start(dp, P, rtol=lrtol, prec=lprec)
         torch.cuda.synchronize()
         t_lin = time.perf_counter() - t0
-        # the apply reads every stored array once: bytes ~ P.nbytes (less the
-        # 4 n FP64 apply scratch); timed with events on the current stream
+        # timed with events on the current stream; bytes: every stored array once
+        # (P.nbytes less the 4 n FP64 apply scratch), or, where FP64 storage holds
+        # 150 MB of band blocks and its banded products are formed from kernel
+        # tables, the triangular inverses without their block diagonals and the
+        # pivot blocks' inverses
         r = torch.ones(dp.n, dtype=torch.float64, device="cuda")
         z = torch.empty_like(r)
         for _ in range(3):
@@ -148,7 +155,10 @@ def time_to_solution(B, W, np, torch, froude, ftol=1e-10, max_newton=15, problem
         e1.record()
         torch.cuda.synchronize()
         apply_ms = e0.elapsed_time(e1) / 20
-        apply_bytes = P.nbytes - 4 * 8 * (dp.n // 3)
+        n, s = dp.n // 3, dp.n // 3 // p.M
+        apply_bytes = P.nbytes - 4 * 8 * n
+        if storage == "fp64" and 4 * 8 * p.M * (2 * P.band + 1) * s * s >= 150e6:
+            apply_bytes = 8 * n * n
         res[f"precond_{storage}"] = {"setup_ms": t_setup * 1e3, "linear_start_ms": t_lin * 1e3,
                                      "linear_start_prec": lprec, "linear_start_rtol": lrtol,
                                      "band_halfwidth": P.band, "bytes": P.nbytes, "apply_ms": apply_ms,
@@ -407,12 +417,12 @@ def main():
     ms_step = dt / args.steps * 1e3
     value = pairs * args.steps / dt
 
-    # dominant kernel: all-pairs sums, HIP events on the launch stream, right
-    # after the timed steps
+    # dominant kernels: the boundary-integral sums, HIP events on the launch stream,
+    # right after the timed steps
     k64, t64 = B.residual_timed(dp, u, "fp64", iters=max(5, args.steps // 2))
     k32, t32 = B.residual_timed(dp, u, "fp32c", iters=max(5, args.steps // 2))
     ach64 = pairs * FLOP_PER_PAIR / (k64 * 1e-3) / 1e12
-    ach32 = pairs * FLOP_PER_PAIR / (k32 * 1e-3) / 1e12
+    ach32 = pairs * FLOP_PER_PAIR_FP32C / (k32 * 1e-3) / 1e12
 
     out = {
         "metric": "pair-interactions/s + time-to-converged-solve, 181x61 grid: FP64 vs mixed/learned",
@@ -432,7 +442,7 @@ def main():
                    "pairs_per_eval": pairs},
         "roofline": {"bound": "alu", "achieved": ach64, "peak": PEAK_FP64_VECTOR, "unit": "TFLOP/s",
                      "frac": ach64 / PEAK_FP64_VECTOR, "traffic": measured_traffic(),
-                     "kernel": "k_allpairs<double>", "kernel_ms": k64,
+                     "kernel": "k_s2_sums + k_allpairs64", "kernel_ms": k64,
                      "flop_per_pair": FLOP_PER_PAIR},
         "fp32c": {"eval_ms": t32, "kernel_ms": k32, "pairs_per_s": pairs / (t32 * 1e-3),
                   "roofline": {"bound": "alu", "achieved": ach32, "peak": PEAK_FP32_VECTOR,

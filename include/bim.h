@@ -141,7 +141,7 @@ int bim_release_workspaces(void);
  * device current.  The call allocates nothing, frees nothing and never
  * synchronises.
  *   u, F, prec: as bim_residual.
- * Size limit: the default launch is used while its workspace fits (27.5 MiB
+ * Size limit: the default launch is used while its workspace fits (35.9 MiB
  * FP64 and 35.5 MiB FP32C at 181 x 61); a larger mesh runs with fewer source
  * chunks, so that its partial sums fit, giving the same sums rounded in a
  * different order; a mesh whose workspace does not fit even with one chunk
@@ -164,8 +164,9 @@ size_t bim_residual_noalloc_max_bytes(void);
  *   unroll:           unroll depth of the loop over source nodes (2, 4 or 8);
  *   rows_per_chunk:   if chunks <= 0: chunks = ceil(2 M / rows_per_chunk);
  *   chunks:           number of source chunks (> 0 overrides rows_per_chunk).
- * With both <= 0 the library picks the chunk count that gives the launch about
- * 24 (FP64) or 32 (FP32C) waves per SIMD of the GPU (24576 or 32768 waves).
+ * With both <= 0 the library picks the chunk count: FP64 three waves per node
+ * of a boundary, at least 1024 and at most 49152 waves; FP32C 32768 waves
+ * (32 per SIMD of the GPU).
  */
 typedef struct bim_pair_config {
     int32_t targets_per_lane;
@@ -271,7 +272,8 @@ typedef struct bim_jfnk_opts {
     int32_t inner_prec;
     int32_t band_halfwidth;
     int32_t use_precond;
-    int32_t use_graphs;  /* 1: replay each Arnoldi step's device work from a HIP graph */
+    int32_t use_graphs;  /* 1: replay each Arnoldi step's device work from a HIP graph, from
+                            the step's fourth use in the solve on (before, it is launched) */
     double fd_eps;       /* epsilon of the shift rule h = sqrt(eps)(1 + |u|)/|v|; <= 0: the
                             unit roundoff of the inner precision (2^-52 or 2^-23) */
     int32_t stall_steps; /* s > 0: stop (BIM_NOT_CONVERGED) once ||F||_inf has not halved over
