@@ -927,8 +927,8 @@ __global__ __launch_bounds__(kInvThreads) void k_invert(const InvItem *__restric
 constexpr int GR = 4;  // rows per wave of the matrix-vector products
 
 // y = alpha A' x + beta c for the strictly lower (part 1) or strictly upper
-// (part 2) slice-block part A' of a dense n x n A (M slices of s): row block l
-// reads columns [0, l s) or [(l+1) s, n).  Each 256-thread workgroup owns GR
+// (part 2) slice-block part A' of the leading M slices of s of a dense A with
+// leading dimension n: row block l reads columns [0, l s) or [(l+1) s, M s).  Each 256-thread workgroup owns GR
 // rows of one slice and its four waves split the row range in quarters (the
 // rows' lengths run from 0 to n - s, and a single wave over a whole row would
 // be the kernel's critical path); the four partial sums are added in LDS.
@@ -947,7 +947,7 @@ __global__ __launch_bounds__(256) void k_gemv_tri(const TA *__restrict__ A, long
     if (g >= M * gps) return;
     const int lw = g / gps, r0 = (g - lw * gps) * GR;
     const int l = (part == 1) ? M - 1 - lw : lw;
-    const long c0 = (part == 1) ? 0 : (long)(l + 1) * s, c1 = (part == 1) ? (long)l * s : n;
+    const long c0 = (part == 1) ? 0 : (long)(l + 1) * s, c1 = (part == 1) ? (long)l * s : (long)M * s;
     const long len = c1 - c0;
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     // this wave's quarter [q0, q1) of the row range (an even length when vec)
@@ -1109,7 +1109,7 @@ __global__ void k_copy_blocks(const double *__restrict__ src, long sl, long sj, 
     const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (l + j >= lim || e >= (long)rows * cols) return;
     const int r = (int)(e / cols), c = (int)(e % cols);
-    dst[(size_t)l * dl + (size_t)j * dj + (size_t)r * ldd + c] = src[(size_t)l * sl + (size_t)j * sj + (size_t)r * lds + c];
+    dst[l * dl + j * dj + r * ldd + c] = src[l * sl + j * sj + r * lds + c];  // (strides may be negative)
 }
 
 __global__ void k_identity(double *A, long n) {

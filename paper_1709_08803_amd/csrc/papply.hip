@@ -13,8 +13,9 @@
 // another 0.34 GB for G = P33^-1 (P32 - P31 E)), and products with the stored
 // blocks are bound by reading them (250 of the 422 us of an apply at 181 x 61).
 // Formed from the tables the same products read a few MB and are bound by FP64
-// FMAs, LDS reads and launches: 422 -> 244 us per apply at 181 x 61, of which
-// 172 us are the two triangular products of the Schur inverse.  The tables
+// FMAs, LDS reads and launches: 422 -> 237 us per apply at 181 x 61, of which
+// 166 us were the two triangular products of the Schur inverse (122 us in groups of
+// slices, precond_groups: 197 us per apply).  The tables
 // hold the exact mesh offsets, where the blocks were formed from rounded node
 // coordinates (a difference of 1e-14 relative next to the target).  (The lockstep
 // solver and the FP32-stored operator go on with the stored blocks: the latter's

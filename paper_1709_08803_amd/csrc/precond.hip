@@ -302,6 +302,36 @@ static int precond_round_to_fp32(Precond *pc, hipStream_t st) {
 }
 
 // Tables, stacked slice blocks and scratch of the single-problem FP64 apply.
+// The number of groups of slices in which that apply takes the products with L^-1
+// and V^-1.  L and V are block-banded (half-width 2h), so that only the diagonal
+// groups of the inverses need be read,
+//   y_k = (L^-1)_kk (x_k - L_k,k-1 y_k-1),
+// with the 2h (2h + 1) / 2 blocks of L (or V) between neighbouring groups beside
+// them: at 181 x 61 two groups read 1080 blocks of 265 KB where the whole triangle
+// has 1830.  A group more costs two launches per product, about 4 us each or 23 MB
+// at the 5.85 TB/s of these products; groups are at least 2h + 1 slices, so that a
+// group meets its neighbours only.  Apply in one group / in groups: 181 x 61, two,
+// 241 / 197 us; 211 x 61, two, 325 / 264; 131 x 131, four, 485 / 272; full 151 x 151,
+// five, 795 / 361; near the line 181 x 31, two, 96.5 / 93.8.  The copies between
+// groups are 5% of P's memory and no measurable part of the setup.
+static int precond_groups(int M, int h, int s) {
+    const long launch = (long)(2 * 23.4e6 / (8.0 * s * s));  // in blocks
+    int best = 1;
+    long cost = (long)M * (M - 1) / 2;
+    for (int K = 2; K <= M / (2 * h + 1); ++K) {
+        long c = (K - 1) * ((long)h * (2 * h + 1) + launch);
+        for (int k = 0; k < K; ++k) {
+            const long m = (long)(k + 1) * M / K - (long)k * M / K;
+            c += m * (m - 1) / 2;
+        }
+        if (c < cost) {
+            cost = c;
+            best = K;
+        }
+    }
+    return best;
+}
+
 static int precond_table_alloc(Precond *pc, const bim_problem *p) {
     const int N = pc->N, M = pc->M, s = pc->s;
     PcDesc &d = pc->d;
@@ -315,16 +345,28 @@ static int precond_table_alloc(Precond *pc, const bim_problem *p) {
     d.dx = p->dx;
     d.dy = p->dy;
     const size_t nst = (size_t)(s + N) * s, nq = (size_t)M * N + kPcSourcePad, np = (size_t)d.chunks * M * (N - 1);
+    pc->groups = precond_groups(M, pc->h, s);
+    const size_t nbnd = (size_t)(2 * pc->h + 1) * s * (2 * pc->h + 1) * s;
     double *ETs, *tab, *corr;
     struct {
         double **p;
         size_t elems;
     } want[] = {{&ETs, nst}, {&tab, (size_t)3 * (2 * M - 1) * (N - 1)}, {&corr, (size_t)(N - 1) * M},
-                {&d.q1, nq},   {&d.q2, nq}, {&d.p1, np}, {&d.p2, np}};
+                {&d.q1, nq},   {&d.q2, nq}, {&d.p1, np}, {&d.p2, np}, {&pc->bnd, (pc->groups - 1) * nbnd}};
+    auto &bnd = want[std::size(want) - 1];
     size_t bytes = 0;
     for (auto &w : want) bytes += (sizeof(double) * w.elems + 255) & ~(size_t)255;
-    const int rc = hip_check(hipMalloc(&pc->table_mem, bytes), "hipMalloc(preconditioner tables)");
-    if (rc) return rc;
+    if (bnd.elems && hipMalloc(&pc->table_mem, bytes) != hipSuccess) {  // no room for more than one group
+        (void)hipGetLastError();
+        pc->table_mem = nullptr;
+        pc->groups = 1;
+        bytes -= (sizeof(double) * bnd.elems + 255) & ~(size_t)255;
+        bnd.elems = 0;
+    }
+    if (!pc->table_mem) {
+        const int rc = hip_check(hipMalloc(&pc->table_mem, bytes), "hipMalloc(preconditioner tables)");
+        if (rc) return rc;
+    }
     pc->bytes += bytes;
     DevArena ar{(char *)pc->table_mem, 0, bytes};
     for (auto &w : want) *w.p = ar.take<double>(w.elems);
@@ -689,6 +731,18 @@ int precond_build(const bim_problem *p, int hb, int storage, Precond **out, hipS
                           "copy"));
             RUN(gemm_enqueue(vitems_dev, M, s, w2 * s, s, s, w2 * s, w2 * s, 1.0, 0.0, st));
         }
+        // the blocks of L and V between the groups of the table-formed apply: boundary k's
+        // array holds L's rows at its start strictly above the block diagonal (block (i, j)
+        // of the 2h x 2h upper triangle at (i, j + 1)) and V's rows before it strictly
+        // below (block (i, j) of the lower triangle at (i + 1, j))
+        for (int k = 1; k < pc->groups; ++k) {
+            const long b = pc->group_start(k), ld = (long)(w2 + 1) * s, lw = (long)w2 * s;
+            double *B = pc->bnd + (size_t)(k - 1) * ld * ld;
+            RUN(copy_blocks_enqueue(Lrow + b * lrow, (long)lrow, s, lw, B + s, s * ld + s, s, ld, s, s, w2, w2, w2,
+                                    st));
+            RUN(copy_blocks_enqueue(Vrow + (b - 1) * lrow + (lw - s), -(long)lrow, -s, lw, B + lw * ld + (lw - s),
+                                    -s * ld - s, -s, ld, s, s, w2, w2, w2, st));
+        }
         // S^-1 = V^-1 D^-1 L^-1: L^-1 (unit lower) below the block diagonal of Sinv and
         // V^-1 (unit upper) above it, identity blocks on it, both read by the
         // substitutions and never written:
@@ -807,10 +861,35 @@ int precond_apply_enqueue(const Precond *pc, const double *r, double *z, hipStre
     double *t3 = d.t2 + d.n;
     int rc = pc_before_schur(d, st);
     if (rc) return rc;
-    // z2 = V^-1 D^-1 L^-1 t2
-    if ((rc = gemv_tri_enqueue(pc->Sinv, d.n, d.M, d.s, 1, d.t2, d.t2, t3, 1.0, 1.0, st))) return rc;
-    if ((rc = bandmv_enqueue(pc->Uinv, d.M, 0, d.s, t3, nullptr, d.t2, 1.0, 0.0, st))) return rc;
-    if ((rc = gemv_tri_enqueue(pc->Sinv, d.n, d.M, d.s, 2, d.t2, d.t2, z + d.n, 1.0, 1.0, st))) return rc;
+    // z2 = V^-1 D^-1 L^-1 t2 by groups of slices: rows of t2 beside a boundary less the
+    // neighbouring group's part, then the group's diagonal part of L^-1 (V^-1)
+    double *z2 = z + d.n;
+    const int s = d.s, w2 = 2 * pc->h, K = pc->groups;
+    const long ld = (long)(w2 + 1) * s;
+    auto group = [&](int k, int part, double *y) {
+        const long b = pc->group_start(k);
+        return gemv_tri_enqueue(pc->Sinv + b * s * (d.n + 1), d.n, (int)(pc->group_start(k + 1) - b), s, part,
+                                d.t2 + b * s, d.t2 + b * s, y + b * s, 1.0, 1.0, st);
+    };
+    for (int k = 0; k < K; ++k) {
+        if (k) {
+            const long b = pc->group_start(k);
+            if ((rc = gemv_tri_enqueue(pc->bnd + (size_t)(k - 1) * ld * ld, ld, w2 + 1, s, 2, t3 + (b - w2 - 1) * s,
+                                       d.t2 + b * s, d.t2 + b * s, -1.0, 1.0, st)))
+                return rc;
+        }
+        if ((rc = group(k, 1, t3))) return rc;
+    }
+    if ((rc = bandmv_enqueue(pc->Uinv, d.M, 0, s, t3, nullptr, d.t2, 1.0, 0.0, st))) return rc;
+    for (int k = K - 1; k >= 0; --k) {
+        if (k < K - 1) {
+            const long b = pc->group_start(k + 1);
+            if ((rc = gemv_tri_enqueue(pc->bnd + (size_t)k * ld * ld, ld, w2 + 1, s, 1, z2 + b * s,
+                                       d.t2 + (b - w2 - 1) * s, d.t2 + (b - w2 - 1) * s, -1.0, 1.0, st)))
+                return rc;
+        }
+        if ((rc = group(k, 2, z2))) return rc;
+    }
     return pc_after_schur(d, st);
 }
 

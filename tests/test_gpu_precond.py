@@ -229,3 +229,23 @@ def test_table_formed_apply_solves_banded_system(bim, N, M, half):
     assert blocks[1] <= 1e-9
     assert max(blocks) <= 1e-9 or N + 1 > 192
     P.close()
+
+
+# The triangular products of the same apply in groups of slices with the factors' blocks between
+# them: two groups of even and odd s, several on a half and a full domain, unequal groups (M no
+# multiple of their number).  P z = r as above, with that bound.
+@pytest.mark.parametrize("N,M,half", [(91, 91, True), (90, 91, True), (131, 131, True), (101, 122, False)])
+def test_grouped_triangular_products_solve_banded_system(bim, N, M, half):
+    x, y = (N - 1) / 6.0, (M - 1) / 3.0
+    p = W.make_problem(N, M, -x, x, 0.0 if half else -y, y, 1.2, [W.Bump(0.2, 1.0, 1.0)], half_domain=half)
+    dp = bim.DeviceProblem(p)
+    P = bim.Preconditioner(dp)
+    r = np.random.default_rng(11).standard_normal(p.n_unknowns)
+    for shift in (0, 1):  # z on a 16-byte boundary and 8 bytes off it
+        z = torch.empty(p.n_unknowns + 1, dtype=torch.float64, device="cuda")[shift:shift + p.n_unknowns]
+        P.apply(torch.as_tensor(r, device="cuda"), out=z)
+        torch.cuda.synchronize()
+        res = Lin.banded_matvec(p, z.cpu().numpy(), P.band) - r
+        print(f"{N}x{M} shift {shift} |Pz - r| / |r|", np.abs(res).max() / np.abs(r).max())
+        assert np.abs(res).max() <= 1e-9 * np.abs(r).max()
+    P.close()
