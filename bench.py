@@ -139,11 +139,10 @@ def time_to_solution(B, W, np, torch, froude, ftol=1e-10, max_newton=15, problem
         ulin = B.linear_start(dp, P, rtol=lrtol, prec=lprec)
         torch.cuda.synchronize()
         t_lin = time.perf_counter() - t0
-        # timed with events on the current stream; bytes: every stored array once
-        # (P.nbytes less the 4 n FP64 apply scratch), or, where FP64 storage holds
-        # 150 MB of band blocks and its banded products are formed from kernel
-        # tables, the triangular inverses without their block diagonals and the
-        # pivot blocks' inverses
+        # timed with events on the current stream; the rate is that of the stored
+        # arrays read once each (P.nbytes less the 4 n FP64 apply scratch), and there
+        # is none where FP64 storage holds 150 MB of band blocks: banded products
+        # then come from kernel tables and the triangular ones read part of the arrays
         r = torch.ones(dp.n, dtype=torch.float64, device="cuda")
         z = torch.empty_like(r)
         for _ in range(3):
@@ -158,11 +157,11 @@ def time_to_solution(B, W, np, torch, froude, ftol=1e-10, max_newton=15, problem
         n, s = dp.n // 3, dp.n // 3 // p.M
         apply_bytes = P.nbytes - 4 * 8 * n
         if storage == "fp64" and 4 * 8 * p.M * (2 * P.band + 1) * s * s >= 150e6:
-            apply_bytes = 8 * n * n
+            apply_bytes = None
         res[f"precond_{storage}"] = {"setup_ms": t_setup * 1e3, "linear_start_ms": t_lin * 1e3,
                                      "linear_start_prec": lprec, "linear_start_rtol": lrtol,
                                      "band_halfwidth": P.band, "bytes": P.nbytes, "apply_ms": apply_ms,
-                                     "apply_GBps": apply_bytes / (apply_ms * 1e-3) / 1e9}
+                                     "apply_GBps": apply_bytes and apply_bytes / (apply_ms * 1e-3) / 1e9}
         for leg, (st, kw) in legs.items():
             if st != storage:
                 continue
