@@ -665,6 +665,13 @@ int precond_build(const bim_problem *p, int hb, int storage, Precond **out, hipS
         // compute unit's registers and would otherwise wait for one to drain.
         constexpr int kAuxTriGroups = 192;
         const bool bw32 = storage == BIM_STORE_FP32 && s > 128 && s <= 384;
+        // Small problems run them after the LU on the setup's own stream, row j of L^-1
+        // with row M - 1 - j of V^-1 in one launch: making and ending a stream and its
+        // events takes 0.25 ms of the host and two waits per step, more than the few us
+        // per row that the overlap hides.  Two streams / one: 31 x 11 0.76 / 0.53 ms,
+        // 61 x 21 1.77 / 1.46, 91 x 31 (n = 2852) 4.3 / 3.6; 106 x 36 (n = 3852) 6.2 /
+        // 5.8 in FP64 but 6.6 / 12 in FP32, 121 x 41 8.6 / 8.6.
+        const bool one_stream = !bw32 && n <= 3072;
         const int far = 1 << 29;  // an offset that leaves klo at 0 / khi at nk
         const size_t lrow = (size_t)s * w2 * s;  // elements of one block row of L (or V)
         float *S32 = nullptr;
@@ -687,7 +694,7 @@ int precond_build(const bim_problem *p, int hb, int storage, Precond **out, hipS
                 fwd.push_back({Lrow + a_off, pc->Sinv + (size_t)q0 * s * n, pc->Sinv + (size_t)lf * s * n, nkf, 0, lf,
                                q0, -far, 0});
         }
-        if (!fwd.empty())
+        if (!fwd.empty() && !one_stream)
             RUN(hip_check(hipMemcpyAsync(tri_dev, fwd.data(), sizeof(GemmTriItem) * fwd.size(), hipMemcpyHostToDevice,
                                          st),
                           "copy"));
@@ -695,13 +702,15 @@ int precond_build(const bim_problem *p, int hb, int storage, Precond **out, hipS
             RUN(hip_check(hipMemcpyAsync(tri32_dev, fwd32.data(), sizeof(GemmTriItemF) * fwd32.size(),
                                          hipMemcpyHostToDevice, st),
                           "copy"));
-        RUN(hip_check(hipStreamCreateWithFlags(&aux, hipStreamNonBlocking), "hipStreamCreate"));
-        RUN(hip_check(hipEventCreateWithFlags(&ev_l, hipEventDisableTiming), "hipEventCreate"));
-        RUN(hip_check(hipEventCreateWithFlags(&ev_f, hipEventDisableTiming), "hipEventCreate"));
+        if (!one_stream) {
+            RUN(hip_check(hipStreamCreateWithFlags(&aux, hipStreamNonBlocking), "hipStreamCreate"));
+            RUN(hip_check(hipEventCreateWithFlags(&ev_l, hipEventDisableTiming), "hipEventCreate"));
+            RUN(hip_check(hipEventCreateWithFlags(&ev_f, hipEventDisableTiming), "hipEventCreate"));
+        }
         for (int l = 0; l < M; ++l) {
             RUN(invert_range(2 + l, 1));
             if (op_bl[l] >= 0) RUN(run_op(ops[op_bl[l]], st));
-            if (l + 1 < M) {  // row l + 1 of L^-1
+            if (l + 1 < M && !one_stream) {  // row l + 1 of L^-1
                 RUN(hip_check(hipEventRecord(ev_l, st), "hipEventRecord"));
                 RUN(hip_check(hipStreamWaitEvent(aux, ev_l, 0), "hipStreamWaitEvent"));
                 if (bw32) {
@@ -714,7 +723,7 @@ int precond_build(const bim_problem *p, int hb, int storage, Precond **out, hipS
             }
             if (op_upd[l] >= 0) RUN(run_op(ops[op_upd[l]], st));
         }
-        RUN(hip_check(hipEventRecord(ev_f, aux), "hipEventRecord"));
+        if (!one_stream) RUN(hip_check(hipEventRecord(ev_f, aux), "hipEventRecord"));
         // U rows: U[l][m] for m = l+1..l+2h packed as [l][s][2h s] (block j = m - l - 1,
         // copied while l + j + 1 < M)
         RUN(copy_blocks_enqueue(S + (size_t)(w2 + 1) * bs, brow, bs, s, Urow, (long)s * w2 * s, s, (long)w2 * s, s, s,
@@ -771,10 +780,18 @@ int precond_build(const bim_problem *p, int hb, int storage, Precond **out, hipS
                 bwd.push_back({Vrow + lb * lrow, pc->Sinv + (size_t)(lb + 1) * s * n, pc->Sinv + (size_t)lb * s * n,
                                nkb, lb + 1, M - 1 - lb, far, lb, 1});
         }
-        if (!bwd.empty())
+        std::vector<GemmTriItem> both;  // row j of L^-1 and row M - 1 - j of V^-1
+        if (one_stream) {
+            for (size_t j = 0; j < bwd.size(); ++j) both.insert(both.end(), {fwd[j], bwd[j]});
+            if (!both.empty())
+                RUN(hip_check(hipMemcpyAsync(tri_dev, both.data(), sizeof(GemmTriItem) * both.size(),
+                                             hipMemcpyHostToDevice, st),
+                              "copy"));
+        } else if (!bwd.empty()) {
             RUN(hip_check(hipMemcpyAsync(tri_dev + M, bwd.data(), sizeof(GemmTriItem) * bwd.size(),
                                          hipMemcpyHostToDevice, st),
                           "copy"));
+        }
         if (!bwd32.empty())
             RUN(hip_check(hipMemcpyAsync(tri32_dev + M, bwd32.data(), sizeof(GemmTriItemF) * bwd32.size(),
                                          hipMemcpyHostToDevice, st),
@@ -782,10 +799,12 @@ int precond_build(const bim_problem *p, int hb, int storage, Precond **out, hipS
         for (int j = 1; j < M; ++j) {
             if (bw32)
                 RUN(gemm_tri_enqueue(tri32_dev + M + (j - 1), 1, s, j, w2 * s, (int)n, (int)n, -1.0, st));
+            else if (one_stream)
+                RUN(gemm_tri_enqueue(tri_dev + 2 * (j - 1), 2, s, j, w2 * s, (int)n, (int)n, -1.0, st));
             else
                 RUN(gemm_tri_enqueue(tri_dev + M + (j - 1), 1, s, j, w2 * s, (int)n, (int)n, -1.0, st));
         }
-        RUN(hip_check(hipStreamWaitEvent(st, ev_f, 0), "hipStreamWaitEvent"));
+        if (!one_stream) RUN(hip_check(hipStreamWaitEvent(st, ev_f, 0), "hipStreamWaitEvent"));
         // a zero pivot in any inverted block makes P singular in this factorisation
         std::vector<int> hinfo(3 * (2 + M), 0);
         RUN(hip_check(hipMemcpyAsync(hinfo.data(), info, sizeof(int) * 3 * (2 + M), hipMemcpyDeviceToHost, st),

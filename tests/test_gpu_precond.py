@@ -249,3 +249,19 @@ def test_grouped_triangular_products_solve_banded_system(bim, N, M, half):
         print(f"{N}x{M} shift {shift} |Pz - r| / |r|", np.abs(res).max() / np.abs(r).max())
         assert np.abs(res).max() <= 1e-9 * np.abs(r).max()
     P.close()
+
+
+# Rows of L^-1 and V^-1 in joint launches on one stream (n = (N + 1) M <= 3072) and on two above:
+# both sides of the line, few slices, one tile of rows and more.  P z = r with the bound above.
+@pytest.mark.parametrize("N,M", [(63, 48), (63, 49), (31, 5), (191, 16), (191, 17)])
+def test_triangular_inverses_on_one_and_two_streams(bim, N, M):
+    p = W.make_problem(N, M, -(N - 1) / 6.0, (N - 1) / 6.0, 0.0, (M - 1) / 3.0, 1.2, [W.Bump(0.2, 1.0, 1.0)])
+    dp = bim.DeviceProblem(p)
+    P = bim.Preconditioner(dp)
+    r = np.random.default_rng(13).standard_normal(p.n_unknowns)
+    z = P.apply(torch.as_tensor(r, device="cuda"))
+    torch.cuda.synchronize()
+    res = Lin.banded_matvec(p, z.cpu().numpy(), P.band) - r
+    print(f"{N}x{M} |Pz - r| / |r|", np.abs(res).max() / np.abs(r).max())
+    assert np.abs(res).max() <= 1e-9 * np.abs(r).max()
+    P.close()
