@@ -52,7 +52,6 @@ struct Precond {
     double *scratch;              // [4 n] apply temporaries
     bool tables = false;          // the single-problem apply convolves with kernel tables
     PcDesc d{};                   // its arrays (r and z set per apply)
-    void *table_mem = nullptr;    // their memory (counted in bytes)
     int groups = 1;               // its triangular products: groups of slices (group_start),
     double *bnd = nullptr;        // [groups - 1][(2h + 1) s][(2h + 1) s] factor blocks between them
     long group_start(int k) const { return (long)k * M / groups; }

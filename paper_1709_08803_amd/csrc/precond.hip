@@ -332,7 +332,10 @@ static int precond_groups(int M, int h, int s) {
     return best;
 }
 
-static int precond_table_alloc(Precond *pc, const bim_problem *p) {
+// Sizes of the tables' arrays (with `ar`, also their places in it): the total in bytes.
+// They lie in the operator's own allocation (a second one of this size costs the
+// setup and the release 0.3 ms).
+static size_t precond_tables(Precond *pc, const bim_problem *p, DevArena *ar) {
     const int N = pc->N, M = pc->M, s = pc->s;
     PcDesc &d = pc->d;
     d.N = N;
@@ -345,7 +348,6 @@ static int precond_table_alloc(Precond *pc, const bim_problem *p) {
     d.dx = p->dx;
     d.dy = p->dy;
     const size_t nst = (size_t)(s + N) * s, nq = (size_t)M * N + kPcSourcePad, np = (size_t)d.chunks * M * (N - 1);
-    pc->groups = precond_groups(M, pc->h, s);
     const size_t nbnd = (size_t)(2 * pc->h + 1) * s * (2 * pc->h + 1) * s;
     double *ETs, *tab, *corr;
     struct {
@@ -353,23 +355,10 @@ static int precond_table_alloc(Precond *pc, const bim_problem *p) {
         size_t elems;
     } want[] = {{&ETs, nst}, {&tab, (size_t)3 * (2 * M - 1) * (N - 1)}, {&corr, (size_t)(N - 1) * M},
                 {&d.q1, nq},   {&d.q2, nq}, {&d.p1, np}, {&d.p2, np}, {&pc->bnd, (pc->groups - 1) * nbnd}};
-    auto &bnd = want[std::size(want) - 1];
     size_t bytes = 0;
     for (auto &w : want) bytes += (sizeof(double) * w.elems + 255) & ~(size_t)255;
-    if (bnd.elems && hipMalloc(&pc->table_mem, bytes) != hipSuccess) {  // no room for more than one group
-        (void)hipGetLastError();
-        pc->table_mem = nullptr;
-        pc->groups = 1;
-        bytes -= (sizeof(double) * bnd.elems + 255) & ~(size_t)255;
-        bnd.elems = 0;
-    }
-    if (!pc->table_mem) {
-        const int rc = hip_check(hipMalloc(&pc->table_mem, bytes), "hipMalloc(preconditioner tables)");
-        if (rc) return rc;
-    }
-    pc->bytes += bytes;
-    DevArena ar{(char *)pc->table_mem, 0, bytes};
-    for (auto &w : want) *w.p = ar.take<double>(w.elems);
+    if (!ar) return bytes;
+    for (auto &w : want) *w.p = ar->take<double>(w.elems);
     d.iD11 = pc->Dinv11;  // their first slice blocks
     d.iD22 = pc->Dinv22;
     d.ETs = ETs;
@@ -378,7 +367,7 @@ static int precond_table_alloc(Precond *pc, const bim_problem *p) {
     d.a1 = pc->scratch;
     d.a3 = d.a1 + pc->n;
     d.t2 = d.a3 + pc->n;
-    return BIM_OK;
+    return bytes;
 }
 
 int precond_build(const bim_problem *p, int hb, int storage, Precond **out, hipStream_t st) {
@@ -406,9 +395,28 @@ int precond_build(const bim_problem *p, int hb, int storage, Precond **out, hipS
     add((size_t)n * n);        // L^-1 | I | V^-1
     add(band_elems(M, 0, s));  // D^-1 (inverse pivot blocks)
     add((size_t)4 * n);        // apply scratch
+    // Tables from 150 MB of stored bands on: below, reading the blocks takes no
+    // longer than the convolutions' launches and latencies (apply from blocks /
+    // from tables, half domains: 61 x 21, 23 MB: 41 / 63 us; 91 x 31, 92 MB: 54 /
+    // 72; 106 x 36, 172 MB: 110 / 79; 121 x 41, 293 MB: 122 / 90; 181 x 61, 1.36
+    // GB: 433 / 249; full 61 x 61, 158 MB: 76 / 75)
+    const bool tables = storage == BIM_STORE_FP64 && sizeof(double) * 4 * band_elems(M, h, s) >= (size_t)150000000;
+    pc->tables = tables;
+    size_t extra = 0;
+    if (tables) {
+        pc->groups = precond_groups(M, h, s);
+        extra = precond_tables(pc, p, nullptr);
+        if (pc->groups > 1 && hipMalloc(&pc->mem, pers + extra) != hipSuccess) {  // no room for more than one
+            (void)hipGetLastError();
+            pc->mem = nullptr;
+            pc->groups = 1;
+            extra = precond_tables(pc, p, nullptr);
+        }
+    }
+    pers += extra;
     pc->bytes = pers;
-    int rc = hip_check(hipMalloc(&pc->mem, pers), "hipMalloc(preconditioner)");
-    if (rc) {
+    int rc = BIM_OK;
+    if (!pc->mem && (rc = hip_check(hipMalloc(&pc->mem, pers), "hipMalloc(preconditioner)"))) {
         delete pc;
         return rc;
     }
@@ -423,17 +431,7 @@ int precond_build(const bim_problem *p, int hb, int storage, Precond **out, hipS
     pc->Sinv = ar.take<double>((size_t)n * n);
     pc->Uinv = ar.take<double>(band_elems(M, 0, s));
     pc->scratch = ar.take<double>((size_t)4 * n);
-    // Tables from 150 MB of stored bands on: below, reading the blocks takes no
-    // longer than the convolutions' launches and latencies (apply from blocks /
-    // from tables, half domains: 61 x 21, 23 MB: 41 / 63 us; 91 x 31, 92 MB: 54 /
-    // 72; 106 x 36, 172 MB: 110 / 79; 121 x 41, 293 MB: 122 / 90; 181 x 61, 1.36
-    // GB: 433 / 249; full 61 x 61, 158 MB: 76 / 75)
-    const bool tables = storage == BIM_STORE_FP64 && sizeof(double) * 4 * band_elems(M, h, s) >= (size_t)150000000;
-    pc->tables = tables;
-    if (tables && (rc = precond_table_alloc(pc, p))) {
-        precond_free(pc);
-        return rc;
-    }
+    if (tables) precond_tables(pc, p, &ar);
 
     // setup-only scratch
     size_t tmp = 0;
@@ -931,7 +929,6 @@ const void *precond_array(const Precond *pc, int which) {
 void precond_free(Precond *pc) {
     if (!pc) return;
     if (pc->mem) (void)hipFree(pc->mem);
-    if (pc->table_mem) (void)hipFree(pc->table_mem);
     delete pc;
 }
 
