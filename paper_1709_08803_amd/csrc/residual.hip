@@ -731,7 +731,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<T
 // its 22082 pairs at 181 x 61 (launches of the sums 613 -> 486 us; full 151 x 151
 // 1570 -> 1120).
 constexpr double kS2Reach = 8.0;   // node-by-node distance, in dx
-constexpr int kS2Flush = 16;       // rows per logarithm (their product stays in range)
+constexpr int kS2Flush = 16;       // rows per logarithm, fewer where their product passes kS2Wide
+// Range of the products: numerators and denominators of a row are 1 or more and the
+// numerator is the larger one.  With A, C <= kS2Steep (slopes up to 10^6) and dy <= kS2Aspect
+// dx it is below (4 kS2Steep (N + 2 M kS2Aspect))^2 < 10^50 (N M <= 2^26), so that no product
+// passes 10^150; steeper targets, and meshes of larger dy, are summed node by node.  (16 rows
+// without the check pass 10^308 from slopes of about 2800 on, half domain, 281 x 141.)
+constexpr double kS2Wide = 1e100, kS2Steep = 1e12, kS2Aspect = 1e3;
 constexpr int kS2Chunks = 16;      // most row chunks per tile of targets (rows c, c + chunks, ..)
 
 // Closed form of the integral of (A s^2 + B s t + C t^2)^(-1/2) over a rectangle
@@ -831,7 +837,36 @@ __device__ __forceinline__ void s2_ratio(double g1, double u1, double g2, double
 // The S2 sums of 64 targets (tile tt of the flattened points of both boundaries)
 // over the lattice rows c, c + chunks, ..: rows -(M-1) .. M-1 on a half domain (the
 // images; the doubled row on the symmetry line counts once whole), less this
-// chunk's part of the closed-form integral.
+// chunk's part of the closed-form integral.  Node by node:
+__device__ __forceinline__ void s2_nodes_item(const double *__restrict__ tg64, int N, int M, int nimg, double dx,
+                                              double dy, int tiles_per_bnd, int tt, int c, int chunks,
+                                              double *__restrict__ out, int lane) {
+    const GlobalPtr<const double> tg = (GlobalPtr<const double>)tg64;
+    const int ntg = (N - 1) * M;
+    const size_t T2 = (size_t)2 * ntg;
+    const int st = tt / tiles_per_bnd, idx = (tt - st * tiles_per_bnd) * 64 + lane;
+    const int ic = min(idx, ntg - 1), l = ic / (N - 1), k = ic - l * (N - 1);
+    const int tid = st * ntg + ic;
+    const double A = tg[4 * T2 + tid], B = tg[5 * T2 + tid], C = tg[6 * T2 + tid];
+    const int rows = nimg == 2 ? 2 * M - 1 : M, off = nimg == 2 ? M - 1 + l : l;
+    const double ry = dy / dx, s0 = -(k + 0.5);
+    double acc = 0.0;
+    for (int jr = c; jr < rows; jr += chunks) {
+        const double t = (jr - off) * ry, Bt = B * t, Ct2 = C * (t * t);
+        const double wy = (jr == 0 || jr == rows - 1) ? 0.5 : 1.0;
+        double row = 0.0;
+#pragma unroll 4
+        for (int i = 0; i < N; ++i) {
+            const double sn = s0 + i, f = rsq(fma(sn, fma(A, sn, Bt), Ct2));
+            row = fma((i == 0 || i == N - 1) ? 0.5 : 1.0, f, row);
+        }
+        acc = fma(wy, row, acc);
+    }
+    const double sum = dy * acc - s2_corners(A, B, C, N, M, nimg, dx, dy, k, l, c, chunks);
+    if (idx < ntg) ((GlobalPtr<double>)out)[(size_t)c * T2 + tid] = sum;
+}
+
+// The same in segments, for dy <= kS2Aspect dx.
 __device__ __forceinline__ void s2_item(const double *__restrict__ tg64, int N, int M, int nimg, double dx, double dy,
                                         int tiles_per_bnd, int tt, int c, int chunks, double *__restrict__ out,
                                         int lane) {
@@ -844,6 +879,10 @@ __device__ __forceinline__ void s2_item(const double *__restrict__ tg64, int N, 
     const double B = tg[5 * T2 + tid], C = tg[6 * T2 + tid];
     S2Row r;
     r.A = tg[4 * T2 + tid];
+    if (!__all(r.A <= kS2Steep && C <= kS2Steep)) {
+        s2_nodes_item(tg64, N, M, nimg, dx, dy, tiles_per_bnd, tt, c, chunks, out, lane);
+        return;
+    }
     const double isqA = rsq_full(r.A);
     r.sqA = r.A * isqA;
     const double D4 = fma(4.0 * r.A, C, -B * B);
@@ -907,7 +946,7 @@ __device__ __forceinline__ void s2_item(const double *__restrict__ tg64, int N, 
         }
         num *= rn;
         den *= rd;
-        if (++pending == kS2Flush) {
+        if (++pending == kS2Flush || __any(num > kS2Wide)) {
             logs += log(num / den);
             num = den = 1.0;
             pending = 0;
@@ -915,35 +954,6 @@ __device__ __forceinline__ void s2_item(const double *__restrict__ tg64, int N, 
     }
     if (pending) logs += log(num / den);
     const double sum = dy * fma(logs, isqA, acc) - s2_corners(r.A, B, C, N, M, nimg, dx, dy, k, l, c, chunks);
-    if (idx < ntg) ((GlobalPtr<double>)out)[(size_t)c * T2 + tid] = sum;
-}
-
-// The same (rows c, c + chunks, ..; less the closed-form integral's part) node by node.
-__device__ __forceinline__ void s2_nodes_item(const double *__restrict__ tg64, int N, int M, int nimg, double dx,
-                                              double dy, int tiles_per_bnd, int tt, int c, int chunks,
-                                              double *__restrict__ out, int lane) {
-    const GlobalPtr<const double> tg = (GlobalPtr<const double>)tg64;
-    const int ntg = (N - 1) * M;
-    const size_t T2 = (size_t)2 * ntg;
-    const int st = tt / tiles_per_bnd, idx = (tt - st * tiles_per_bnd) * 64 + lane;
-    const int ic = min(idx, ntg - 1), l = ic / (N - 1), k = ic - l * (N - 1);
-    const int tid = st * ntg + ic;
-    const double A = tg[4 * T2 + tid], B = tg[5 * T2 + tid], C = tg[6 * T2 + tid];
-    const int rows = nimg == 2 ? 2 * M - 1 : M, off = nimg == 2 ? M - 1 + l : l;
-    const double ry = dy / dx, s0 = -(k + 0.5);
-    double acc = 0.0;
-    for (int jr = c; jr < rows; jr += chunks) {
-        const double t = (jr - off) * ry, Bt = B * t, Ct2 = C * (t * t);
-        const double wy = (jr == 0 || jr == rows - 1) ? 0.5 : 1.0;
-        double row = 0.0;
-#pragma unroll 4
-        for (int i = 0; i < N; ++i) {
-            const double sn = s0 + i, f = rsq(fma(sn, fma(A, sn, Bt), Ct2));
-            row = fma((i == 0 || i == N - 1) ? 0.5 : 1.0, f, row);
-        }
-        acc = fma(wy, row, acc);
-    }
-    const double sum = dy * acc - s2_corners(A, B, C, N, M, nimg, dx, dy, k, l, c, chunks);
     if (idx < ntg) ((GlobalPtr<double>)out)[(size_t)c * T2 + tid] = sum;
 }
 
@@ -1306,7 +1316,9 @@ PairDesc make_desc(const bim_problem *p, const Dims &d, const PairLaunch &pl, co
 // (whole evaluation, nodes / segments in us: 31 x 11 22 / 28, 61 x 21 34 / 36, 76 x 26 45 /
 // 48, 91 x 31 70 / 68, 121 x 41 156 / 137, 181 x 61 660 / 511; full 51 x 51 51 / 55,
 // 61 x 61 74.5 / 72.5, 101 x 101 358 / 302).
-static bool s2_by_nodes(const Dims &d) { return (double)d.nnode * d.nnode * d.nimg < 1.1e7; }
+static bool s2_by_nodes(const Dims &d, const bim_problem *p) {
+    return (double)d.nnode * d.nnode * d.nimg < 1.1e7 || p->dy > kS2Aspect * p->dx;
+}
 
 int residual_enqueue(const bim_problem *p, const double *u, double *F, int prec, const PairLaunch &pl,
                      const ResidualWork &w, hipStream_t s, hipEvent_t *ev_pair, int linear,
@@ -1338,7 +1350,7 @@ int residual_enqueue(const bim_problem *p, const double *u, double *F, int prec,
     // FP64: the S2 sums' row chunks share the partial-sum buffer (two values per chunk
     // and target) with the pair sums; on small meshes they are summed node by node in
     // the same launch (s2_by_nodes)
-    const bool by_nodes = s2_by_nodes(d);
+    const bool by_nodes = s2_by_nodes(d, p);
     const int s2_chunks = std::min(kS2Chunks, pl.chunks);
     const int s2_blocks = cdiv((long)2 * cdiv((long)(N - 1) * M, 64) * s2_chunks, 4);
     if (lin_tables) {

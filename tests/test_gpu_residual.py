@@ -102,6 +102,45 @@ def test_residual_fp64_s2_routes_match_oracle(bim, monkeypatch, N, M, half, stee
     assert err.max() <= 1e-12
 
 
+# Slopes far beyond any solution's, where the products of the segments' ratios would leave
+# the FP64 range (from about 2800 on with 16 or more rows per chunk), up to and past the
+# slope from which targets are summed node by node, and one source chunk (all rows in one
+# product, as the allocation-free entry point may run)
+@pytest.mark.parametrize("N,M,half,slope,chunks", [(281, 141, True, 3e3, 0), (281, 141, True, 3e4, 0),
+                                                   (281, 141, True, 3e6, 0), (151, 300, False, 1e4, 0),
+                                                   (151, 100, False, 500.0, 1)])
+def test_residual_fp64_steep_surfaces(bim, monkeypatch, N, M, half, slope, chunks):
+    import ctypes
+    monkeypatch.setattr(R, "s2_integral", _s2_integral_extended)
+    L, Ly = 0.05 * (N - 1), 0.1 * (M - 1)
+    p = W.make_problem(N, M, -L, L, 0 if half else -0.5 * Ly, Ly if half else 0.5 * Ly, 0.9, [W.Bump(0.2, 1.0, 1.0)],
+                       half_domain=half)
+    u = W.perturbed_state(p, 21)
+    nb = (N + 1) * M
+    nf = R.reconstruct(p, u)
+    u[:nb] *= slope / max(np.abs(nf.zeta_x).max(), np.abs(nf.zeta_y).max())
+    nf = R.reconstruct(p, u)
+    zx, zy = R.half_mesh(nf.zeta_x), R.half_mesh(nf.zeta_y)
+    steep = np.argsort((zx * zx + zy * zy).reshape(-1))[-40:]  # the steepest targets, and some others
+    rng = np.random.default_rng(3)
+    some = np.concatenate([steep, rng.choice((N - 1) * M, 60, replace=False)])
+    rows = np.unique([R.row_index(p, b, i // (N - 1), i % (N - 1)) for i in some for b in (1, 2)])
+    dp = bim.DeviceProblem(p)
+    ud = torch.as_tensor(u, device="cuda")
+    Fd = torch.empty_like(ud)
+    k, t = ctypes.c_double(), ctypes.c_double()
+    cfg = ctypes.byref(bim.PairConfig(1, 4, 0, chunks)) if chunks else None
+    assert bim.lib().bim_residual_timed(dp.ref(), ud.data_ptr(), Fd.data_ptr(), bim._PREC["fp64"], 1, cfg,
+                                        torch.cuda.current_stream().cuda_stream, ctypes.byref(k), ctypes.byref(t)) == 0
+    F = Fd.cpu().numpy()
+    assert np.isfinite(F).all()
+    err = np.abs(F[rows] - R.residual_rows(p, u, rows)) / R.term_magnitude_rows(p, u, rows)
+    print(N, M, "max slopes", np.abs(zx).max(), np.abs(zy).max(), "max rel err", err.max())
+    # along its valley a form is up to A + C times smaller than its terms, which hold the
+    # rounding of A, B, C (one unit each) and of the products (a few)
+    assert err.max() <= 1e-12 + 8 * 2.0 ** -52 * (2.0 + zx * zx + zy * zy).max()
+
+
 @pytest.mark.parametrize("name,mk,seed", CASES[:4], ids=[c[0] for c in CASES[:4]])
 def test_residual_fp32c_matches_oracle(bim, name, mk, seed):
     p = mk()
