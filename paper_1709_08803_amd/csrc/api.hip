@@ -111,7 +111,7 @@ static int residual_call(const bim_problem *prob, const double *u, double *F, in
     void *ws = nullptr;
     // (the tables of the linear sums in every size, so that any evaluation leaves a
     // workspace for a captured one of the same mesh)
-    const bool conv = linear && prec == BIM_FP64;
+    const bool conv = linear && prec == BIM_FP64 && lin_conv_applies(d, false);
     if ((rc = stream_workspace(s, residual_work_bytes(d, pl) + lin_table_bytes(d), &ws))) return rc;
     ResidualWork w;
     residual_work_carve(ws, d, pl, &w);

@@ -186,8 +186,10 @@ int residual_enqueue(const bim_problem *p, const double *u, double *F, int prec,
                      const PairLaunch &pl, const ResidualWork &w, hipStream_t s,
                      hipEvent_t *ev_pair = nullptr, int linear = 0, const double *lin_tables = nullptr);
 
-// The convolution form of the linear sums (linconv.hip): bytes of its tables, its
+// The convolution form of the linear sums (linconv.hip): whether it is the faster form for
+// the mesh (tables_kept: the tables serve many evaluations), bytes of its tables, its
 // source chunks (at most `most`), and its launch (D.chunks chunks into D.part).
+bool lin_conv_applies(const Dims &d, bool tables_kept);
 size_t lin_table_bytes(const Dims &d);
 int lin_conv_chunks(const Dims &d, int most);
 int lin_conv_enqueue(const PairDesc &D, const double *tables, hipStream_t s);

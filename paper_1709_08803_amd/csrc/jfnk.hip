@@ -322,7 +322,7 @@ int solve_impl(const bim_problem *p, const bim_precond *P, double *u_io, const b
     K.n = n;
     K.m = m;
     // one workspace sized for the larger chunk count of the two precisions
-    const bool lin_conv = linear_start_only && o->inner_prec == BIM_FP64;
+    const bool lin_conv = linear_start_only && o->inner_prec == BIM_FP64 && lin_conv_applies(d, true);
     const PairLaunch pl64 = o->inner_prec == BIM_FP64 ? pair_launch_for(p, BIM_FP64) : pair_launch_batch(p, BIM_FP64);
     const PairLaunch pl32 = pair_launch_for(p, BIM_FP32C);
     PairLaunch plw = pl64.chunks >= pl32.chunks ? pl64 : pl32;

@@ -226,6 +226,19 @@ int conv_targets(int N) {
 
 }  // namespace
 
+// A wave fills a window of 64 R + N entries for every pair of slices, however short these
+// are, where the pairwise form's work goes with nimg N^2: narrow meshes stay with that (whole
+// evaluation, pairwise / convolution in us, M = 900: half domain N = 3 60 / 583, 16 822 /
+// 898, 20 1308 / 995; full N = 16 438 / 899, 24 938 / 1121; M = 300: full N = 24 134 / 142,
+// 31 211 / 173).  So do meshes of few nodes, whose convolution is one chunk of launches and
+// latencies (N < 31: 24 x 31 42.6 / 45.1, 24 x 61 44.6 / 35.7; from 31 on the line is lower:
+// 66 x 3 20.3 / 23.5, 31 x 11 28.2 / 29.1, 31 x 12 29.3 / 29.4, 129 x 3 31.2 / 30.4, 40 x 12
+// 35.4 / 32.9, and the tables' launch, 2 to 3 us of it, is not paid again where they are kept).
+bool lin_conv_applies(const Dims &d, bool tables_kept) {
+    if ((long)d.nimg * d.N * d.N < 648) return false;
+    return d.N < 31 ? d.nnode >= 768 : tables_kept || d.nnode >= 372;
+}
+
 size_t lin_table_bytes(const Dims &d) {
     return ((sizeof(double) * 3 * (size_t)(2 * d.M - 1) * (d.N - 1)) + 255) & ~(size_t)255;
 }

@@ -405,3 +405,47 @@ def test_linear_convolutions_match_oracle(bim, N, M, half):
     err = (np.abs(F.cpu().numpy() - F_ref) / scale).max()
     print(f"{N}x{M}", err)
     assert err <= 1e-12
+
+
+# Beside the smallest meshes that are summed as convolutions (by nodes and by row length), and
+# the pairwise form on their other side
+@pytest.mark.parametrize("N,M,half", [(65, 6, True), (66, 6, False), (31, 12, True), (31, 11, True), (24, 32, True),
+                                      (24, 31, True), (26, 31, False), (25, 33, False), (18, 43, True), (17, 46, True)])
+def test_linear_sums_beside_the_convolution_line(bim, N, M, half):
+    from oracle import linear as Lin
+    x, y = (N - 1) / 6.0, (M - 1) / 3.0
+    p = W.make_problem(N, M, -x, x, 0.0 if half else -y, y, 0.8, [W.Bump(0.2, 1.1, 0.9, cx=0.3)], half_domain=half)
+    u = W.perturbed_state(p, 3)
+    F = bim.residual_linear(bim.DeviceProblem(p), torch.as_tensor(u, device="cuda"))
+    err = (np.abs(F.cpu().numpy() - Lin.F_lin(p, u)) / R.term_magnitude_rows(p, u)).max()
+    print(f"{N}x{M}", err)
+    assert err <= 1e-12
+
+
+def _best_us(fn, reps=20):
+    import time
+    fn()
+    best = float("inf")
+    for _ in range(5):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        for _ in range(reps):
+            fn()
+        torch.cuda.synchronize()
+        best = min(best, (time.perf_counter() - t) / reps * 1e6)
+    return best
+
+
+# On narrow meshes the convolution form took up to ten times the pairwise one (3 x 900: 583
+# against 60 us; F(u) itself takes 58)
+@pytest.mark.parametrize("N,M,half", [(3, 900, True), (5, 900, False), (8, 900, False)])
+def test_linear_residual_of_narrow_meshes_is_no_slower_than_the_nonlinear_one(bim, N, M, half):
+    L, Ly = (N - 1) / 2.0, float(M - 1)
+    p = W.make_problem(N, M, -L, L, 0 if half else -0.5 * Ly, Ly if half else 0.5 * Ly, 0.9, [W.Bump(0.2, 1.0, 1.0)],
+                       half_domain=half)
+    dp = bim.DeviceProblem(p)
+    u = torch.as_tensor(W.perturbed_state(p, 3), device="cuda")
+    out = torch.empty_like(u)
+    lin, non = _best_us(lambda: bim.residual_linear(dp, u, out=out)), _best_us(lambda: bim.residual(dp, u, out=out))
+    print(N, M, "linear", lin, "nonlinear", non)
+    assert lin <= 2.0 * non
