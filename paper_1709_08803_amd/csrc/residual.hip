@@ -1315,9 +1315,13 @@ PairDesc make_desc(const bim_problem *p, const Dims &d, const PairLaunch &pl, co
 // 10^7 targets times lattice nodes the segments' own launch and latency cost more
 // (whole evaluation, nodes / segments in us: 31 x 11 22 / 28, 61 x 21 34 / 36, 76 x 26 45 /
 // 48, 91 x 31 70 / 68, 121 x 41 156 / 137, 181 x 61 660 / 511; full 51 x 51 51 / 55,
-// 61 x 61 74.5 / 72.5, 101 x 101 358 / 302).
+// 61 x 61 74.5 / 72.5, 101 x 101 358 / 302).  A row costs its N nodes one way and two ends
+// and up to 17 nodes the other, so that the line rises as rows get shorter than about 45
+// (3 x 900 58 / 101, 8 x 900 277 / 337, 12 x 900 599 / 599, 16 x 300 139 / 148, 16 x 900 1042 / 979,
+// 24 x 121 63 / 68, 24 x 300 281 / 264, 31 x 121 93 / 90, 40 x 61 49 / 53, 50 x 61 67 / 66).
 static bool s2_by_nodes(const Dims &d, const bim_problem *p) {
-    return (double)d.nnode * d.nnode * d.nimg < 1.1e7 || p->dy > kS2Aspect * p->dx;
+    const double row = std::max(1.0, 45.0 / d.N);
+    return (double)d.nnode * d.nnode * d.nimg < 1.1e7 * row * row || p->dy > kS2Aspect * p->dx;
 }
 
 int residual_enqueue(const bim_problem *p, const double *u, double *F, int prec, const PairLaunch &pl,
