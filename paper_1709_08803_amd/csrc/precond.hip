@@ -399,8 +399,12 @@ int precond_build(const bim_problem *p, int hb, int storage, Precond **out, hipS
     // longer than the convolutions' launches and latencies (apply from blocks /
     // from tables, half domains: 61 x 21, 23 MB: 41 / 63 us; 91 x 31, 92 MB: 54 /
     // 72; 106 x 36, 172 MB: 110 / 79; 121 x 41, 293 MB: 122 / 90; 181 x 61, 1.36
-    // GB: 433 / 249; full 61 x 61, 158 MB: 76 / 75)
-    const bool tables = storage == BIM_STORE_FP64 && sizeof(double) * 4 * band_elems(M, h, s) >= (size_t)150000000;
+    // GB: 433 / 249; full 61 x 61, 158 MB: 76 / 75).  Not for fewer slices than s / 160: one
+    // workgroup per slice forms a3 (k_pc_a3), and few of them take longer over their s^2
+    // products than reading the blocks (apply from blocks / from tables: 1000 x 4 189 / 216,
+    // 900 x 4 172 / 188, 800 x 4 152 / 158; 700 x 6 152 / 150, 600 x 4 85 / 66, 1000 x 7 267 / 264).
+    const bool tables = storage == BIM_STORE_FP64 && 160L * M >= s &&
+                        sizeof(double) * 4 * band_elems(M, h, s) >= (size_t)150000000;
     pc->tables = tables;
     size_t extra = 0;
     if (tables) {

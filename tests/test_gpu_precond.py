@@ -265,3 +265,25 @@ def test_triangular_inverses_on_one_and_two_streams(bim, N, M):
     print(f"{N}x{M} |Pz - r| / |r|", np.abs(res).max() / np.abs(r).max())
     assert np.abs(res).max() <= 1e-9 * np.abs(r).max()
     P.close()
+
+
+# Few long slices keep the stored blocks (fewer than s / 160, where the one workgroup per slice
+# that forms a3 takes longer than reading them); both sides of the line, P z = r in the rows of
+# block 2 as for the other s > 192
+@pytest.mark.parametrize("N,M,tables", [(640, 4, False), (639, 4, True)])
+def test_tables_need_a_slice_per_160_rows(bim, N, M, tables):
+    p = W.make_problem(N, M, -(N - 1) / 6.0, (N - 1) / 6.0, 0.0, (M - 1) / 3.0, 1.2, [W.Bump(0.2, 1.0, 1.0)])
+    dp = bim.DeviceProblem(p)
+    P = bim.Preconditioner(dp)
+    s, w = N + 1, 2 * P.band + 1
+    stored = 8 * (4 * M * s * s + 4 * M * w * s * s + (M * s) ** 2 + 4 * M * s)  # the arrays of the blocks
+    assert (P.nbytes - stored >= 8 * (2 * N + 1) * s) == tables  # E and the node-value map of a slice
+    r = np.random.default_rng(9).standard_normal(p.n_unknowns)
+    z = P.apply(torch.as_tensor(r, device="cuda"))
+    torch.cuda.synchronize()
+    res = Lin.banded_matvec(p, z.cpu().numpy(), P.band) - r
+    nb = (N + 1) * M
+    blocks = [np.abs(res[b * nb:(b + 1) * nb]).max() / np.abs(r).max() for b in range(3)]
+    print(f"{N}x{M} |Pz - r| / |r| by block", blocks)
+    assert blocks[1] <= 1e-9
+    P.close()
