@@ -287,3 +287,22 @@ def test_tables_need_a_slice_per_160_rows(bim, N, M, tables):
     print(f"{N}x{M} |Pz - r| / |r| by block", blocks)
     assert blocks[1] <= 1e-9
     P.close()
+
+
+# Blocks longer than 192 rows are inverted as 2 x 2 block matrices, which pivot within their parts
+# only; that leaves 1e-8 to 6e-8 of r in the rows of blocks 1 and 3 of P z = r.  The bound is ten
+# times that: a wrong entry or a term left out of z1 or z3 is of the order of r.
+@pytest.mark.parametrize("N,M", [(257, 21), (300, 21), (600, 5)])
+def test_table_formed_apply_bounds_every_block_of_long_slices(bim, N, M):
+    p = W.make_problem(N, M, -(N - 1) / 6.0, (N - 1) / 6.0, 0.0, (M - 1) / 3.0, 1.2, [W.Bump(0.2, 1.0, 1.0)])
+    dp = bim.DeviceProblem(p)
+    P = bim.Preconditioner(dp)
+    r = np.random.default_rng(9).standard_normal(p.n_unknowns)
+    z = P.apply(torch.as_tensor(r, device="cuda"))
+    torch.cuda.synchronize()
+    res = Lin.banded_matvec(p, z.cpu().numpy(), P.band) - r
+    nb = (N + 1) * M
+    blocks = [np.abs(res[b * nb:(b + 1) * nb]).max() / np.abs(r).max() for b in range(3)]
+    print(f"{N}x{M} |Pz - r| / |r| by block", blocks)
+    assert max(blocks) <= 6e-7
+    P.close()
