@@ -132,6 +132,35 @@ def test_graph_replay_matches_eager_solve(bim):
     assert torch.equal(ua, ub)
 
 
+# The same for a mesh that takes the large-mesh kernels (n = 33306 > 4096: shift, multiple dot
+# products, update and norm in launches of their own with the column copied to the host; FP64:
+# S2 sums in their own launch, P applied from tables in groups of slices; mixed: FP32C sums,
+# FP32-stored P).  A step is launched at its first three uses, captured at the fourth and
+# replayed from then on; every cycle of `restart` = 4 iterations uses step 0, so that more than
+# 16 iterations use it at least five times.  The host's reductions, the residuals of the outer
+# iteration and (third run) new buffers lie between the replays.
+@pytest.mark.parametrize("inner,storage", [("fp64", "fp64"), ("fp32c", "fp32")])
+def test_graph_replay_of_large_mesh_steps_matches_eager(bim, inner, storage):
+    p = W.working(1.4)
+    dp = bim.DeviceProblem(p)
+    P = bim.Preconditioner(dp, storage=storage)
+    s = p.N + 1
+    assert p.n_unknowns > 4096 and 4 * 8 * p.M * (2 * P.band + 1) * s * s >= 150e6 and p.M >= 2 * (2 * P.band + 1)
+    u0 = bim.linear_start(dp, P)
+    runs = []
+    for graphs in (0, 1, 1):
+        u = u0.clone()
+        rep = bim.solve(dp, u, P, restart=4, max_restarts=40, ftol=1e-9, inner_prec=inner, use_graphs=graphs,
+                        check=False)
+        print(inner, graphs, rep["newton_iters"], rep["gmres_iters"], rep["fnorm_inf"])
+        assert rep["gmres_iters"] > 16
+        runs.append((u, rep))
+    for u, rep in runs[1:]:
+        assert torch.equal(u, runs[0][0])
+        assert rep["history"] == runs[0][1]["history"] and rep["gmres_iters"] == runs[0][1]["gmres_iters"]
+    P.close()
+
+
 # Vectors of n = 3 (N + 1) M entries around 1024, 2048 and 4096, where the orthogonalisation and
 # the step u + h v change between one entry per thread, two, four and many workgroups
 @pytest.mark.parametrize("N,M,n", [(30, 11, 1023), (17, 19, 1026), (21, 31, 2046), (35, 19, 2052), (64, 21, 4095),
