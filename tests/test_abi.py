@@ -43,3 +43,10 @@ def test_invalid_arguments_are_rejected_without_gpu(lib):
     lib.bim_last_error.restype = ctypes.c_char_p
     assert lib.bim_residual(None, None, None, 0, None) == -1
     assert b"NULL" in lib.bim_last_error()
+
+
+def test_host_functions_start_on_cache_lines(lib):
+    # the build's function alignment: without it the speed of host loops (a network's initial
+    # weights) hung on where the linker put their functions
+    off = {n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value % 64 for n in declared_functions()}
+    assert not any(off.values()), {n: o for n, o in off.items() if o}
