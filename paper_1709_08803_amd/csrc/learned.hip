@@ -51,6 +51,16 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
     return (uint16_t)(u >> 16);
 }
 
+// A ReLU's activation in bf16 that also tells whether its FP32 value was positive, which the
+// gradient's mask asks for: positive values that round to zero (below 4.6e-41) are held as
+// -0, the others that become zero as +0 (the products do not tell these apart).
+__device__ __forceinline__ uint16_t relu_bf(float v) {
+    if (v <= 0.f) return 0;
+    const uint16_t h = f2bf(v);
+    return h ? h : (uint16_t)0x8000u;
+}
+__device__ __forceinline__ bool relu_on(uint16_t h) { return h == 0x8000u || bf2f(h) > 0.f; }
+
 typedef short short8_t __attribute__((ext_vector_type(8)));
 
 __host__ __device__ __forceinline__ int pad16(int n) { return (n + 15) & ~15; }
@@ -218,14 +228,13 @@ __global__ __launch_bounds__(64) void k_conv(ConvArgs P) {
     for (int r = 0; r < 4; ++r) {
         const int m = rt * 16 + kq + r;
         if (m >= rows) break;
-        float v = acc[r] + bias;
-        if (v < 0.f) v = 0.f;
+        const uint16_t v = relu_bf(acc[r] + bias);
         if (P.out) {
-            P.out[(size_t)m * P.C + c] = f2bf(v);
+            P.out[(size_t)m * P.C + c] = v;
         } else {
             const int bb = m / npix, col = (m - bb * npix) * P.C + c;
-            P.outR[pk(bb, col, dkp)] = f2bf(v);
-            if (P.outT) P.outT[pk(col, bb, P.bp)] = f2bf(v);
+            P.outR[pk(bb, col, dkp)] = v;
+            if (P.outT) P.outT[pk(col, bb, P.bp)] = v;
         }
     }
 }
@@ -233,7 +242,7 @@ __global__ __launch_bounds__(64) void k_conv(ConvArgs P) {
 // A fully connected layer (or a backward product): result 32 rows x 16 columns per wave.
 // mode 0 hidden layer: bias, ReLU, bf16 by rows (kp ldk) and, training, by columns
 //      1 output layer: bias into Y; training (T): G = (Y - T) / (B n) and its bf16 copies
-//      2 gradient through a ReLU whose activations (by rows) are `act`: G and bf16 copies,
+//      2 gradient through a ReLU whose activations (relu_bf, by rows) are `act`: G and bf16 copies,
 //        rows split into `split` rows of cols / split columns (conv2's pixels)
 //      3 plain: G
 struct FcArgs {
@@ -266,12 +275,12 @@ __global__ __launch_bounds__(64) void k_fc(FcArgs P) {
             const size_t e = (size_t)(m + r) * P.cols + n;
             float v = acc[t][r] + bias;
             if (P.mode == 0) {
-                if (v < 0.f) v = 0.f;
+                v = bf2f(relu_bf(v));
             } else if (P.mode == 1) {
                 P.Y[e] = v;
                 if (P.T) P.G[e] = v = (v - P.T[e]) * P.inv;
             } else if (P.mode == 2) {
-                v = bf2f(P.act[pk(m + r, n, P.actkp)]) > 0.f ? v : 0.f;
+                v = relu_on(P.act[pk(m + r, n, P.actkp)]) ? v : 0.f;
                 P.G[e] = v;
             } else {
                 P.G[e] = v;
@@ -304,7 +313,7 @@ __global__ __launch_bounds__(64) void k_fc(FcArgs P) {
 }
 
 // Adjoint of the im2col of k_conv, through the ReLU of the layer below (its NHWC
-// activations): dX[b][iy][ix][c] = sum over the (oy, ox, ky, kx) that read it, and its
+// activations, relu_bf): dX[b][iy][ix][c] = sum over the (oy, ox, ky, kx) that read it, and its
 // bf16 copy by columns (zero rows behind the last).
 __global__ void k_col2im(const float *__restrict__ dcols, const uint16_t *__restrict__ act, float *__restrict__ dX,
                          uint16_t *__restrict__ dXT, int B, int H, int W, int Cin, int Ho, int Wo) {
@@ -332,7 +341,7 @@ __global__ void k_col2im(const float *__restrict__ dcols, const uint16_t *__rest
             v += dcols[r * 9L * Cin + (ky * 3 + kx) * Cin + c];
         }
     }
-    v = bf2f(act[e]) > 0.f ? v : 0.f;
+    v = relu_on(act[e]) ? v : 0.f;
     dX[e] = v;
     dXT[pk(c, row, rowsp)] = f2bf(v);
 }

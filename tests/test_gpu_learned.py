@@ -290,3 +290,27 @@ def test_training_step_edges_match_rounded_reference(bim, N, M, C1, C2, D3, lin,
                 e = float((torch.as_tensor(g).double() - r).abs().max() / (r.abs().max() + 1e-30))
                 print(N, M, B, "layer", l, e)
                 assert e < 2e-3
+
+
+# The ReLU masks are those of the FP32 values: 2e-41 is positive and rounds to zero in bf16, -0
+# and -2e-41 are not.  One hidden layer at a time gets zero weights and such biases; its own bias
+# gradients then are the column sums of what arrives from above, or zero.
+@pytest.mark.parametrize("layer", [0, 1, 2])
+def test_relu_masks_are_those_of_the_fp32_values(bim, layer):
+    N, M, B = 21, 9, 5
+    net = bim.LearnedNet(N, M, seed=3, max_batch=B, C1=8, C2=16, D3=24)
+    fan_out = [8, 16, 24, 2 * M * N]
+    X, f, T = _inputs(N, M, B, 4, net.in_channels)
+    Xd, fd, Td = _bf16_tensor(X), torch.as_tensor(f, device="cuda"), torch.as_tensor(T, device="cuda")
+    w = net.get(layer)[0]
+    for l in range(layer + 1, 3):  # the layers above pass gradients on even from a zero input
+        net.set(l, None, np.full(fan_out[l], 0.5, np.float32))
+    grads = {}
+    for name, b in (("one", 1.0), ("tiny", 2e-41), ("zero", -0.0), ("negative", -2e-41)):
+        net.set(layer, np.zeros_like(w), np.full(fan_out[layer], b, np.float32))
+        net.train_step(Xd, fd, Td, lr=0.0, update=False)
+        grads[name] = net.get(layer)[3].copy()
+    assert np.abs(grads["one"]).max() > 0
+    assert not grads["zero"].any() and not grads["negative"].any()
+    # the layers above see 0 instead of 1, so that only the mask can be compared
+    assert (grads["tiny"] != 0).sum() >= 0.2 * fan_out[layer]
