@@ -191,7 +191,10 @@ int bim_residual_timed(const bim_problem *prob, const double *u, double *F, int 
  * this mesh and precision (with u as the evaluation point), remembers the
  * fastest for all later calls in this process with the same (N, M,
  * half_domain, prec), and returns it in *best (host, may be NULL) with its
- * kernel time in *best_ms (host, may be NULL).  Synchronises the stream.
+ * kernel time in *best_ms (host, may be NULL).  In FP64 the kernels of a batch
+ * (and of the outer residual of a mixed-precision solve), which form the S2 sums
+ * with the pairs, are tuned beside those of one problem and keep a choice of
+ * their own; *best is that of one problem.  Synchronises the stream.
  */
 int bim_tune_residual(const bim_problem *prob, const double *u, int prec, void *stream,
                       bim_pair_config *best, double *best_ms);

@@ -128,19 +128,17 @@ int bim_residual_linear(const bim_problem *prob, const double *u, double *F, int
     return residual_call(prob, u, F, prec, stream, 1);
 }
 
-int bim_residual_timed(const bim_problem *prob, const double *u, double *F, int prec, int iters,
-                       const bim_pair_config *cfg, void *stream, double *kernel_ms, double *total_ms) {
+}  // extern "C"
+
+namespace bim {
+
+int residual_timed(const bim_problem *prob, const double *u, double *F, int prec, int iters, const PairLaunch &pl,
+                   hipStream_t s, double *kernel_ms, double *total_ms) {
     g_last_error.clear();
-    int rc = validate(prob);
-    if (rc) return rc;
-    if (!u || !F || u == F) return fail(BIM_EINVAL, "u and F must be distinct device pointers");
-    if (prec != BIM_FP64 && prec != BIM_FP32C) return fail(BIM_EINVAL, "unknown precision");
-    if (iters < 1 || !kernel_ms || !total_ms) return fail(BIM_EINVAL, "iters >= 1 and result pointers required");
-    hipStream_t s = (hipStream_t)stream;
     const Dims d(prob);
-    const PairLaunch pl = cfg ? pair_launch_cfg(d, prec, *cfg) : pair_launch_for(prob, prec);
     Scratch sc(s);
-    if ((rc = sc.alloc(residual_work_bytes(d, pl)))) return rc;
+    int rc = sc.alloc(residual_work_bytes(d, pl));
+    if (rc) return rc;
     ResidualWork w;
     residual_work_carve(sc.ptr, d, pl, &w);
     std::vector<hipEvent_t> ev(4 * (size_t)iters, nullptr);
@@ -170,7 +168,19 @@ int bim_residual_timed(const bim_problem *prob, const double *u, double *F, int 
     return BIM_OK;
 }
 
-}  // extern "C"
+}  // namespace bim
+
+extern "C" int bim_residual_timed(const bim_problem *prob, const double *u, double *F, int prec, int iters,
+                                  const bim_pair_config *cfg, void *stream, double *kernel_ms, double *total_ms) {
+    g_last_error.clear();
+    int rc = validate(prob);
+    if (rc) return rc;
+    if (!u || !F || u == F) return fail(BIM_EINVAL, "u and F must be distinct device pointers");
+    if (prec != BIM_FP64 && prec != BIM_FP32C) return fail(BIM_EINVAL, "unknown precision");
+    if (iters < 1 || !kernel_ms || !total_ms) return fail(BIM_EINVAL, "iters >= 1 and result pointers required");
+    const PairLaunch pl = cfg ? pair_launch_cfg(Dims(prob), prec, *cfg) : pair_launch_for(prob, prec);
+    return residual_timed(prob, u, F, prec, iters, pl, (hipStream_t)stream, kernel_ms, total_ms);
+}
 
 // ------------------------------------------------------------------ allocation-free residual
 namespace bim {

@@ -124,6 +124,9 @@ PairLaunch pair_launch_for(const bim_problem *p, int prec);
 // the single solve and the lockstep one share that arithmetic; it evaluates
 // the outer residual a handful of times (181 x 61: 0.1 ms of 75 each).
 PairLaunch pair_launch_batch(const bim_problem *p, int prec);
+// `iters` evaluations with this launch, as bim_residual_timed.
+int residual_timed(const bim_problem *p, const double *u, double *F, int prec, int iters, const PairLaunch &pl,
+                   hipStream_t s, double *kernel_ms, double *total_ms);
 // Chunks giving every work item about pairs_target pairs per collocation
 // point (node ranges of pairs_target / nimg nodes), to even out work items
 // across the meshes of a batch.

@@ -1,5 +1,7 @@
 // Autotuner for the all-pairs launch shape: times every supported variant on
-// the caller's mesh and keeps the fastest per (N, M, half_domain, precision).
+// the caller's mesh and keeps the fastest per (N, M, half_domain, precision) and, in FP64,
+// form of the kernel: with the S2 sums formed on their own (one problem) or with the
+// pairs (a batch and the mixed solves' outer residual), whose fastest shapes differ.
 #include <hip/hip_runtime.h>
 
 #include <map>
@@ -12,7 +14,7 @@
 namespace bim {
 
 namespace {
-using Key = std::tuple<int, int, int, int>;
+using Key = std::tuple<int, int, int, int, bool>;  // last: FP64 with the S2 sums formed with the pairs
 std::mutex g_mu;
 std::map<Key, bim_pair_config> g_best;
 }  // namespace
@@ -54,9 +56,9 @@ PairLaunch pair_launch_cfg(const Dims &d, int prec, const bim_pair_config &cfg) 
     return pair_launch(d, cfg.targets_per_lane, cfg.unroll, chunks);
 }
 
-static bool tuned_launch(const bim_problem *p, int prec, bim_pair_config *cfg) {
+static bool tuned_launch(const bim_problem *p, int prec, bool s2_with_pairs, bim_pair_config *cfg) {
     std::lock_guard<std::mutex> lk(g_mu);
-    auto it = g_best.find(Key(p->N, p->M, p->half_domain ? 1 : 0, prec));
+    auto it = g_best.find(Key(p->N, p->M, p->half_domain ? 1 : 0, prec, s2_with_pairs && prec == BIM_FP64));
     if (it == g_best.end()) return false;
     *cfg = it->second;
     return true;
@@ -65,7 +67,7 @@ static bool tuned_launch(const bim_problem *p, int prec, bim_pair_config *cfg) {
 PairLaunch pair_launch_for(const bim_problem *p, int prec) {
     const Dims d(p);
     bim_pair_config cfg;
-    if (tuned_launch(p, prec, &cfg)) return pair_launch_cfg(d, prec, cfg);
+    if (tuned_launch(p, prec, false, &cfg)) return pair_launch_cfg(d, prec, cfg);
     // untuned defaults, the fastest shapes measured: FP64 4-way unroll, two rows per
     // lane on a full domain of some size, where the shared record work is half of a
     // pair's (151 x 151: 1242 us with one row, 1119 with two; 71 x 71: 109 / 106; 41 x 41:
@@ -79,7 +81,7 @@ PairLaunch pair_launch_for(const bim_problem *p, int prec) {
 PairLaunch pair_launch_batch(const bim_problem *p, int prec) {
     const Dims d(p);
     bim_pair_config cfg;
-    if (!tuned_launch(p, prec, &cfg)) {
+    if (!tuned_launch(p, prec, true, &cfg)) {
         cfg = {1, prec == BIM_FP32C ? 2 : 4, 0, 0};
         // about 24 waves per SIMD in FP64, the best count of these kernels at 181 x 61
         if (prec == BIM_FP64) cfg.chunks = chunks_for_waves(d, 1, 4, 24576);
@@ -104,37 +106,44 @@ extern "C" int bim_tune_residual(const bim_problem *prob, const double *u, int p
     double *F = nullptr;
     if ((rc = hip_check(hipMallocAsync((void **)&F, sizeof(double) * d.nvec, s), "hipMallocAsync"))) return rc;
     // every variant at its default chunk count and those giving 8 to 48 waves per SIMD
-    // (1024 SIMDs)
-    std::vector<bim_pair_config> cands;
-    for (int tpl : {1, 2})
-        for (int unr : {2, 4, 8})
-            for (long want : {0L, 8192L, 16384L, 24576L, 32768L, 49152L}) {
-                const int chunks = want ? pair_launch(d, tpl, unr, chunks_for_waves(d, tpl, unr, want)).chunks
-                                        : pair_launch_cfg(d, prec, {tpl, unr, 0, 0}).chunks;
-                bim_pair_config c{tpl, unr, 0, chunks};
-                bool dup = false;
-                for (auto &o : cands)
-                    dup |= (o.targets_per_lane == tpl && o.unroll == unr && o.chunks == chunks);
-                if (!dup) cands.push_back(c);
+    // (1024 SIMDs); the form with the pairs at 24 and 32, its best counts (a batch takes only the
+    // variant from the choice)
+    const int forms = prec == BIM_FP64 ? 2 : 1;
+    bim_pair_config pick[2] = {};
+    double pick_ms[2] = {1e30, 1e30};
+    for (int f = 0; f < forms && !rc; ++f) {
+        std::vector<bim_pair_config> cands;
+        const std::vector<long> wants = f ? std::vector<long>{24576, 32768}
+                                          : std::vector<long>{0, 8192, 16384, 24576, 32768, 49152};
+        for (int tpl : {1, 2})
+            for (int unr : {2, 4, 8})
+                for (long want : wants) {
+                    const int chunks = want ? pair_launch(d, tpl, unr, chunks_for_waves(d, tpl, unr, want)).chunks
+                                            : pair_launch_cfg(d, prec, {tpl, unr, 0, 0}).chunks;
+                    bim_pair_config c{tpl, unr, 0, chunks};
+                    bool dup = false;
+                    for (auto &o : cands)
+                        dup |= (o.targets_per_lane == tpl && o.unroll == unr && o.chunks == chunks);
+                    if (!dup) cands.push_back(c);
+                }
+        for (auto &c : cands) {
+            PairLaunch pl = pair_launch_cfg(d, prec, c);
+            pl.s2_with_pairs = f == 1;
+            double kms = 0, tms = 0;
+            if ((rc = residual_timed(prob, u, F, prec, 3, pl, s, &kms, &tms))) break;
+            if (kms < pick_ms[f]) {
+                pick_ms[f] = kms;
+                pick[f] = c;
             }
-    bim_pair_config pick = cands[0];
-    double pick_ms = 1e30;
-    for (auto &c : cands) {
-        double kms = 0, tms = 0;
-        rc = bim_residual_timed(prob, u, F, prec, 3, &c, stream, &kms, &tms);
-        if (rc) break;
-        if (kms < pick_ms) {
-            pick_ms = kms;
-            pick = c;
         }
     }
     (void)hipFreeAsync(F, s);
     if (rc) return rc;
     {
         std::lock_guard<std::mutex> lk(g_mu);
-        g_best[Key(prob->N, prob->M, prob->half_domain ? 1 : 0, prec)] = pick;
+        for (int f = 0; f < forms; ++f) g_best[Key(prob->N, prob->M, prob->half_domain ? 1 : 0, prec, f == 1)] = pick[f];
     }
-    if (best) *best = pick;
-    if (best_ms) *best_ms = pick_ms;
+    if (best) *best = pick[0];
+    if (best_ms) *best_ms = pick_ms[0];
     return BIM_OK;
 }

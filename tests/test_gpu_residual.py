@@ -468,3 +468,22 @@ def test_residual_fp64_of_short_rows_keeps_near_the_fp32c_one(bim, N, M):
     t64, t32 = _best_us(lambda: bim.residual(dp, u, out=out)), _best_us(lambda: bim.residual(dp, u, "fp32c", out=out))
     print(N, M, "fp64", t64, "fp32c", t32)
     assert t64 <= 1.35 * t32
+
+
+def test_tuned_batch_and_single_launches_match_oracle(bim):
+    # FP64 tunes the kernels of one problem and those of a batch separately; each then runs its own
+    # choice (a batch takes that of its largest problem)
+    ps = [W.make_problem(45, 15, -12, 12, 0, 6, 0.9, [W.Bump(0.25, 1.3, 0.9)]),
+          W.make_problem(31, 13, -10, 10, -6, 6, 1.2, [W.Bump(0.2, 1.0, 1.0, cy=1.5)], half_domain=False)]
+    us = [W.perturbed_state(p, 5) for p in ps]
+    dps = [bim.DeviceProblem(p) for p in ps]
+    uds = [torch.as_tensor(u, device="cuda") for u in us]
+    before = [F.cpu().numpy() for F in bim.residual_batched(dps, uds, "fp64")]
+    for dp, u in zip(dps, uds):
+        best, ms = bim.tune_residual(dp, u, "fp64")
+        assert best[0] in (1, 2) and best[1] in (2, 4, 8) and ms > 0
+    after = [F.cpu().numpy() for F in bim.residual_batched(dps, uds, "fp64")]
+    for i, (p, u) in enumerate(zip(ps, us)):
+        ref, scale = R.residual(p, u), R.term_magnitude_rows(p, u)
+        for F in (before[i], after[i], bim.residual(dps[i], uds[i]).cpu().numpy()):
+            assert (np.abs(F - ref) / scale).max() <= 1e-12
