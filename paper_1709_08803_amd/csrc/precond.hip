@@ -403,40 +403,8 @@ int precond_build(const bim_problem *p, int hb, int storage, Precond **out, hipS
     // workgroup per slice forms a3 (k_pc_a3), and few of them take longer over their s^2
     // products than reading the blocks (apply from blocks / from tables: 1000 x 4 189 / 216,
     // 900 x 4 172 / 188, 800 x 4 152 / 158; 700 x 6 152 / 150, 600 x 4 85 / 66, 1000 x 7 267 / 264).
-    const bool tables = storage == BIM_STORE_FP64 && 160L * M >= s &&
-                        sizeof(double) * 4 * band_elems(M, h, s) >= (size_t)150000000;
-    pc->tables = tables;
-    size_t extra = 0;
-    if (tables) {
-        pc->groups = precond_groups(M, h, s);
-        extra = precond_tables(pc, p, nullptr);
-        if (pc->groups > 1 && hipMalloc(&pc->mem, pers + extra) != hipSuccess) {  // no room for more than one
-            (void)hipGetLastError();
-            pc->mem = nullptr;
-            pc->groups = 1;
-            extra = precond_tables(pc, p, nullptr);
-        }
-    }
-    pers += extra;
-    pc->bytes = pers;
-    int rc = BIM_OK;
-    if (!pc->mem && (rc = hip_check(hipMalloc(&pc->mem, pers), "hipMalloc(preconditioner)"))) {
-        delete pc;
-        return rc;
-    }
-    DevArena ar{(char *)pc->mem, 0, pers};
-    pc->Dinv11 = ar.take<double>(band_elems(M, 0, s));
-    pc->Dinv22 = ar.take<double>(band_elems(M, 0, s));
-    pc->E = ar.take<double>(band_elems(M, 0, s));
-    pc->B21 = ar.take<double>(band_elems(M, h, s));
-    pc->B23 = ar.take<double>(band_elems(M, h, s));
-    pc->B31 = ar.take<double>(band_elems(M, h, s));
-    pc->G = ar.take<double>(band_elems(M, h, s));
-    pc->Sinv = ar.take<double>((size_t)n * n);
-    pc->Uinv = ar.take<double>(band_elems(M, 0, s));
-    pc->scratch = ar.take<double>((size_t)4 * n);
-    if (tables) precond_tables(pc, p, &ar);
-
+    bool tables = storage == BIM_STORE_FP64 && 160L * M >= s &&
+                  sizeof(double) * 4 * band_elems(M, h, s) >= (size_t)150000000;
     // setup-only scratch
     size_t tmp = 0;
     auto addt = [&](size_t bytes) { tmp += (bytes + 255) & ~(size_t)255; };
@@ -460,12 +428,42 @@ int precond_build(const bim_problem *p, int hb, int storage, Precond **out, hipS
     addt(sizeof(GemmTriItemF) * 2 * M);      // the same in FP32
     addt(sizeof(InvItem) * (M + 4));
     addt(sizeof(GemmKItem) * (size_t)M * (2 * w2 + 1));
+
+    // Both allocations, in the fastest form that there is room for: tables with the triangular
+    // products in groups, in one group, the blocks alone.
     void *tbase = nullptr;
-    rc = hip_check(hipMallocAsync(&tbase, tmp, st), "hipMallocAsync(preconditioner setup)");
+    int rc = BIM_OK;
+    for (int groups = tables ? precond_groups(M, h, s) : 1;;) {
+        pc->tables = tables;
+        pc->groups = groups;
+        pc->bytes = pers + (tables ? precond_tables(pc, p, nullptr) : 0);
+        rc = hip_check(hipMalloc(&pc->mem, pc->bytes), "hipMalloc(preconditioner)");
+        if (!rc && (rc = hip_check(hipMallocAsync(&tbase, tmp, st), "hipMallocAsync(preconditioner setup)"))) {
+            (void)hipFree(pc->mem);
+            pc->mem = nullptr;
+        }
+        if (rc != BIM_ENOMEM || !tables) break;
+        (void)hipGetLastError();
+        (void)fail(BIM_OK, "");
+        if (groups > 1) groups = 1;
+        else tables = false;
+    }
     if (rc) {
-        precond_free(pc);
+        delete pc;
         return rc;
     }
+    DevArena ar{(char *)pc->mem, 0, pc->bytes};
+    pc->Dinv11 = ar.take<double>(band_elems(M, 0, s));
+    pc->Dinv22 = ar.take<double>(band_elems(M, 0, s));
+    pc->E = ar.take<double>(band_elems(M, 0, s));
+    pc->B21 = ar.take<double>(band_elems(M, h, s));
+    pc->B23 = ar.take<double>(band_elems(M, h, s));
+    pc->B31 = ar.take<double>(band_elems(M, h, s));
+    pc->G = ar.take<double>(band_elems(M, h, s));
+    pc->Sinv = ar.take<double>((size_t)n * n);
+    pc->Uinv = ar.take<double>(band_elems(M, 0, s));
+    pc->scratch = ar.take<double>((size_t)4 * n);
+    if (tables) (void)precond_tables(pc, p, &ar);
     DevArena ta{(char *)tbase, 0, tmp};
     double *D11 = ta.take<double>((size_t)3 * s * s);
     double *D12 = D11 + (size_t)s * s;
