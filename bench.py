@@ -13,7 +13,8 @@ this workload: 0.55 ms per evaluation over the first evaluations from idle,
 0.504 ms once warm).  With the solver legs (the
 default) the GPU is busy for seconds before the warm-up starts.
 
-Also reported: the FP32-compensated evaluation, the all-pairs kernel's
+Also reported (`--report FILE` writes every figure, the printed line holds the
+main ones): the FP32-compensated evaluation, the all-pairs kernel's
 roofline fraction from HIP events on the launch stream, the time to a converged
 solve (preconditioner setup, linear start and JFNK with FP64 or FP32-compensated
 inner sums and an FP64- or FP32-stored preconditioner, with the distance between
@@ -141,8 +142,8 @@ def time_to_solution(B, W, np, torch, froude, ftol=1e-10, max_newton=15, problem
         t_lin = time.perf_counter() - t0
         # timed with events on the current stream; the rate is that of the stored
         # arrays read once each (P.nbytes less the 4 n FP64 apply scratch), and there
-        # is none where FP64 storage holds 150 MB of band blocks: banded products
-        # then come from kernel tables and the triangular ones read part of the arrays
+        # is none where P holds kernel tables beside them: banded products then come
+        # from the tables and the triangular ones read part of the arrays
         r = torch.ones(dp.n, dtype=torch.float64, device="cuda")
         z = torch.empty_like(r)
         for _ in range(3):
@@ -156,7 +157,9 @@ def time_to_solution(B, W, np, torch, froude, ftol=1e-10, max_newton=15, problem
         apply_ms = e0.elapsed_time(e1) / 20
         n, s = dp.n // 3, dp.n // 3 // p.M
         apply_bytes = P.nbytes - 4 * 8 * n
-        if storage == "fp64" and 4 * 8 * p.M * (2 * P.band + 1) * s * s >= 150e6:
+        elem = 8 if storage == "fp64" else 4
+        blocks = elem * (4 * p.M * s * s + 4 * p.M * (2 * P.band + 1) * s * s + n * n)
+        if apply_bytes - blocks >= elem * (2 * p.N + 1) * s:  # the smallest of the tables' arrays
             apply_bytes = None
         res[f"precond_{storage}"] = {"setup_ms": t_setup * 1e3, "linear_start_ms": t_lin * 1e3,
                                      "linear_start_prec": lprec, "linear_start_rtol": lrtol,
@@ -328,6 +331,50 @@ def node_values(p, u, f):
     return blk[:, :1] + np.concatenate([np.zeros((p.M, 1)), np.cumsum(steps, axis=1)], axis=1)
 
 
+def headline(out):
+    """The printed line: the contract's keys, the roofline and a few figures of each leg, in
+    five digits (the whole report is tens of kilobytes; lines that long have been cut)."""
+    def short(x):
+        if isinstance(x, float):
+            return float(f"{x:.5g}")
+        if isinstance(x, dict):
+            return {k: short(v) for k, v in x.items()}
+        return [short(v) for v in x] if isinstance(x, (list, tuple)) else x
+
+    def solution(r):
+        row = {"froude": r["froude"]}
+        for leg in ("fp64", "fp32c"):
+            row[leg] = {k: r[leg][k] for k in ("status", "total_ms", "newton", "gmres")}
+            if "max_dzeta_vs_oracle" in r[leg]:
+                row[leg]["max_dzeta_vs_oracle"] = r[leg]["max_dzeta_vs_oracle"]
+        for st in ("fp64", "fp32"):
+            row[f"precond_{st}"] = {k: r[f"precond_{st}"][k] for k in ("setup_ms", "linear_start_ms", "apply_ms")}
+        if "speedup_fp32c_total" in r:
+            row["speedup_fp32c_total"] = r["speedup_fp32c_total"]
+        return row
+
+    line = {k: v for k, v in out.items() if k not in ("time_to_solution", "time_to_solution_extended_domain",
+                                                      "time_to_solution_full_domain", "sweep", "exact_linear",
+                                                      "learned_start_121x41")}
+    if "time_to_solution" in out:
+        line["time_to_solution"] = [solution(r) for r in out["time_to_solution"]]
+        for dom in ("extended", "full"):
+            line[f"time_to_solution_{dom}_domain"] = solution(out[f"time_to_solution_{dom}_domain"])
+    if "sweep" in out:
+        line["sweep"] = {k: out["sweep"]["sweep"][k] for k in (
+            "precond_setup_s", "linear_starts_s", "batched_solve_s", "converged", "newton_total", "gmres_total")}
+        for k in ("batched_residual_fp64", "batched_residual_fp32c"):
+            line["sweep"][k + "_ms"] = out["sweep"][k]["ms"]
+    if "exact_linear" in out:
+        line["exact_linear"] = {m["name"]: {"total_ms": m["total_ms"], "contract_tflops": m["contract_tflops"]}
+                                for m in out["exact_linear"]["meshes"]}
+    if "learned_start_121x41" in out:
+        line["learned_start_121x41"] = out["learned_start_121x41"]["summary"]
+    full = short(line)
+    full["value"], full["ms_per_step"] = out["value"], out["ms_per_step"]
+    return full
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -338,6 +385,8 @@ def main():
     ap.add_argument("--no-sweep", action="store_true", help="skip the 64-instance batched sweep")
     ap.add_argument("--no-exact", action="store_true", help="skip the exact linear solution legs")
     ap.add_argument("--no-learned", action="store_true", help="skip the learned-start leg (trains a network, ~1 min)")
+    ap.add_argument("--report", metavar="FILE", help="write every figure of the run to FILE (JSON); the printed line "
+                                                     "holds the main ones")
     ap.add_argument("--copy-calibration", type=int, default=0, metavar="MB",
                     help="first run a plain elementwise copy of MB megabytes (reads MB, writes MB), "
                          "the reference for scaling hardware byte counters")
@@ -454,7 +503,10 @@ def main():
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(p, u_host)
         progress("CPU baseline")
-    print(json.dumps(out))
+    if args.report:
+        with open(args.report, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(headline(out)))
 
 
 if __name__ == "__main__":
