@@ -487,3 +487,77 @@ def test_tuned_batch_and_single_launches_match_oracle(bim):
         ref, scale = R.residual(p, u), R.term_magnitude_rows(p, u)
         for F in (before[i], after[i], bim.residual(dps[i], uds[i]).cpu().numpy()):
             assert (np.abs(F - ref) / scale).max() <= 1e-12
+
+
+def _bie_rows_extended(p, u, which, idx):
+    """Boundary-integral rows `idx` of one boundary ("S" or "B") in extended precision: the oracle's
+    steps with every value in numpy's long double."""
+    E = np.longdouble
+    N, M, dx, dy = p.N, p.M, E(p.dx), E(p.dy)
+    x, y = E(p.x1) + dx * np.arange(N), E(p.y1) + dy * np.arange(M)
+
+    def field(f):
+        blk = u[f * (N + 1) * M:(f + 1) * (N + 1) * M].reshape(M, N + 1).astype(E)
+        inc = 0.5 * dx * (blk[:, 1:-1] + blk[:, 2:])
+        return blk[:, :1] + np.concatenate([np.zeros((M, 1), E), np.cumsum(inc, axis=1)], axis=1), blk[:, 1:]
+
+    (zeta, zx), (phi, _), (psi, _) = field(0), field(1), field(2)
+    zy = np.empty_like(zeta)
+    zy[1:-1] = (zeta[2:] - zeta[:-2]) / (2 * dy)
+    zy[-1] = (3 * zeta[-1] - 4 * zeta[-2] + zeta[-3]) / (2 * dy)
+    zy[0] = 0 if p.half_domain else (-3 * zeta[0] + 4 * zeta[1] - zeta[2]) / (2 * dy)
+    b, bx, by = (a.astype(E) for a in (p.beta, p.beta_x, p.beta_y))
+    end = lambda n: np.where((np.arange(n) == 0) | (np.arange(n) == n - 1), E(0.5), E(1))
+    w = dx * dy * end(M)[:, None] * end(N)[None]
+    layers = (("S", zeta, zx, zy, phi - x, zx, 1), ("B", b, bx, by, psi - x, bx, -1))
+    _, a, ax, ay, D, sig, sign = layers["SB".index(which)]
+    mid = lambda g, l, k: 0.5 * (g[l, k] + g[l, k + 1])
+    out = []
+    for i in idx:
+        l, k = divmod(int(i), N - 1)
+        xs, ys, d, Ds, gx, gy = x[k] + 0.5 * dx, y[l], mid(a, l, k), mid(D, l, k), mid(ax, l, k), mid(ay, l, k)
+        ss = sign * mid(sig, l, k)
+        A, B, C = 1 + gx * gx, 2 * gx * gy, 1 + gy * gy
+        v = E(0)
+        for image in (1, -1) if p.half_domain else (1,):
+            s, t = (x - xs)[None], (image * y - ys)[:, None]
+            for name, h, hx, hy, Dn, sn, sg in layers:
+                dz = h - d
+                ri = 1 / np.sqrt(s * s + t * t + dz * dz)
+                v += (sg * w * ((Dn - (Ds if name == which else 0)) * (dz - s * hx - image * t * hy) * ri ** 3
+                                + sn * ri)).sum()
+            v -= ss * (w / np.sqrt(A * s * s + B * s * t + C * t * t)).sum()
+
+        def G(s, t):
+            Q = A * s * s + B * s * t + C * t * t
+            g = t / np.sqrt(A) * np.log(2 * A * s + B * t + 2 * np.sqrt(A * Q)) if t != 0 else E(0)
+            return g + (s / np.sqrt(C) * np.log(2 * C * t + B * s + 2 * np.sqrt(C * Q)) if s != 0 else E(0))
+
+        s1, s2, t1, t2 = x[0] - xs, x[-1] - xs, (-y[-1] if p.half_domain else y[0]) - ys, y[-1] - ys
+        v += ss * (G(s2, t2) - G(s1, t2) - G(s2, t1) + G(s1, t1)) - E("6.283185307179586476925287") * Ds
+        out.append(v)
+    return np.array(out)
+
+
+@pytest.mark.parametrize("N,M,half", [(31, 11, True), (61, 21, True), (70, 40, False)])
+def test_fp64_rows_are_no_further_from_extended_precision_than_the_batched_ones(bim, N, M, half):
+    # a row's error is mostly the rounding of node values; the one-launch form of one problem forms
+    # them in its own order, the batched kernels in that of a plain scan
+    p = W.working(0.7, N=N, M=M) if half else W.make_problem(N, M, -10, 20, -10, 10, 0.7, [W.Bump(0.2, 1.0, 1.0)],
+                                                             half_domain=False)
+    dp = bim.DeviceProblem(p)
+    err = {"single": [], "batched": []}
+    for seed in range(5):
+        u = W.perturbed_state(p, seed)
+        ud = torch.as_tensor(u, device="cuda")
+        F = {"single": bim.residual(dp, ud).cpu().numpy(), "batched": bim.residual_batched([dp], [ud])[0].cpu().numpy()}
+        for block, which in ((1, "S"), (2, "B")):
+            idx = np.random.default_rng(seed).choice((N - 1) * M, 60, replace=False)
+            ref = _bie_rows_extended(p, u, which, idx)
+            rows = [R.row_index(p, block, i // (N - 1), i % (N - 1)) for i in idx]
+            for k in F:
+                err[k] += [float(e) for e in F[k][rows] - ref]
+    rms = {k: float(np.sqrt(np.mean(np.square(v)))) for k, v in err.items()}
+    print(N, M, rms)
+    assert rms["batched"] < 1e-12  # the reference is the same system
+    assert rms["single"] <= rms["batched"]
