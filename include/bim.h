@@ -211,10 +211,12 @@ int bim_tune_residual(const bim_problem *prob, const double *u, int prec, void *
  *   Newton step fall several-fold for a modest rise in setup and apply cost;
  *   beyond 10 slices the setup grows faster than the solve shrinks).
  * precond_setup factors P on the device and returns a library-owned handle
- * (free with precond_destroy).  It synchronises `stream`; part of the work runs
- * on a second stream of its own (default priority), joined before it returns,
- * so it must not be called under stream capture.  Device memory used:
- * precond_bytes().  Requires N + 1 <= 1024.  Returns BIM_EDOMAIN if a block
+ * (free with precond_destroy).  It synchronises `stream`; for (N + 1) M > 3072
+ * (and FP32 storage with 128 < N + 1 <= 384) part of the work runs on a second
+ * stream of its own (default priority), joined before it returns.  It must not
+ * be called under stream capture.  Device memory used: precond_bytes(); where
+ * memory is short it holds less and applies more slowly (the tables and copied
+ * blocks of the FP64 apply are left out).  Requires N + 1 <= 1024.  Returns BIM_EDOMAIN if a block
  * that must be inverted is singular.
  * precond_apply enqueues z = P^-1 r (device vectors of 3(N+1)M, z must not
  * alias r).  Applies on one handle share its scratch: do not overlap them.

@@ -172,7 +172,8 @@ struct ResidualWork {
     float *tg32;     // [7][2 ntg] FP32 copies for the FP32C kernel
     void *srcS;      // SrcRec<T>[nnode]
     void *srcB;      // SrcRec<T>[nnode]
-    double *part;    // [chunks][2 ntg][2]
+    double *part;    // [chunks][2 ntg][2]; one problem's FP64 sums: [chunks][2 ntg] of the pairs and
+                     // behind them [S2 chunks][2 ntg], S2 chunks <= chunks
     double *scal;    // [4] device scalars (h, norms)
     size_t bytes;
 };

@@ -92,7 +92,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     // product is a clamped one that only feeds outputs that are not stored, and B rows
     // past K are zeroed when staged (the select sits there so that no load waits for
     // its value).  A step inside a K-block loads at a uniform base and fixed 32-bit
-    // offsets (64 rows of A, 16 of B; far below 4 GB apart).
+    // offsets: m rows of A, m at most a block's 1024 and lda at most n, so below 4 GB for
+    // any n whose n x n inverses fit the memory (n < 190,000); one row of B.
     double ra[4], rb[4];
     const int ac = tid & 15;
     unsigned oa[4];
@@ -501,9 +502,9 @@ __global__ __launch_bounds__(64 * RT) void k_gemm_tri(const GemmTriItemT<T> *__r
 #pragma unroll
             for (int u = 0; u < NB; ++u) acc[u] = MF::step(a, b[u], acc[u]);
             __builtin_amdgcn_sched_barrier(0);
-            // behind the first MFMAs: step k0 + 32 (loaded during the previous step)
+            // behind the first MFMAs: step k0 + TK (loaded during the previous step)
             // into the other buffer, last read before the barrier that ended that
-            // step, then the loads of step k0 + 64
+            // step, then the loads of step k0 + 2 TK
             if (kk == 0 && k0 + TK < k) store(buf ^ 1, k0 + TK);
             if (kk == 4 && k0 + 2 * TK < k) load(k0 + 2 * TK);
             __builtin_amdgcn_sched_barrier(0);

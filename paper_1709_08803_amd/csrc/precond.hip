@@ -301,9 +301,8 @@ static int precond_round_to_fp32(Precond *pc, hipStream_t st) {
     return rc;
 }
 
-// Tables, stacked slice blocks and scratch of the single-problem FP64 apply.
-// The number of groups of slices in which that apply takes the products with L^-1
-// and V^-1.  L and V are block-banded (half-width 2h), so that only the diagonal
+// The number of groups of slices in which the single-problem FP64 apply takes the products
+// with L^-1 and V^-1.  L and V are block-banded (half-width 2h), so that only the diagonal
 // groups of the inverses need be read,
 //   y_k = (L^-1)_kk (x_k - L_k,k-1 y_k-1),
 // with the 2h (2h + 1) / 2 blocks of L (or V) between neighbouring groups beside
@@ -332,7 +331,8 @@ static int precond_groups(int M, int h, int s) {
     return best;
 }
 
-// Sizes of the tables' arrays (with `ar`, also their places in it): the total in bytes.
+// Tables, stacked slice blocks and scratch of the single-problem FP64 apply: sizes of their
+// arrays (with `ar`, also their places in it), and the total in bytes.
 // They lie in the operator's own allocation (a second one of this size costs the
 // setup and the release 0.3 ms).
 static size_t precond_tables(Precond *pc, const bim_problem *p, DevArena *ar) {
@@ -670,7 +670,9 @@ int precond_build(const bim_problem *p, int hb, int storage, Precond **out, hipS
         // events takes 0.25 ms of the host and two waits per step, more than the few us
         // per row that the overlap hides.  Two streams / one: 31 x 11 0.76 / 0.53 ms,
         // 61 x 21 1.77 / 1.46, 91 x 31 (n = 2852) 4.3 / 3.6; 106 x 36 (n = 3852) 6.2 /
-        // 5.8 in FP64 but 6.6 / 12 in FP32, 121 x 41 8.6 / 8.6.
+        // 5.8 in FP64 but 6.6 / 12 in FP32, 121 x 41 8.6 / 8.6.  Long slices the same, as their
+        // inversions are few: 191 x 16 4.91 / 4.59, 150 x 20 4.63 / 4.34, 300 x 10 5.67 / 5.41,
+        // 31 x 95 5.75 / 4.91, 121 x 25 4.17 / 3.77.
         const bool one_stream = !bw32 && n <= 3072;
         const int far = 1 << 29;  // an offset that leaves klo at 0 / khi at nk
         const size_t lrow = (size_t)s * w2 * s;  // elements of one block row of L (or V)
