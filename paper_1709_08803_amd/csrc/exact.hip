@@ -735,8 +735,8 @@ extern "C" int bim_exact_linear(double froude, const bim_bump *bumps, int nbumps
     const int tiles_i = (N + 63) / 64, tiles_j = (M + jt - 1) / jt, tiles = tiles_i * tiles_j;
     const long steps_total = (long)nbumps * (L.qpad / kStep);
     // node chunks: two workgroups to a compute unit, 512 at a time, in whole rounds (281 x
-    // 281, 15 tiles: 34 chunks, one round, 0.96 ms; 35 chunks 1.39; 137 chunks, about 2048
-    // workgroups, 1.07; total with the reduction at 96 x 96, 2 tiles: 255 chunks 0.21 ms, 891 0.40);
+    // 281, 15 tiles: 34 chunks, one round, 0.98 ms; 35 chunks 1.44; 137 chunks, about 2048
+    // workgroups, 1.02; total with the reduction at 96 x 96, 2 tiles: 255 chunks 0.21 ms, 891 0.25);
     // few tiles fit one round, many take the number of rounds (up to 4) they fill best
     long chunks = (cfg.workgroups + tiles - 1) / tiles;
     if (cfg.workgroups <= 0) {

@@ -585,6 +585,7 @@ static int stage_out(LgNet *net, const HostPart *part, int n, hipStream_t s) {
             const int words = (int)((len + 15) / 16);  // arrays are padded to 256 bytes
             hipLaunchKernelGGL(k_to_host, dim3(std::min(cdiv(words, 256), 256)), dim3(256), 0, s, (const uint4 *)(lo + at),
                                (uint4 *)(net->stage + (i & 1) * kStage), words);
+            if ((rc = hip_check(hipGetLastError(), "copy launch"))) return rc;
             if ((rc = hip_check(hipEventRecord(net->ev[i & 1], s), "hipEventRecord"))) return rc;
         }
         if (i == 0) continue;

@@ -268,7 +268,7 @@ __device__ __forceinline__ Two wave_scan(Two v) {
 // l.  Its y-differences need the node values of three rows of zeta and phi; each
 // workgroup integrates those (7 slices with psi's) into LDS itself, which takes less
 // than a second launch (bound by latency; 31 x 11: 2.8 + 3.9 -> 5.0 us; 181 x 61: 5.1 + 5.5 ->
-// 9.3 us, and the gap between the launches).
+// 9.5 us, and the gap between the launches).
 __global__ __launch_bounds__(256) void k_prepare64(PairDesc D) {
     extern __shared__ double val[];  // [7][N]: zeta and phi on rows base .. base + 2, psi on row l
     const int N = D.N, M = D.M, l = blockIdx.x;
@@ -749,9 +749,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<T
 // six corrections leave 1e-13 of one end's term and 1.5e-15 of the sum, and three
 // suffice from 32 on.  The segments' integrals are (1/sqrt A) ln of a ratio; a
 // wave multiplies the ratios of 16 rows before it takes a logarithm.
-// A target costs about 15 thousand FP64 instructions instead of the 220 thousand of
-// its 22082 pairs at 181 x 61 (launches of the sums 613 -> 486 us; full 151 x 151
-// 1570 -> 1120).
+// A target costs about 16 thousand FP64 instructions (29 thousand in all) instead of the 220
+// thousand of its 22082 pairs at 181 x 61 (launches of the sums by HIP events 613 -> 495 us;
+// full 151 x 151 1570 -> 1142).
 constexpr double kS2Reach = 8.0;   // node-by-node distance, in dx
 constexpr int kS2Flush = 16;       // rows per logarithm, fewer where their product passes kS2Wide
 // Range of the products: numerators and denominators of a row are 1 or more and the
